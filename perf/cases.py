@@ -292,7 +292,7 @@ def tolerance(case):
     if c["kind"] == "prefill":
         return {"rel": 2.5e-7, "max": 2e-6, "differ": 5e-6}
     if c["kind"] == "prompt":
-        return {"rel": 1e-5, "max": 1e-4, "differ": 1e-5}
+        return {"rel": 1e-5, "max": 1e-4, "differ": 1e-4}    # (one word of a small prompt is 1e-5 of them)
     # float32 sums and the float32 inclusion probability (measured 0.6e-6 to 2e-6 from 64 bits); codes are exact
     return {"rel": 1e-5, "max": 1e-4, "differ": 0.0}
 
