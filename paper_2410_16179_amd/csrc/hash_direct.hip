@@ -1,7 +1,7 @@
 // Direct SimHash coding with an exact fallback (Sec. 2.2; Algorithm 1 "Encode").
 //
-// Used for the decode queries (a few thousand projections), for float32 inputs, and as the
-// reference-accurate path for bf16 keys when the matrix-core kernel cannot be used.  A
+// hash_rows_kernel: the decode queries and the few keys a step appends (bf16 and float32).
+// hash_direct_kernel: bf16 keys when the matrix-core kernel's list of undecided pairs overflowed.  A
 // projection is accumulated in float64 from exact products (hash_rows_kernel: in float32
 // first, float64 only where the float32 error bound leaves the sign open); results inside
 // the float64 error bound are re-summed exactly (exact_dot.h), so the bits do not depend on
@@ -39,7 +39,6 @@ __device__ inline void load_x8(const HashDirectArgs& a, int64_t idx, float (&v)[
 
 // One wavefront codes two vectors at a time: lanes 0..31 take tables 32w..32w+31 of the
 // first, lanes 32..63 of the second; a ballot turns the 64 sign tests into two code words.
-template <bool FP32>
 __global__ __launch_bounds__(256) void hash_direct_kernel(HashDirectArgs a) {
   __shared__ long long limbs[4][kLimbs];
   if (a.run_flag && *a.run_flag == 0) return;
@@ -78,16 +77,12 @@ __global__ __launch_bounds__(256) void hash_direct_kernel(HashDirectArgs a) {
       float wf[kHeadDim], xf[kHeadDim];
 #pragma unroll
       for (int i = 0; i < kHeadDim; ++i) {
-        if constexpr (FP32) {
-          wf[i] = reinterpret_cast<const float*>(a.W)[(int64_t)i * ncol + j];
-        } else {
-          wf[i] = __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(a.W)[(int64_t)i * ncol + j] << 16);
-        }
+        wf[i] = __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(a.W)[(int64_t)i * ncol + j] << 16);
       }
 #pragma unroll
       for (int i = 0; i < kHeadDim; i += 8) {
         float v[8];
-        load_x8<FP32>(a, xbase + i, v);
+        load_x8<false>(a, xbase + i, v);
 #pragma unroll
         for (int e = 0; e < 8; ++e) xf[i + e] = v[e];
       }
@@ -118,8 +113,8 @@ __global__ __launch_bounds__(256) void hash_direct_kernel(HashDirectArgs a) {
       const float* smu = a.mu ? a.mu + su * kHeadDim : nullptr;
       const bool r = exact_sign_nonneg_wave(
           limbs[wave],
-          [&](int d) { return load_x_elem<FP32>(a, xb + d); },
-          [&](int d) { return load_elem<FP32>(a.W, (int64_t)d * ncol + sj); },
+          [&](int d) { return load_x_elem<false>(a, xb + d); },
+          [&](int d) { return load_elem<false>(a.W, (int64_t)d * ncol + sj); },
           [&](int d) { return smu ? (double)smu[d] : 0.0; }, smu != nullptr);
       if (lane == src) bit = r;
       pending &= pending - 1;
@@ -501,8 +496,7 @@ hipError_t launch_hash_direct(const HashDirectArgs& a, hipStream_t s) {
   // behind the matrix-core path the kernel normally only reads its flag and leaves: a capped
   // grid keeps that cheap, and the groups are walked in a loop if it does have to run
   const unsigned nx = (unsigned)(a.run_flag && groups > 2048 ? 2048 : groups);
-  if (a.is_fp32) hipLaunchKernelGGL(hash_direct_kernel<true>, dim3(nx, ny), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(hash_direct_kernel<false>, dim3(nx, ny), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(hash_direct_kernel, dim3(nx, ny), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

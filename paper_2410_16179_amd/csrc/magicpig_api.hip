@@ -415,7 +415,11 @@ int magicpig_hash_keys(const magicpig_params* p, const void* K_cache, const floa
     const hipError_t e = mp::launch_hash_rows(a, nullptr, stream);
     return e == hipSuccess ? MAGICPIG_OK : fail_hip(e);
   }
-  if (p->dtype == MAGICPIG_BF16) {
+  if (p->dtype == MAGICPIG_FP32) {
+    const hipError_t e = mp::launch_hash_keys_f32(a, p->batch * p->n_kv_heads, stream);
+    return e == hipSuccess ? MAGICPIG_OK : fail_hip(e);
+  }
+  {
     // matrix-core path; the direct kernel runs afterwards only if its list overflowed
     const HashWs wl = ws_hash_layout(p);
     char* wsb = reinterpret_cast<char*>(workspace);

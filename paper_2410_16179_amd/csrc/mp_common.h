@@ -245,6 +245,7 @@ constexpr int kFusedIters = 8;             // its gather batch: rows per quarter
 // host-side launchers (defined next to their kernels)
 hipError_t launch_hash_direct(const HashDirectArgs& a, hipStream_t s);
 hipError_t launch_hash_rows(const HashDirectArgs& a, const HashDirectArgs* b, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+hipError_t launch_hash_keys_f32(const HashDirectArgs& a, int units, hipStream_t s);
 hipError_t launch_hash_keys_mfma(const HashMfmaArgs& a, hipStream_t s);
 hipError_t launch_key_mean(const MeanArgs& a, hipStream_t s);
 hipError_t launch_prepare_projector(const void* W, void* prepared, int K, int L, hipStream_t s);
