@@ -1,15 +1,14 @@
 // Direct SimHash coding with an exact fallback (Sec. 2.2; Algorithm 1 "Encode").
 //
 // hash_rows_kernel: the decode queries and the few keys a step appends (bf16 and float32).
-// hash_direct_kernel: bf16 keys when the matrix-core kernel's list of undecided pairs overflowed.  A
+// finish_hash_keys_kernel: what the matrix-core key hashing leaves over (bf16 keys).  A
 // projection is accumulated in float64 from exact products (hash_rows_kernel: in float32
 // first, float64 only where the float32 error bound leaves the sign open); results inside
 // the float64 error bound are re-summed exactly (exact_dot.h), so the bits do not depend on
 // summation order.
 #include <type_traits>
 #include "mp_common.h"
-#include "exact_dot.h"
-#include "device_utils.h"
+#include "recheck_pairs.h"
 #include <hip/hip_bf16.h>
 #include <hip/hip_ext.h>
 
@@ -39,16 +38,11 @@ __device__ inline void load_x8(const HashDirectArgs& a, int64_t idx, float (&v)[
 
 // One wavefront codes two vectors at a time: lanes 0..31 take tables 32w..32w+31 of the
 // first, lanes 32..63 of the second; a ballot turns the 64 sign tests into two code words.
-__global__ __launch_bounds__(256) void hash_direct_kernel(HashDirectArgs a) {
-  __shared__ long long limbs[4][kLimbs];
-  if (a.run_flag && *a.run_flag == 0) return;
+__device__ inline void hash_direct(const HashDirectArgs& a, long long (*limbs)[kLimbs]) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  if (lane < kLimbs) limbs[wave][lane] = 0;
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __builtin_amdgcn_wave_barrier();
 
   const int half = lane >> 5, beta = lane & 31;
-  // workgroups walk the groups of eight vectors (one step unless the grid was capped)
+  // workgroups walk the groups of eight vectors
   for (int64_t grp = blockIdx.x; grp * 8 < a.total_rows; grp += gridDim.x) {
   const int64_t row0 = (grp * 4 + wave) * 2;
   if (row0 >= a.total_rows) continue;
@@ -128,12 +122,10 @@ __global__ __launch_bounds__(256) void hash_direct_kernel(HashDirectArgs a) {
   auto store_key_word = [&](int x, uint32_t word) {
     if (beta == 0 && row_ok) kdst[slot_in_block(a.NW, x, (int)(key % kBlockKeys))] = word;
   };
-  // blockIdx.y walks the items of a vector - its plane words, and for keys the densely packed
-  // last table group as one item - so that the few vectors of a small call are spread over
-  // the chip.
+  // the items of a vector: its plane words, and for keys the densely packed last table group as one
   const int xs = a.query_layout ? a.NQ : tail_begin(a.K, a.L);
   const int nitems = a.query_layout ? a.NQ : xs + 1;
-  for (int it = blockIdx.y; it < nitems; it += gridDim.y) {
+  for (int it = 0; it < nitems; ++it) {
     if (it < xs) {
       const uint32_t word = plane(it);
       if (a.query_layout) {
@@ -152,6 +144,27 @@ __global__ __launch_bounds__(256) void hash_direct_kernel(HashDirectArgs a) {
     }
   }
   }
+}
+
+// Behind the matrix-core key hashing: re-evaluates the pairs that did not fit a workgroup's own list
+// (normally none), or, if the global list overflowed too, codes every key of the call in float64.  As a
+// rule it reads two words and ends: one launch of few workgroups.
+__global__ __launch_bounds__(256) void finish_hash_keys_kernel(HashMfmaArgs m, HashDirectArgs a) {
+  __shared__ long long limbs[4][kLimbs];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const uint64_t listed = *m.list_count;
+  const bool redo = *m.overflow != 0;
+  if (!redo && listed == 0) return;
+  if (lane < kLimbs) limbs[wave][lane] = 0;
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  if (redo) {
+    hash_direct(a, limbs);
+    return;
+  }
+  const uint64_t count = listed < m.list_cap ? listed : m.list_cap;
+  recheck_pairs<16>(m, limbs[wave], count, ((uint64_t)blockIdx.x * 4 + wave) * 4, (uint64_t)gridDim.x * 16,
+                    [&](uint64_t i) { return m.list[i]; });
 }
 
 // Coding of a few vectors: the queries of a decode step (Algorithm 1 "Encode(q, W)") or the
@@ -488,15 +501,8 @@ hipError_t launch_hash_rows(const HashDirectArgs& a, const HashDirectArgs* b, hi
   return hipGetLastError();
 }
 
-hipError_t launch_hash_direct(const HashDirectArgs& a, hipStream_t s) {
-  if (a.total_rows <= 0) return hipSuccess;
-  const int64_t groups = (a.total_rows + 7) / 8;
-  // few vectors (queries): one workgroup per (8 vectors, word); many (keys): words looped
-  const unsigned ny = groups >= 4096 ? 1u : (unsigned)(a.query_layout ? a.NQ : tail_begin(a.K, a.L) + 1);
-  // behind the matrix-core path the kernel normally only reads its flag and leaves: a capped
-  // grid keeps that cheap, and the groups are walked in a loop if it does have to run
-  const unsigned nx = (unsigned)(a.run_flag && groups > 2048 ? 2048 : groups);
-  hipLaunchKernelGGL(hash_direct_kernel, dim3(nx, ny), dim3(256), 0, s, a);
+hipError_t launch_finish_hash_keys(const HashMfmaArgs& m, const HashDirectArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL(finish_hash_keys_kernel, dim3(4 * kNumCU), dim3(256), 0, s, m, a);
   return hipGetLastError();
 }
 

@@ -6,7 +6,7 @@
 // operand, so an accumulator register of a lane holds one (projection, key) pair with
 // lane%32 = key: the 32 sign bits of a code word are assembled inside one lane with one
 // funnel shift per element and no cross-lane traffic.  Rows of the A operand are
-// arranged (prep_projector_kernel) so that the two lane halves of two consecutive MFMA
+// arranged (prep_hash_keys_kernel) so that the two lane halves of two consecutive MFMA
 // tiles produce two complete code words; one half-swap then gives every lane the four
 // words of "its" key and a wavefront stores a contiguous kilobyte of the code layout.
 //
@@ -18,11 +18,10 @@
 // by Cauchy-Schwarz.
 // Elements with |acc| <= bound_i (a few in ten thousand) are listed in LDS and re-evaluated
 // at the end of the workgroup in float64 with the exact fallback of exact_dot.h, which
-// patches the bit.  Pairs beyond the LDS list go to a global list and recheck_kernel; if that
-// overflows too, a flag makes the direct float64 kernel redo the whole call.
+// patches the bit.  Pairs beyond the LDS list go to a global list and finish_hash_keys_kernel
+// (hash_direct.hip); if that overflows too, that kernel redoes the whole call in float64.
 #include "mp_common.h"
-#include "exact_dot.h"
-#include "device_utils.h"
+#include "recheck_pairs.h"
 
 namespace mp {
 
@@ -42,183 +41,92 @@ __host__ __device__ inline void tile_row_to_bit(int T, int rho, int* x, int* bet
   *beta = 31 - (16 * (T & 1) + r);
 }
 
-// A-operand fragments, transposed bf16 copy of W for the recheck, norm of every projector
-// column (by tile row).  One thread per (tile row, 8-element piece of d).  Also clears the
-// counters the later kernels of the call add to.
-__global__ __launch_bounds__(256) void prep_projector_kernel(HashMfmaArgs a) {
-  const int gid = blockIdx.x * 256 + threadIdx.x;
-  if (gid == 0) {
-    *a.list_count = 0u;
-    *a.overflow = 0;
-    *a.flagged_total = 0u;
-    *a.wmax_bits = 0u;                                   // largest column norm: raised by the threshold kernel
-  }
-  const int row = gid >> 4, piece = gid & 15;        // row = T*32 + rho
-  if (row >= a.ntiles * 32) return;
-  const int T = row >> 5, rho = row & 31;
-  int x, beta;
-  tile_row_to_bit(T, rho, &x, &beta);
-  const int t = 32 * (x / a.K) + beta;
-  const bool real = x < a.NQ && t < a.L;
-  const int j = real ? t * a.K + x % a.K : 0;
+// One launch prepares a call.
+// The first `proj_blocks` workgroups (16 tile rows each): A-operand fragments, transposed bf16 copy
+// of W for the recheck, largest column norm of the 16 rows.  One thread per (tile row, 8-element piece
+// of d).  The first also clears the counters the later kernels of the call add to.
+// The others, 256 projector columns of one (batch, KV head) each: initial accumulators -fl(mu.W_j) in
+// fragment order, the same sums in float64, |mu|.  A thread takes a column, neighbouring threads
+// neighbouring columns, so that W is read in whole lines as it is stored.  (As two launches, the second
+// reading the transposed copy row by row, they took 4.8 + 9.4 us.)
+__global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int proj_blocks, int thr_blocks) {
+  __shared__ float smax[4];
+  const int tid = threadIdx.x;
   const int ncol = a.K * a.L;
   const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
-  uint16_t v[8];
-  float ss = 0.f;
+  if ((int)blockIdx.x < proj_blocks) {
+    const int gid = blockIdx.x * 256 + tid;
+    if (gid == 0) {
+      *a.list_count = 0u;
+      *a.overflow = 0;
+      *a.flagged_total = 0u;
+    }
+    const int row = gid >> 4, piece = gid & 15;        // row = T*32 + rho  (ntiles is a multiple of four: no partial workgroup)
+    const int T = row >> 5, rho = row & 31;
+    int x, beta;
+    tile_row_to_bit(T, rho, &x, &beta);
+    const int t = 32 * (x / a.K) + beta;
+    const bool real = x < a.NQ && t < a.L;
+    const int j = real ? t * a.K + x % a.K : 0;
+    uint16_t v[8];
+    float ss = 0.f;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    v[e] = real ? W[(int64_t)(piece * 8 + e) * ncol + j] : (uint16_t)0;
-    const float f = __uint_as_float((uint32_t)v[e] << 16);
-    ss += f * f;
+    for (int e = 0; e < 8; ++e) {
+      v[e] = real ? W[(int64_t)(piece * 8 + e) * ncol + j] : (uint16_t)0;
+      const float f = __uint_as_float((uint32_t)v[e] << 16);
+      ss += f * f;
+    }
+    // fragment order: k-step s = piece/2, lane = (piece%2)*32 + rho, eight bf16 per lane
+    const int s = piece >> 1, lane = (piece & 1) * 32 + rho;
+    uint4 pk;
+    pk.x = v[0] | ((uint32_t)v[1] << 16); pk.y = v[2] | ((uint32_t)v[3] << 16);
+    pk.z = v[4] | ((uint32_t)v[5] << 16); pk.w = v[6] | ((uint32_t)v[7] << 16);
+    reinterpret_cast<uint4*>(a.afrag)[((int64_t)T * 8 + s) * 64 + lane] = pk;
+    if (real) reinterpret_cast<uint4*>(a.wt)[(int64_t)j * 16 + piece] = pk;
+    ss = wave_max(row_sum16(ss));                      // the 16 pieces of a row sit in one DPP row; padding rows: 0
+    if ((tid & 63) == 0) smax[tid >> 6] = ss;
+    __syncthreads();
+    if (tid == 0) a.rownorm[blockIdx.x] = sqrtf(fmaxf(fmaxf(smax[0], smax[1]), fmaxf(smax[2], smax[3]))) * 1.000001f;
+    return;
   }
-  // fragment order: k-step s = piece/2, lane = (piece%2)*32 + rho, eight bf16 per lane
-  const int s = piece >> 1, lane = (piece & 1) * 32 + rho;
-  uint4 pk;
-  pk.x = v[0] | ((uint32_t)v[1] << 16); pk.y = v[2] | ((uint32_t)v[3] << 16);
-  pk.z = v[4] | ((uint32_t)v[5] << 16); pk.w = v[6] | ((uint32_t)v[7] << 16);
-  reinterpret_cast<uint4*>(a.afrag)[((int64_t)T * 8 + s) * 64 + lane] = pk;
-  if (real) reinterpret_cast<uint4*>(a.wt)[(int64_t)j * 16 + piece] = pk;
-  ss = row_sum16(ss);                                  // the 16 pieces of a row sit in one DPP row
-  if (piece == 0) a.rownorm[row] = sqrtf(ss) * 1.000001f;   // 0 for padding rows
-}
-
-// Per (batch, KV head): initial accumulators -fl(mu.W_j) in fragment order, and |mu|.
-__global__ __launch_bounds__(256) void prep_threshold_kernel(HashMfmaArgs a) {
-  const int unit = blockIdx.y;
-  const int row = blockIdx.x * 256 + threadIdx.x;
+  const int at = (int)blockIdx.x - proj_blocks;
+  const int unit = at / thr_blocks;
   const float* mu = a.mu ? a.mu + (int64_t)unit * kHeadDim : nullptr;
-  if (row == 0) {
+  if (at % thr_blocks == 0 && tid < 64) {
     double ss = 0.0;
-    if (mu) for (int d = 0; d < kHeadDim; ++d) ss += (double)mu[d] * (double)mu[d];
-    a.munorm[unit] = (float)sqrt(ss) * 1.000001f;
+    if (mu) {
+      const double m0 = (double)mu[tid], m1 = (double)mu[tid + 64];
+      ss = m0 * m0 + m1 * m1;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    if (tid == 0) a.munorm[unit] = (float)sqrt(ss) * 1.000001f;
   }
-  if (row >= a.ntiles * 32) return;
-  // the largest column norm of the projector, once per call (non-negative floats order like integers)
-  if (unit == 0) atomicMax(a.wmax_bits, __float_as_uint(a.rownorm[row]));
-  const int T = row >> 5, rho = row & 31;
-  int x, beta;
-  tile_row_to_bit(T, rho, &x, &beta);
-  const int t = 32 * (x / a.K) + beta;
-  const bool real = x < a.NQ && t < a.L;
+  // column i of the whole table groups (32 K columns each), then the words that pad the last quad
+  const int i = at % thr_blocks * 256 + tid;
+  if (i >= a.ntiles * 32) return;
+  const bool grouped = i < 32 * a.NQ;
+  const int w = i / (32 * a.K), rem = i % (32 * a.K);
+  const int x = grouped ? w * a.K + rem % a.K : i >> 5, beta = grouped ? rem / a.K : i & 31;
   float c = -INFINITY;                                 // pad rows: never >= 0, never flagged
-  if (real) {
-    const int j = t * a.K + x % a.K;
+  if (i < ncol) {                                      // (i is the projector column itself)
     double th = 0.0, mg = 0.0;
     if (mu) {
-      const uint16_t* wt = reinterpret_cast<const uint16_t*>(a.wt) + (int64_t)j * kHeadDim;
+#pragma unroll 32
       for (int d = 0; d < kHeadDim; ++d) {
-        const double pm = (double)mu[d] * (double)__uint_as_float((uint32_t)wt[d] << 16);   // exact
+        const double pm = (double)mu[d] * (double)__uint_as_float((uint32_t)W[(uint32_t)d * (uint32_t)ncol + (uint32_t)i] << 16);   // exact
         th += pm;
         mg += fabs(pm);
       }
     }
     c = 0.0f - (float)th;                              // +0 when the threshold is zero
     // for the exact re-evaluation: the same sum in float64 and a float32 upper bound of its magnitude sum
-    a.thr64[(int64_t)unit * a.K * a.L + j] = th;
-    a.magmu[(int64_t)unit * a.K * a.L + j] = (float)mg * 1.000001f;
+    a.thr64[(int64_t)unit * ncol + i] = th;
+    a.magmu[(int64_t)unit * ncol + i] = (float)mg * 1.000001f;
   }
-  const int eta = (rho >> 2) & 1, r = 4 * (rho >> 3) + (rho & 3);
-  a.thr[(((int64_t)unit * a.ntiles + T) * 2 + eta) * 16 + r] = c;
-}
-
-// Float64 / exact re-evaluation of listed (key, projection) pairs, for one wavefront: pairs
-// first, first + step, ... below count, 64/LPP of them per sweep (step = 64/LPP * wavefronts).
-// LPP lanes share a pair (128/LPP elements each, read in 16-byte pieces from the key row and
-// from the transposed projector row); their float64 partial sums are combined by shuffles.
-// Any summation order is covered by the float64 error bound; what it cannot decide is summed
-// exactly.  The bit is then set or cleared in the stored code word.
-// List entry: unit (16 bits) | key (32 bits) | code word x (11 bits) | bit of the word (5 bits).
-template <int LPP, class GetEntry>
-__device__ inline void recheck_pairs(const HashMfmaArgs& a, long long* limb, uint64_t count,
-                                     uint64_t first, uint64_t step, GetEntry get) {
-  constexpr int kPieces = 16 / LPP;                      // 8-element pieces per lane
-  const int lane = threadIdx.x & 63;
-  const uint16_t* Kc = reinterpret_cast<const uint16_t*>(a.Kc);
-  const uint16_t* WT = reinterpret_cast<const uint16_t*>(a.wt);
-  const int grp = lane / LPP, sl = lane % LPP;
-  for (uint64_t i0 = first; i0 < count; i0 += step) {
-    const uint64_t i = i0 + grp;
-    const bool on = i < count;
-    const unsigned long long e = get(on ? i : i0);
-    const int x = (int)((e >> 5) & 0x7ff), tbit = (int)(e & 31);
-    const int j = (32 * (x / a.K) + tbit) * a.K + x % a.K;
-    const int64_t unit = (int64_t)(e >> 48);
-    const int64_t k = (int64_t)((e >> 16) & 0xffffffffull);
-    const int ub = (int)unit / a.n_kv_heads, uh = (int)unit % a.n_kv_heads;
-    const int64_t xoff = (int64_t)ub * a.stride_b + (int64_t)uh * a.stride_h + k * a.stride_n;
-    // Products of two bf16 values are exact in float32; they are added in float64 (at most 128
-    // roundings of 2^-53 of the magnitude sum) and the centering term mu.W_j comes ready-made in
-    // float64 from the threshold kernel, with the same kind of error on its own magnitude sum:
-    // |s - exact| < 2^-45 (sum|k w| + sum|mu w|).  The magnitude sums are float32 upper bounds.
-    uint4 kraw[kPieces], wraw[kPieces];
-#pragma unroll
-    for (int p = 0; p < kPieces; ++p) {
-      const int d0 = (p * LPP + sl) * 8;
-      if (a.kv_fp8) {                                    // e4m3 bytes, widened to the same values in bf16
-        const uint2 r8 = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(a.Kc) + xoff + d0);
-        kraw[p] = fp8x8_to_bf16x8(r8.x, r8.y);
-      } else {
-        kraw[p] = *reinterpret_cast<const uint4*>(Kc + xoff + d0);
-      }
-      wraw[p] = *reinterpret_cast<const uint4*>(WT + (int64_t)j * kHeadDim + d0);
-    }
-    double s = 0.0;
-    float magf = 0.f;
-#pragma unroll
-    for (int p = 0; p < kPieces; ++p) {
-      const uint32_t ku[4] = {kraw[p].x, kraw[p].y, kraw[p].z, kraw[p].w};
-      const uint32_t wu[4] = {wraw[p].x, wraw[p].y, wraw[p].z, wraw[p].w};
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const float p0 = __uint_as_float(ku[t] << 16) * __uint_as_float(wu[t] << 16);                 // exact
-        const float p1 = __uint_as_float(ku[t] & 0xffff0000u) * __uint_as_float(wu[t] & 0xffff0000u);   // exact
-        s += (double)p0;
-        s += (double)p1;
-        magf += fabsf(p0);
-        magf += fabsf(p1);
-      }
-    }
-#pragma unroll
-    for (int o = LPP / 2; o > 0; o >>= 1) {
-      s += __shfl_xor(s, o);
-      magf += __shfl_xor(magf, o);
-    }
-    double mag = (double)(magf * 1.0001f);
-    if (a.mu) {
-      s -= a.thr64[unit * (a.K * a.L) + j];
-      mag += (double)a.magmu[unit * (a.K * a.L) + j];
-    }
-    bool bit = s >= 0.0;
-    // (1e-42: float32 products below 2^-126 are rounded to multiples of 2^-149; 128 of them)
-    const bool unsure = on && sl == 0 && mag > 0.0 && fabs(s) <= kF64Slack * mag + 1e-42;
-    uint64_t pending = __ballot(unsure);
-    while (pending) {
-      const int src = __ffsll((unsigned long long)pending) - 1;
-      const int64_t sx = ((int64_t)__shfl((int)(xoff >> 32), src) << 32) | (uint32_t)__shfl((int)(xoff & 0xffffffff), src);
-      const int sj = __shfl(j, src);
-      const int64_t su = ((int64_t)__shfl((int)(unit >> 32), src) << 32) | (uint32_t)__shfl((int)(unit & 0xffffffff), src);
-      const float* smu = a.mu ? a.mu + su * kHeadDim : nullptr;
-      const bool r = exact_sign_nonneg_wave(
-          limb,
-          [&](int d) {
-            return a.kv_fp8 ? (double)fp8_to_float(reinterpret_cast<const uint8_t*>(a.Kc)[sx + d])
-                            : (double)__uint_as_float((uint32_t)Kc[sx + d] << 16);
-          },
-          [&](int d) { return (double)__uint_as_float((uint32_t)WT[(int64_t)sj * kHeadDim + d] << 16); },
-          [&](int d) { return smu ? (double)smu[d] : 0.0; }, smu != nullptr);
-      if (lane == src) bit = r;
-      pending &= pending - 1;
-    }
-    if (on && sl == 0) {
-      int kword, kbit;
-      key_bit_position(a.K, a.L, x, tbit, &kword, &kbit);
-      const uint32_t mask = 1u << kbit;
-      uint32_t* word = a.codes + (unit * a.blocks_cap + k / kBlockKeys) * (kBlockKeys * (int64_t)a.NW) +
-                       slot_in_block(a.NW, kword, (int)(k % kBlockKeys));
-      if (bit) atomicOr(word, mask);
-      else atomicAnd(word, ~mask);
-    }
-  }
+  // word x, bit beta: tile 2 (x / 2) + el / 16, lane half x % 2, register el % 16, el = 31 - beta
+  const int el = 31 - beta, T = 2 * (x >> 1) + (el >> 4);
+  a.thr[(((int64_t)unit * a.ntiles + T) * 2 + (x & 1)) * 16 + (el & 15)] = c;
 }
 
 // One pair of tiles (2 tiles x 8 k-steps x 64 lanes x 16 bytes = 16 KB of fragments), global -> LDS
@@ -253,11 +161,11 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   const bool wave_on = cb * kBlockKeys < last;
   if (tid == 0) sCount = 0;
 
-  const int nquads = a.ntiles / 4;                       // the fragment array holds whole quads
+  const int q0 = a.part_begin[blockIdx.z], nquads = a.part_begin[blockIdx.z + 1];   // quads of this workgroup
   const uint4* gA = reinterpret_cast<const uint4*>(a.afrag);
   const float* gThr = a.thr + (int64_t)unit * a.ntiles * 32;
-  stage_pair(gA, sA0, tid, wave);
-  if (tid < 128) sThr[0][tid] = gThr[tid];
+  stage_pair(gA + (int64_t)q0 * 2 * 1024, sA0, tid, wave);
+  if (tid < 128) sThr[q0 & 1][tid] = gThr[q0 * 128 + tid];
 
   // ---- B operand: my 64 keys, resident in registers for the whole kernel ----
   const uint16_t* Kc = reinterpret_cast<const uint16_t*>(a.Kc);
@@ -284,8 +192,9 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
         B[bt][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(Kc + ubase + krow * a.stride_n + s * 16 + hh * 8));
     }
   }
-  // largest column norm of the projector (from the threshold kernel; requested together with the keys)
-  const float wmax = __uint_as_float(*a.wmax_bits);
+  // largest column norm of the projector (of every 16 tile rows; requested together with the keys)
+  float wmax = 0.f;
+  for (int i = lane; i < a.ntiles * 2; i += 64) wmax = fmaxf(wmax, a.rownorm[i]);
   const float munorm = a.munorm[unit];
   float knorm[2];
 #pragma unroll
@@ -310,6 +219,8 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
 
   const int NW = a.NW;
   uint32_t* blk_codes = a.codes + ((int64_t)unit * a.blocks_cap + cb) * (kBlockKeys * (int64_t)NW);
+  wmax = wave_max(wmax);
+  if (blockIdx.x == 0 && unit == 0 && blockIdx.z == 0 && tid == 0) *a.wmax_bits = __float_as_uint(wmax);   // statistics only
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   // flagged iff |acc| < bnd, bnd being just above the rigorous bound (so "<=" is covered)
@@ -372,7 +283,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
     const int cur = q & 1;
     const bool more = q + 1 < nquads;
     float stt = -INFINITY;
-    if (q > 0) store_quad(q - 1);
+    if (q > q0) store_quad(q - 1);
     stage_pair(gA + ((int64_t)q * 2 + 1) * 1024, sA1, tid, wave);
     if (more && tid < 128) stt = gThr[(q + 1) * 128 + tid];
 
@@ -471,7 +382,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // the next stage has landed in LDS
     __syncthreads();
   };
-  for (int q = 0; q < nquads; ++q) do_quad(q);
+  for (int q = q0; q < nquads; ++q) do_quad(q);
   store_quad(nquads - 1);
 
   // ---- re-evaluate this workgroup's flagged pairs while its key rows are still in L2 ----
@@ -489,32 +400,40 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   recheck_pairs<4>(a, sLimbs[wave], keep, (uint64_t)wave * 16, 64, [&](uint64_t i) { return sList[i]; });
 }
 
-// Re-evaluates the pairs that did not fit a workgroup's own list (normally none).
-__global__ __launch_bounds__(256) void recheck_kernel(HashMfmaArgs a) {
-  __shared__ long long limbs[4][kLimbs];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  if (lane < kLimbs) limbs[wave][lane] = 0;
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-  if (*a.overflow) return;                               // the direct kernel redoes everything
-  const uint64_t count = *a.list_count < a.list_cap ? *a.list_count : a.list_cap;
-  recheck_pairs<16>(a, limbs[wave], count, ((uint64_t)blockIdx.x * 4 + wave) * 4, (uint64_t)gridDim.x * 16,
-                [&](uint64_t i) { return a.list[i]; });
+// The sweep over the projector is split over grid layers while all of them are resident at once: a
+// workgroup alone on its compute unit takes 4 us per quad and 15 to 25 us besides (keys from HBM,
+// norms, re-evaluation), so a few workgroups leave the chip idle for a whole sweep.  Measured for
+// the call, (10,150): 128 workgroups 79 -> 46 us in six parts, 256 workgroups 80 -> 60 us in three;
+// 512 workgroups 96 -> 100 us in two, 3072 workgroups 458 -> 556 us: a second round of workgroups costs
+// its fixed part.  The quads of the last table group stay together (their words are one bit string).
+static int split_sweep(int64_t groups, int nquads, int tail_quad, int* begin) {
+  constexpr int64_t kResident = 3 * kNumCU;
+  int64_t parts = kResident / groups;
+  parts = parts < 1 ? 1 : (parts > kMaxSweepParts ? kMaxSweepParts : parts);
+  const int per = (int)((nquads + parts - 1) / parts);
+  int n = 0;
+  for (int q = 0; q < nquads;) {
+    begin[n++] = q;
+    q = q + per < nquads && q + per <= tail_quad && n < parts ? q + per : nquads;
+  }
+  begin[n] = nquads;
+  return n;
 }
 
 hipError_t launch_hash_keys_mfma(const HashMfmaArgs& a, hipStream_t s) {
-  const int rows = a.ntiles * 32;
-  hipLaunchKernelGGL(prep_projector_kernel, dim3((unsigned)((rows * 16 + 255) / 256)), dim3(256), 0, s, a);
+  const int proj_blocks = a.ntiles * 2, thr_blocks = (a.ntiles * 32 + 255) / 256;   // 16 tile rows, 256 columns each
+  hipLaunchKernelGGL(prep_hash_keys_kernel, dim3((unsigned)(proj_blocks + (int64_t)thr_blocks * a.units)), dim3(256), 0, s, a,
+                     proj_blocks, thr_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(prep_threshold_kernel, dim3((unsigned)((rows + 255) / 256), (unsigned)a.units), dim3(256), 0, s, a);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t first_blk = a.first_key / kBlockKeys;
   const int64_t last_blk = (a.first_key + a.n_keys - 1) / kBlockKeys;
   const int64_t nblk = last_blk - first_blk + 1;
-  hipLaunchKernelGGL(hash_keys_mfma_kernel, dim3((unsigned)((nblk + 3) / 4), (unsigned)a.units), dim3(256), 0, s, a);
+  const int64_t groups = (nblk + 3) / 4 * a.units;
+  HashMfmaArgs b = a;
+  const int parts = split_sweep(groups, a.ntiles / 4, tail_begin(a.K, a.L) / 4, b.part_begin);
+  hipLaunchKernelGGL(hash_keys_mfma_kernel, dim3((unsigned)((nblk + 3) / 4), (unsigned)a.units, (unsigned)parts), dim3(256), 0, s, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(recheck_kernel, dim3(256), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

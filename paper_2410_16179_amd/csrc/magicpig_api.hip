@@ -241,7 +241,6 @@ mp::HashDirectArgs key_rows(const magicpig_params* p, const void* K_cache, const
   a.stride_b = p->k_stride_b; a.stride_h = p->k_stride_h; a.stride_n = p->k_stride_n;
   a.blocks_cap = mp::key_blocks(p->n_cap);
   a.total_rows = (int64_t)p->batch * p->n_kv_heads * n_keys;
-  a.run_flag = nullptr;
   a.n_dev = nullptr; a.n_cap = p->n_cap;
   return a;
 }
@@ -258,7 +257,6 @@ mp::HashDirectArgs query_rows(const magicpig_params* p, const void* q, const voi
   a.n_kv_heads = 1;
   a.stride_b = 0; a.stride_h = 0; a.stride_n = mp::kHeadDim;
   a.blocks_cap = 0;
-  a.run_flag = nullptr;
   a.n_dev = nullptr; a.n_cap = 0;
   return a;
 }
@@ -419,33 +417,29 @@ int magicpig_hash_keys(const magicpig_params* p, const void* K_cache, const floa
     const hipError_t e = mp::launch_hash_keys_f32(a, p->batch * p->n_kv_heads, stream);
     return e == hipSuccess ? MAGICPIG_OK : fail_hip(e);
   }
-  {
-    // matrix-core path; the direct kernel runs afterwards only if its list overflowed
-    const HashWs wl = ws_hash_layout(p);
-    char* wsb = reinterpret_cast<char*>(workspace);
-    mp::HashMfmaArgs m{};
-    m.Kc = K_cache; m.W = W; m.mu = mu; m.codes = key_codes;
-    m.K = p->K; m.L = p->L; m.NW = a.NW; m.NQ = a.NQ; m.ntiles = wl.ntiles;
-    m.units = p->batch * p->n_kv_heads; m.n_kv_heads = p->n_kv_heads;
-    m.kv_fp8 = p->kv_dtype == MAGICPIG_KV_FP8_E4M3;
-    m.n_keys = n_keys; m.first_key = first_key; m.n_cap = p->n_cap; m.blocks_cap = a.blocks_cap;
-    m.stride_b = p->k_stride_b; m.stride_h = p->k_stride_h; m.stride_n = p->k_stride_n;
-    m.afrag = wsb + wl.afrag_off; m.wt = wsb + wl.wt_off;
-    m.thr = reinterpret_cast<float*>(wsb + wl.thr_off);
-    m.thr64 = reinterpret_cast<double*>(wsb + wl.thr64_off);
-    m.magmu = reinterpret_cast<float*>(wsb + wl.magmu_off);
-    m.munorm = reinterpret_cast<float*>(wsb + wl.munorm_off);
-    m.rownorm = reinterpret_cast<float*>(wsb + wl.rownorm_off);
-    m.wmax_bits = reinterpret_cast<unsigned*>(wsb + wl.scalar_off);
-    m.list_count = m.wmax_bits + 1;
-    m.overflow = reinterpret_cast<int*>(m.wmax_bits + 2);
-    m.flagged_total = m.wmax_bits + 3;
-    m.list = reinterpret_cast<unsigned long long*>(wsb + wl.list_off); m.list_cap = wl.list_cap;
-    const hipError_t e = mp::launch_hash_keys_mfma(m, stream);
-    if (e != hipSuccess) return fail_hip(e);
-    a.run_flag = m.overflow;
-  }
-  const hipError_t e = mp::launch_hash_direct(a, stream);
+  // matrix-core path, and what it leaves over
+  const HashWs wl = ws_hash_layout(p);
+  char* wsb = reinterpret_cast<char*>(workspace);
+  mp::HashMfmaArgs m{};
+  m.Kc = K_cache; m.W = W; m.mu = mu; m.codes = key_codes;
+  m.K = p->K; m.L = p->L; m.NW = a.NW; m.NQ = a.NQ; m.ntiles = wl.ntiles;
+  m.units = p->batch * p->n_kv_heads; m.n_kv_heads = p->n_kv_heads;
+  m.kv_fp8 = p->kv_dtype == MAGICPIG_KV_FP8_E4M3;
+  m.n_keys = n_keys; m.first_key = first_key; m.n_cap = p->n_cap; m.blocks_cap = a.blocks_cap;
+  m.stride_b = p->k_stride_b; m.stride_h = p->k_stride_h; m.stride_n = p->k_stride_n;
+  m.afrag = wsb + wl.afrag_off; m.wt = wsb + wl.wt_off;
+  m.thr = reinterpret_cast<float*>(wsb + wl.thr_off);
+  m.thr64 = reinterpret_cast<double*>(wsb + wl.thr64_off);
+  m.magmu = reinterpret_cast<float*>(wsb + wl.magmu_off);
+  m.munorm = reinterpret_cast<float*>(wsb + wl.munorm_off);
+  m.rownorm = reinterpret_cast<float*>(wsb + wl.rownorm_off);
+  m.wmax_bits = reinterpret_cast<unsigned*>(wsb + wl.scalar_off);
+  m.list_count = m.wmax_bits + 1;
+  m.overflow = reinterpret_cast<int*>(m.wmax_bits + 2);
+  m.flagged_total = m.wmax_bits + 3;
+  m.list = reinterpret_cast<unsigned long long*>(wsb + wl.list_off); m.list_cap = wl.list_cap;
+  hipError_t e = mp::launch_hash_keys_mfma(m, stream);
+  if (e == hipSuccess) e = mp::launch_finish_hash_keys(m, a, stream);
   return e == hipSuccess ? MAGICPIG_OK : fail_hip(e);
 }
 

@@ -66,7 +66,7 @@ struct BitString {
   }
 };
 
-// Launch description of the direct (float64 + exact fallback) SimHash kernel.
+// Launch description of the SimHash kernels that code vectors without a prepared projector.
 struct HashDirectArgs {
   const void* X;        // vectors to hash
   const void* W;        // [128, K*L] row-major
@@ -82,13 +82,14 @@ struct HashDirectArgs {
   int64_t stride_b, stride_h, stride_n;   // element strides (query layout: stride_n = 128, others 0)
   int64_t blocks_cap;   // code blocks per unit
   int64_t total_rows;
-  const int* run_flag;  // if not null the kernel does nothing unless *run_flag != 0
   // hash_rows_kernel only: if not null, the context length in device memory; the vectors are then
   // the newest n_keys keys [*n_dev - n_keys, *n_dev) of every unit instead of first_key ..
   // (nothing is coded when that range does not lie inside [0, n_cap))
   const int64_t* n_dev;
   int64_t n_cap;
 };
+
+constexpr int kMaxSweepParts = 8;
 
 // Launch description of the matrix-core key hashing (bf16 keys).
 struct HashMfmaArgs {
@@ -104,10 +105,13 @@ struct HashMfmaArgs {
   double* thr64;               // [units][K*L] mu.W_j in float64 (exact products, 128 roundings of 2^-53)
   float* magmu;                // [units][K*L] an upper bound of sum_d |mu_d W_dj|
   float* munorm;               // [units]
-  float* rownorm;              // [ntiles*32] norm of the projector column behind each tile row
+  float* rownorm;              // [ntiles*2] largest norm among the projector columns behind 16 tile rows
   unsigned* wmax_bits;         // max column norm of W (float bits), kept for the statistics
   unsigned* list_count; int* overflow; unsigned* flagged_total;
   unsigned long long* list; uint64_t list_cap;
+  // the sweep over the projector in parts, one grid layer each: layer z takes the quads (of MFMA tiles)
+  // part_begin[z] .. part_begin[z + 1] - 1
+  int part_begin[kMaxSweepParts + 1];
 };
 
 // Matrix-core projections (bf16 products are exact in float32; float32 accumulation): whatever the
@@ -243,7 +247,7 @@ constexpr int kFusedFill = 768;               // workgroups of it that are resid
 constexpr int kFusedIters = 8;             // its gather batch: rows per quarter wavefront
 
 // host-side launchers (defined next to their kernels)
-hipError_t launch_hash_direct(const HashDirectArgs& a, hipStream_t s);
+hipError_t launch_finish_hash_keys(const HashMfmaArgs& m, const HashDirectArgs& a, hipStream_t s);
 hipError_t launch_hash_rows(const HashDirectArgs& a, const HashDirectArgs* b, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 hipError_t launch_hash_keys_f32(const HashDirectArgs& a, int units, hipStream_t s);
 hipError_t launch_hash_keys_mfma(const HashMfmaArgs& a, hipStream_t s);
