@@ -157,42 +157,34 @@ __device__ inline uint64_t report_block(const AttnArgs& a, const Ctx& c, int64_t
 // One wavefront compares BPW consecutive 64-key code blocks (lane = key) of KV unit `unit`,
 // starting at block blk0 < key_blocks(n), with the codes of the query heads h_begin .. h_end-1
 // of the unit's G, and hands emit(h, blk, ballot) the sampled keys of every (head, block).
-// KT, WDT, LT: compile-time K, ceil(L/32) and tables in the last group for the tuned
-// instantiations, 0 for the generic one.
+// KT, WDT, LT: compile-time K, ceil(L/32) and tables in the last group (scan_block_any takes the others).
 // BPW: all code words of the blocks are requested before the first comparison, and each
 // scalar-loaded query word serves BPW keys per lane.
 template <int KT, int WDT, int LT, int BPW, bool DBG, class Emit>
 __device__ inline void scan_blocks(const AttnArgs& a, const Ctx& c, int unit, int64_t blk0, int lane, int h_begin, int h_end, Emit emit) {
-  constexpr bool kGeneric = (KT == 0);
   const int64_t nblk = key_blocks(c.n);
   const int G = a.Hq / a.Hkv;
-  const int K = kGeneric ? a.K : KT;
-  const int Wd = kGeneric ? a.Wd : WDT;
-  const int NQ = K * Wd;                                 // plane words of a query code
-  constexpr int kTailWords = kGeneric ? 0 : (KT * LT + 31) / 32;
-  constexpr int kNWT = kGeneric ? 1 : KT * (WDT - 1) + kTailWords;   // words of a key code
-  const int NW = kGeneric ? a.NW : kNWT;
+  constexpr int NQ = KT * WDT;                           // plane words of a query code
+  constexpr int NW = KT * (WDT - 1) + (KT * LT + 31) / 32;   // words of a key code
   const int64_t head0 = (int64_t)(unit / a.Hkv) * a.Hq + (int64_t)(unit % a.Hkv) * G;
   // Query codes are wave-uniform and constant during the kernel: read through the constant
   // address space they are scalar loads into SGPRs and feed the bit operations directly.
   const const_u32_ptr qc = (const_u32_ptr)(a.qcodes + head0 * NQ);
   const uint32_t* blkp = a.kcodes + ((int64_t)unit * a.blocks_cap + blk0) * (kBlockKeys * (int64_t)NW);
 
-  [[maybe_unused]] uint32_t kw[BPW][kNWT];
+  uint32_t kw[BPW][NW];
   // the planes of the last table group, taken out of their bit string once per key
-  [[maybe_unused]] uint32_t kt[BPW][kGeneric ? 1 : KT];
-  if constexpr (!kGeneric) {
+  uint32_t kt[BPW][KT];
 #pragma unroll
-    for (int j = 0; j < BPW; ++j) {
-      if (blk0 + j < nblk) load_code_block<kNWT>(blkp + j * (kBlockKeys * (int64_t)NW), lane, kw[j]);
+  for (int j = 0; j < BPW; ++j) {
+    if (blk0 + j < nblk) load_code_block<NW>(blkp + j * (kBlockKeys * (int64_t)NW), lane, kw[j]);
 #pragma unroll
-      for (int p = 0; p < KT; ++p) {
-        constexpr int xs = KT * (WDT - 1);
-        const int off = p * LT, wi = xs + off / 32, sh = off % 32;
-        if (sh == 0) kt[j][p] = kw[j][wi];
-        else if (sh + LT <= 32) kt[j][p] = kw[j][wi] >> sh;
-        else kt[j][p] = __builtin_amdgcn_alignbit(kw[j][wi + 1], kw[j][wi], sh);
-      }
+    for (int p = 0; p < KT; ++p) {
+      constexpr int xs = KT * (WDT - 1);
+      const int off = p * LT, wi = xs + off / 32, sh = off % 32;
+      if (sh == 0) kt[j][p] = kw[j][wi];
+      else if (sh + LT <= 32) kt[j][p] = kw[j][wi] >> sh;
+      else kt[j][p] = __builtin_amdgcn_alignbit(kw[j][wi + 1], kw[j][wi], sh);
     }
   }
 
@@ -205,43 +197,133 @@ __device__ inline void scan_blocks(const AttnArgs& a, const Ctx& c, int unit, in
     uint32_t cnt[BPW];
 #pragma unroll
     for (int j = 0; j < BPW; ++j) cnt[j] = 0;
-    if constexpr (!kGeneric) {
 #pragma unroll
-      for (int w = 0; w < WDT; ++w) {
-        const bool tail = w == WDT - 1;
-        uint32_t same[BPW];
+    for (int w = 0; w < WDT; ++w) {
+      const bool tail = w == WDT - 1;
+      uint32_t same[BPW];
 #pragma unroll
-        for (int j = 0; j < BPW; ++j) same[j] = ~((tail ? kt[j][0] : kw[j][w * KT]) ^ qh[w * KT]);
+      for (int j = 0; j < BPW; ++j) same[j] = ~((tail ? kt[j][0] : kw[j][w * KT]) ^ qh[w * KT]);
 #pragma unroll
-        for (int p = 1; p < KT; ++p) {
+      for (int p = 1; p < KT; ++p) {
 #pragma unroll
-          for (int j = 0; j < BPW; ++j)
-            same[j] &= ~((tail ? kt[j][p] : kw[j][w * KT + p]) ^ qh[w * KT + p]);   // one 3-input op
-        }
-        // beyond the real tables of the last group the key planes hold bits of the next plane
-        if (tail && LT < 32) {
-#pragma unroll
-          for (int j = 0; j < BPW; ++j) same[j] &= (1u << (LT & 31)) - 1u;
-        }
-#pragma unroll
-        for (int j = 0; j < BPW; ++j) cnt[j] += __popc(same[j]);
+        for (int j = 0; j < BPW; ++j)
+          same[j] &= ~((tail ? kt[j][p] : kw[j][w * KT + p]) ^ qh[w * KT + p]);   // one 3-input op
       }
-    } else {
-      for (int w = 0; w < Wd; ++w) {
-        uint32_t same = ~0u;
-        for (int p = 0; p < K; ++p) {
-          const int x = w * K + p;
-          same &= ~(load_plane_word(blkp, NW, K, a.L, x, lane) ^ qh[x]);
-        }
-        if (w == Wd - 1 && (a.L & 31)) same &= (1u << (a.L & 31)) - 1u;
-        cnt[0] += __popc(same);
+      // beyond the real tables of the last group the key planes hold bits of the next plane
+      if (tail && LT < 32) {
+#pragma unroll
+        for (int j = 0; j < BPW; ++j) same[j] &= (1u << (LT & 31)) - 1u;
       }
+#pragma unroll
+      for (int j = 0; j < BPW; ++j) cnt[j] += __popc(same[j]);
     }
 #pragma unroll
     for (int j = 0; j < BPW; ++j) {
       const int64_t blk = blk0 + j;
       if (blk < nblk) emit(h, blk, report_block<DBG>(a, c, head0 + h, blk, lane, cnt[j], eligible[j]));
     }
+  }
+}
+
+// Any K and L: one wavefront compares the 64-key code block blk < key_blocks(n) of KV unit `unit`
+// (lane = key) with the codes of the query heads h_begin .. h_begin + G - 1 of the unit, G <= GT, and
+// hands emit(h, blk, ballot) the sampled keys.  The words of a key are taken in the order they are
+// stored, 16 bytes per load with four loads in flight, and each is compared with all heads while it
+// is in registers: diff collects the planes of a table group, and every K words the group's colliding
+// tables are counted.  The last group's planes are taken off its bit string as its words come in.
+// GT = 1, 2, 4, 8: heads the registers are laid out for (heads beyond G repeat the last one).
+// (The first version read every word anew for every head, one at a time: 32 KV heads of one query head,
+// 20011 keys, (9,110): scan_gather_kernel 54 us; now 30 us for 87 MB.)
+template <int GT, bool DBG, class Emit>
+__device__ inline void scan_block_any(const AttnArgs& a, const Ctx& c, int unit, int64_t blk, int lane, int h_begin, int G, Emit emit) {
+  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+  const int K = a.K, NW = a.NW, NQ = a.NQ;
+  const int xs = tail_begin(K, a.L), Lt = tail_tables(a.L);
+  const int full = NW >> 2, rem = NW & 3, groups = (NW + 3) >> 2;
+  const int64_t head0 = (int64_t)(unit / a.Hkv) * a.Hq + (int64_t)(unit % a.Hkv) * (a.Hq / a.Hkv) + h_begin;
+  const uint32_t* blkp = a.kcodes + ((int64_t)unit * a.blocks_cap + blk) * (kBlockKeys * (int64_t)NW);
+  // (wave-uniform and constant during the kernel: scalar loads, see scan_blocks)
+  const_u32_ptr q[GT];
+#pragma unroll
+  for (int h = 0; h < GT; ++h) q[h] = (const_u32_ptr)(a.qcodes + (head0 + (h < G ? h : G - 1)) * NQ);
+  uint32_t diff[GT], cnt[GT];
+#pragma unroll
+  for (int h = 0; h < GT; ++h) { diff[h] = 0u; cnt[h] = 0u; }
+  uint64_t acc = 0;                                      // the last group's bit string: bits not taken yet
+  int have = 0, plane = 0;                               // how many, and the plane of the group that comes next
+  auto load = [&](int g, u32x4& v) {
+    if (g < full) {
+      v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(blkp + g * 256) + lane);
+    } else if (g == full) {
+      const uint32_t* p = blkp + full * 256 + lane * rem;
+      if (rem > 0) v.x = __builtin_nontemporal_load(p);
+      if (rem > 1) v.y = __builtin_nontemporal_load(p + 1);
+      if (rem > 2) v.z = __builtin_nontemporal_load(p + 2);
+    }
+  };
+  auto flush = [&]() {
+    plane = 0;
+#pragma unroll
+    for (int h = 0; h < GT; ++h) { cnt[h] += __popc(~diff[h]); diff[h] = 0u; }
+  };
+  auto consume = [&](int x, uint32_t word) {             // key word x (all tests are wave-uniform)
+    if (x < xs) {
+#pragma unroll
+      for (int h = 0; h < GT; ++h) diff[h] |= word ^ q[h][x];
+      if (++plane == K) flush();
+    } else if (x < NW) {
+      acc |= (uint64_t)word << have;
+      have += 32;
+      while (have >= Lt && plane < K) {
+        const uint32_t f = (uint32_t)acc;                // (bits beyond Lt belong to the next plane: masked in the end)
+#pragma unroll
+        for (int h = 0; h < GT; ++h) diff[h] |= f ^ q[h][xs + plane];
+        acc >>= Lt;
+        have -= Lt;
+        ++plane;
+      }
+    }
+  };
+  u32x4 v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = (u32x4)(0u);
+    load(i, v[i]);
+  }
+#pragma unroll 1
+  for (int g = 0; g < groups; g += 4) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (g + i >= groups) break;
+      const u32x4 cur = v[i];
+      load(g + i + 4, v[i]);
+      const int x0 = 4 * (g + i);
+      if (x0 + 4 <= xs) {                                // four planes: the queries' words in one go
+        const uint32_t w4[4] = {cur.x, cur.y, cur.z, cur.w};
+        uint32_t qw[GT][4];
+#pragma unroll
+        for (int h = 0; h < GT; ++h)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) qw[h][k] = q[h][x0 + k];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+          for (int h = 0; h < GT; ++h) diff[h] |= w4[k] ^ qw[h][k];
+          if (++plane == K) flush();
+        }
+      } else {
+        consume(x0, cur.x);
+        consume(x0 + 1, cur.y);
+        consume(x0 + 2, cur.z);
+        consume(x0 + 3, cur.w);
+      }
+    }
+  }
+  const uint32_t real = Lt >= 32 ? ~0u : (1u << Lt) - 1u;
+  const uint64_t eligible = eligible_keys(a, c, blk, lane);
+#pragma unroll
+  for (int h = 0; h < GT; ++h) {
+    if (h < G) emit(h_begin + h, blk, report_block<DBG>(a, c, head0 + h, blk, lane, cnt[h] + __popc(~diff[h] & real), eligible));
   }
 }
 

@@ -118,8 +118,9 @@ size_t ws_hash_for(const magicpig_params* p, int64_t n_keys) {
 }
 
 // decode workspace: [partials | ballots]
-struct AttnWs { size_t partial_off, masks_off, total; int nranges, nscan, f_nranges, f_wave_blocks, f_touch; int64_t n_static; };
-AttnWs ws_attention_layout(const magicpig_params* p) {
+struct AttnWs { size_t partial_off, masks_off, total; int nranges, nscan, f_nranges, f_wave_blocks, f_parts, f_touch; int64_t n_static; };
+// `bytes`: what there is for the partials (the size queries ask with no bound).
+AttnWs ws_attention_layout(const magicpig_params* p, size_t bytes = SIZE_MAX) {
   AttnWs w{};
   const int64_t nblk = mp::key_blocks(p->n_ctx);
   const size_t heads = (size_t)p->batch * p->n_q_heads;
@@ -127,28 +128,60 @@ AttnWs ws_attention_layout(const magicpig_params* p) {
   const int64_t st = (int64_t)p->n_sink + p->n_local;
   w.n_static = st < p->n_ctx ? st : p->n_ctx;
   w.nranges = w.nscan + (int)((w.n_static + mp::kStaticPerRange - 1) / mp::kStaticPerRange);
-  // the one-launch scan + gather: one partial per run and head
-  // The shortest runs (4 wave_blocks key blocks per workgroup) whose workgroups are all resident
-  // at once, give or take a dozen: a second, mostly empty round of workgroups would
-  // start late and end last (measured at 8 KV heads: 100000 keys 48.6 -> 44.8 us per step, 65536
-  // keys 36.1 -> 33.7, 32768 keys 27.4 -> 23.9 against runs of 16, 8 or 4 blocks chosen to fill
-  // the chip at least once).  When even the longest runs do not fit (large batches) the rounds
-  // are many anyway: the longest runs, 24 blocks (fewer partials; batch 16 x 65536 keys: 275 ->
-  // 272.5 us against 16 blocks), and the wavefronts touch the rows of their last block early.
-  const int64_t units = (int64_t)p->batch * p->n_kv_heads;
-  auto groups = [&](int wb) { return units * ((nblk + 4 * wb - 1) / (4 * wb)); };
-  const int64_t fits = mp::kFusedFill + mp::kFusedFill / 64;   // 780: a dozen late workgroups cost less than longer runs
-  w.f_wave_blocks = 1;
-  while (w.f_wave_blocks < mp::kFusedWaveBlocks && groups(w.f_wave_blocks) > fits) ++w.f_wave_blocks;
-  w.f_touch = 0;
-  if (groups(w.f_wave_blocks) > fits) { w.f_wave_blocks = mp::kFusedWaveBlocks; w.f_touch = 1; }
-  w.f_nranges = (int)((nblk + 4 * w.f_wave_blocks - 1) / (4 * w.f_wave_blocks));
   // lookup + gather in one launch: 16 partials per slice
   const int lg = (int)((nblk + mp::kLgSliceBlocks - 1) / mp::kLgSliceBlocks) * 16;
-  size_t most = (size_t)(w.f_nranges > w.nranges ? w.f_nranges : w.nranges);
-  if ((size_t)lg > most) most = (size_t)lg;
+
+  // The one-launch scan + gather: one workgroup per run of 4 wave_blocks key blocks.
+  const int64_t units = (int64_t)p->batch * p->n_kv_heads;
+  auto runs = [&](int wb) { return (nblk + 4 * wb - 1) / (4 * wb); };
+  // Least scratch that a step is promised to run with: runs of the shortest length whose workgroups
+  // fit a round of 780, or of 24 blocks.
+  int wb0 = 1;
+  const int64_t fits = mp::kFusedFill + mp::kFusedFill / 64;
+  while (wb0 < mp::kFusedWaveBlocks && units * runs(wb0) > fits) ++wb0;
+  size_t least = (size_t)(runs(wb0) > w.nranges ? runs(wb0) : w.nranges);
+  if ((size_t)lg > least) least = (size_t)lg;
+  const size_t per = heads * mp::kPartialStride * sizeof(float);   // one partial of every head
+  // Length of the runs.  (a) The shortest whose workgroups are resident at once, three per compute unit
+  // (kFusedFill, give or take a dozen): a second, mostly empty round starts late and ends last.  (b) If
+  // there is none, or a KV head has one query head (its gather is the work of one or two wavefronts:
+  // short runs), four per compute unit, with the kernel compiled for that.  (c) Otherwise the rounds are
+  // many: the compute unit that gets most blocks takes longest, r workgroups of 4 wb blocks and about
+  // two blocks' worth of time besides for each (its gather).
+  // Measured (us, the kernel with its merge): (a) 8 units x 1563 blocks: 48.6 -> 44.8 per step against runs of
+  // 16 blocks, 16 workgroups of which came in a second round; (b) 24 units x 798 blocks, e4m3, (10,220): 816
+  // workgroups of wb 6 86, 960 of wb 5 79; 64 x 313, (9,100): 896 of wb 6 64, 1024 of wb 5 58, 1280 of wb 4 74; one
+  // query head per KV head, 32 x 313: 640 of wb 4 37.7, 864 of wb 3 34.1; (c) 24 x 1024: wb 6 (r = 5) 71, wb 4 (r =
+  // 6) 65; 32 x 1563, eight heads: wb 6 (r = 9) 150, wb 5 (r = 10) 147; 128 x 1024, (9,120): 283 to 288 for 4, 5, 6.
+  const int G = p->n_q_heads / p->n_kv_heads;
+  const int64_t all = 4 * mp::kNumCU;
+  int wb = 1;
+  while (wb < mp::kFusedWaveBlocks && units * runs(wb) > (G == 1 ? all : fits)) ++wb;
+  if (units * runs(wb) > fits && units * runs(wb) <= all) {
+    while (wb > 1 && units * runs(wb - 1) <= all) --wb;
+  } else if (units * runs(wb) > all) {
+    int64_t best = INT64_MAX;
+    for (int v = 1; v <= mp::kFusedWaveBlocks; ++v) {
+      const int64_t r = (units * runs(v) + mp::kNumCU - 1) / mp::kNumCU, cost = r * (4 * v + 2);
+      if (cost <= best) { best = cost; wb = v; }           // (equal: fewer partials)
+    }
+  }
+  w.f_wave_blocks = wb;
+  w.f_parts = mp::scan_parts(mp::tuned_tables(p->K, p->L) ? p->K : 0, G);
+  // More partials than the promised scratch holds only where there is room for them, and where the call
+  // with the library's own scratch has it too (its result is the same bit for bit).
+  const size_t want = (size_t)runs(wb) * w.f_parts * per, own = MAGICPIG_STATIC_SCRATCH_BYTES;
+  if (want > bytes || (want > own && least * per <= own)) {
+    w.f_wave_blocks = wb0;
+    w.f_parts = 1;
+  }
+  w.f_touch = units * runs(w.f_wave_blocks) > fits;
+  w.f_nranges = (int)runs(w.f_wave_blocks);
+  size_t most = (size_t)w.f_nranges * w.f_parts;
+  if (least > most) most = least;
+  if (bytes != SIZE_MAX) most = least;
   w.partial_off = 0;
-  w.masks_off = align256(heads * most * mp::kPartialStride * sizeof(float));
+  w.masks_off = align256(per * most);
   w.total = w.masks_off + align256(heads * (size_t)nblk * sizeof(uint64_t));
   return w;
 }
@@ -290,7 +323,7 @@ int run_attention_impl(const magicpig_params* p, const void* q, const void* K_ca
   if (!aligned16(q) || !aligned16(K_cache) || !aligned16(V_cache) || !aligned16(key_codes) || !aligned16(tables) ||
       !aligned16(q_codes) || !aligned16(out) || !aligned16(workspace) || (mu && !aligned16(mu)))
     return MAGICPIG_INVALID_ARG;
-  const AttnWs wl = ws_attention_layout(p);
+  const AttnWs wl = ws_attention_layout(p, use_static_scratch ? (size_t)MAGICPIG_STATIC_SCRATCH_BYTES : workspace_bytes);
   if (use_static_scratch) {
     // everything above ran without a GPU call; the library's own scratch replaces the workspace
     if (wl.masks_off > (size_t)MAGICPIG_STATIC_SCRATCH_BYTES) return MAGICPIG_SCRATCH_TOO_SMALL;
@@ -305,7 +338,7 @@ int run_attention_impl(const magicpig_params* p, const void* q, const void* K_ca
   a.partial = reinterpret_cast<float*>(wsb + wl.partial_off); a.out = out;
   a.masks = reinterpret_cast<uint64_t*>(wsb + wl.masks_off);
   a.nranges = wl.nranges; a.nscan = wl.nscan; a.n_static = wl.n_static;
-  a.f_nranges = wl.f_nranges; a.f_wave_blocks = wl.f_wave_blocks; a.f_touch = wl.f_touch;
+  a.f_nranges = wl.f_nranges; a.f_wave_blocks = wl.f_wave_blocks; a.f_parts = wl.f_parts; a.f_touch = wl.f_touch;
   a.dbg_counts = dbg_counts; a.dbg_cand = dbg_cand; a.dbg_ncand = dbg_ncand; a.dbg_cand_cap = dbg_cand_cap;
   a.dbg_stride = p->n_ctx; a.n_dev = p->n_ctx_dev;
   a.is_fp32 = p->dtype == MAGICPIG_FP32;

@@ -52,9 +52,11 @@ __global__ __launch_bounds__(256) void collision_scan_kernel(AttnArgs a) {
   if (blk0 >= nblk) return;
   const int G = a.Hq / a.Hkv;
   const int64_t head0 = (int64_t)(unit / a.Hkv) * a.Hq + (int64_t)(unit % a.Hkv) * G;
-  scan_blocks<KT, WDT, LT, BPW, true>(a, c, unit, blk0, lane, 0, G, [&](int h, int64_t blk, uint64_t m) {
+  auto emit = [&](int h, int64_t blk, uint64_t m) {
     if (lane == 0) a.masks[(head0 + h) * nblk + blk] = m;
-  });
+  };
+  if constexpr (KT == 0) scan_block_any<WDT, true>(a, c, unit, blk0, lane, 0, G, emit);
+  else scan_blocks<KT, WDT, LT, BPW, true>(a, c, unit, blk0, lane, 0, G, emit);
 }
 
 // rows per quarter wavefront and batch of the stand-alone gather: 32 K and 32 V rows in flight
@@ -137,6 +139,7 @@ __global__ __launch_bounds__(512) void gather_estimate_kernel(AttnArgs a) {
 // they cost neither workgroups nor batches nor partials of their own.
 // One partial per (head, run).
 // DBG: with the debug outputs (counts, candidate lists).
+// KT, WDT, LT: see scan_blocks; KT = 0: any K and L, WDT = the heads scan_block_any is laid out for.
 // ET: element type of the caches (kBF16, kFP32, or kFP8 with bf16 queries).
 template <int KT, int WDT, int LT, int ET, bool DBG, int OCC>
 __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
@@ -164,7 +167,7 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   for (int j = 0; j < wave_blocks; ++j) {
     const int bi = wave * wave_blocks + j;
     if (blk0 + bi < nblk) {
-      scan_blocks<KT, WDT, LT, 1, DBG>(a, c, unit, blk0 + bi, lane, 0, G, [&](int h, int64_t, uint64_t m) {
+      auto emit = [&](int h, int64_t, uint64_t m) {
         if (m) {                                           // (wave-uniform)
           const int at = __builtin_amdgcn_readlane(found, h);
           const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
@@ -172,7 +175,9 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
           if (lane == h) found = at + __popcll(m);
         }
         if (j == wave_blocks - 1) last_found |= m;
-      });
+      };
+      if constexpr (KT == 0) scan_block_any<WDT, DBG>(a, c, unit, blk0 + bi, lane, 0, G, emit);
+      else scan_blocks<KT, WDT, LT, 1, DBG>(a, c, unit, blk0 + bi, lane, 0, G, emit);
     }
   }
   if (lane < G) seg_n[lane][wave] = found;
@@ -221,7 +226,9 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  for (int h = wave; h < G; h += 4) {
+  const int parts = scan_parts(KT, WDT) > 1 ? ga.f_parts : 1;   // wavefronts that share a head's candidates
+  const int part = wave & (parts - 1);
+  for (int h = wave / parts; h < G; h += 4 / parts) {
     HeadVectors<FP32> hv;
     request_head_vectors<FP32>(ga, unit, head0 + h, hv);
     // the four wavefronts' keys of head h, one after the other: candidate cc is entry cc - s_w of
@@ -232,15 +239,19 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
     const int total = s3 + __builtin_amdgcn_readfirstlane(seg_n[h][3]);
     const uint16_t* segh = &seg[h][0][0];
     // static keys run, run + nruns, ... ride along behind the sampled ones
-    const int nst = static_share(c, run, nruns);
-    gather_estimate_wave<ET, kIt>(ga, unit, head0 + h, total + nst, total, hv,
-                                    [&](int cc) {
+    const int all = total + static_share(c, run, nruns);
+    // this wavefront's share: candidates lo .. lo + mine - 1
+    const int share = (all + parts - 1) / parts, lo = part * share;
+    const int mine = parts == 1 ? all : (all - lo < share ? (all > lo ? all - lo : 0) : share);
+    gather_estimate_wave<ET, kIt>(ga, unit, head0 + h, mine, total - lo, hv,
+                                    [&](int cl) {
+                                      const int cc = cl + lo;
                                       if (cc >= total) return static_key(ga, c, run + (int64_t)(cc - total) * nruns);
                                       const int w = (cc >= s1) + (cc >= s2) + (cc >= s3);
                                       const int first = w == 0 ? 0 : (w == 1 ? s1 : (w == 2 ? s2 : s3));
                                       return blk0 * kBlockKeys + (int64_t)segh[w * kSeg + cc - first];
                                     },
-                                    ga.partial + ((head0 + h) * ga.f_nranges + run) * kPartialStride);
+                                    ga.partial + (((head0 + h) * ga.f_nranges + run) * parts + part) * kPartialStride);
   }
 #pragma unroll
   for (int l = 0; l < 2 * kLines; ++l) asm volatile("" ::"v"(touched[l]));
@@ -335,7 +346,7 @@ static hipError_t launch_scan(const AttnArgs& a, hipStream_t s, hipEvent_t start
   MP_TUNED(10, 150) MP_TUNED(9, 120) MP_TUNED(10, 170) MP_TUNED(8, 75) MP_TUNED(10, 220) MP_TUNED(11, 300)
 #undef MP_TUNED
   const dim3 grid((unsigned)((nscanned + 3) / 4), (unsigned)(a.B * a.Hkv));
-  launch_timed(collision_scan_kernel<0, 0, 0, 1>, grid, block, s, start, stop, a);
+  launch_timed(collision_scan_kernel<0, 8, 0, 1>, grid, block, s, start, stop, a);
   return hipGetLastError();
 }
 
@@ -356,21 +367,23 @@ static hipError_t launch_merge(const AttnArgs& a, int64_t heads, hipStream_t s, 
 template <int KT, int WDT, int LT, int ET, bool DBG>
 static void launch_scan_gather_as(const AttnArgs& a, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 block(256);
-  if (a.f_touch) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 4>, grid, block, s, start, stop, a);
-  else launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 3>, grid, block, s, start, stop, a);
+  // (any K and L: 127 registers, four workgroups fit either way)
+  if (KT == 0 || a.f_touch) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 4>, grid, block, s, start, stop, a);
+  else if constexpr (KT != 0) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 3>, grid, block, s, start, stop, a);
 }
 
 template <int KT, int WDT, int LT>
 static void launch_scan_gather_for(const AttnArgs& a, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  constexpr int W = KT == 0 && scan_parts(KT, WDT) == 1 ? 8 : WDT;   // (debug outputs of any K and L: one form for all)
   const bool dbg = a.dbg_counts || a.dbg_cand;
   if (a.is_fp32) {
-    if (dbg) launch_scan_gather_as<KT, WDT, LT, kFP32, true>(a, grid, s, start, stop);
+    if (dbg) launch_scan_gather_as<KT, W, LT, kFP32, true>(a, grid, s, start, stop);
     else launch_scan_gather_as<KT, WDT, LT, kFP32, false>(a, grid, s, start, stop);
   } else if (a.kv_fp8) {
-    if (dbg) launch_scan_gather_as<KT, WDT, LT, kFP8, true>(a, grid, s, start, stop);
+    if (dbg) launch_scan_gather_as<KT, W, LT, kFP8, true>(a, grid, s, start, stop);
     else launch_scan_gather_as<KT, WDT, LT, kFP8, false>(a, grid, s, start, stop);
   } else {
-    if (dbg) launch_scan_gather_as<KT, WDT, LT, kBF16, true>(a, grid, s, start, stop);
+    if (dbg) launch_scan_gather_as<KT, W, LT, kBF16, true>(a, grid, s, start, stop);
     else launch_scan_gather_as<KT, WDT, LT, kBF16, false>(a, grid, s, start, stop);
   }
 }
@@ -383,7 +396,13 @@ static hipError_t launch_scan_gather(const AttnArgs& a, hipStream_t s, hipEvent_
   else if (a.K == 8 && a.L == 75) launch_scan_gather_for<8, 3, 11>(a, grid, s, start, stop);
   else if (a.K == 10 && a.L == 220) launch_scan_gather_for<10, 7, 28>(a, grid, s, start, stop);   // App. E (K, L) study
   else if (a.K == 11 && a.L == 300) launch_scan_gather_for<11, 10, 12>(a, grid, s, start, stop);
-  else launch_scan_gather_for<0, 0, 0>(a, grid, s, start, stop);
+  else {                                                   // any other: by the heads that share a KV head
+    const int G = a.Hq / a.Hkv;
+    if (G == 1) launch_scan_gather_for<0, 1, 0>(a, grid, s, start, stop);
+    else if (G == 2) launch_scan_gather_for<0, 2, 0>(a, grid, s, start, stop);
+    else if (G <= 4) launch_scan_gather_for<0, 4, 0>(a, grid, s, start, stop);
+    else launch_scan_gather_for<0, 8, 0>(a, grid, s, start, stop);
+  }
   return hipGetLastError();
 }
 
@@ -432,7 +451,7 @@ hipError_t launch_sampled_attention(const AttnArgs& a, const TableArgs* tables, 
     if ((e = launch_scan_gather(a, s, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr)) != hipSuccess) return e;
     if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return e;
     AttnArgs b = a;
-    b.nranges = a.f_nranges;
+    b.nranges = a.f_nranges * a.f_parts;
     if ((e = launch_merge(b, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr)) != hipSuccess) return e;
     return hipGetLastError();
   }

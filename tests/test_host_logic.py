@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2410_16179_amd import binding as mp
 
@@ -120,6 +121,35 @@ def test_table_codes_from_words_roundtrip():
     codes = mp.table_codes_from_words(words, K, L)
     expect = (bits * (1 << np.arange(K))).sum(axis=2)
     np.testing.assert_array_equal(codes, expect)
+
+
+@pytest.mark.parametrize("b,hq,hkv,n,K,L", [(1, 32, 8, 98304, 10, 150), (3, 40, 8, 51027, 10, 220), (8, 32, 8, 20000, 9, 100),
+                                            (1, 32, 32, 20011, 9, 110), (16, 32, 8, 65536, 9, 120), (4, 32, 32, 8000, 10, 150),
+                                            (1, 8, 8, 60000, 8, 90), (1, 1, 1, 1, 8, 75)])
+def test_scratch_that_a_decode_step_is_promised_to_run_with(b, hq, hkv, n, K, L):
+    # the partials (528 bytes each) of one run of key blocks per workgroup - runs of the shortest length
+    # with which at most 780 workgroups are needed, 24 blocks at most -, of 16 blocks and 32 static keys,
+    # or of 16 wavefronts per window of 16384 keys, whichever are most
+    lib = mp.lib()
+    ws = (ctypes.c_char * 4096)()
+    wsp = ctypes.addressof(ws)
+    fake = ctypes.c_void_p(wsp + (-wsp) % 16)
+    nblk, units = (n + 63) // 64, b * hkv
+    wb = next((w for w in range(1, 6) if units * -(-nblk // (4 * w)) <= 780), 6)
+    partials = max(-(-nblk // (4 * wb)), -(-nblk // 16) + -(-min(n, 68) // 32), -(-nblk // 256) * 16)
+    need = (b * hq * partials * 528 + 255) // 256 * 256
+    p = params(batch=b, n_q_heads=hq, n_kv_heads=hkv, n_ctx=n, n_cap=n, K=K, L=L)
+    assert mp.magicpig_workspace_bytes(p) >= need
+
+    def attend(nbytes):
+        return lib.magicpig_sampled_attention(ctypes.byref(p), fake, fake, fake, None, fake, fake, fake, None, None, None, 0,
+                                              fake, nbytes, None)
+
+    assert attend(need - 1) == -3
+    if not torch.cuda.is_available():
+        assert attend(need) != -3                                # gets as far as the launch
+        st = lib.magicpig_sampled_attention_noalloc(ctypes.byref(p), fake, fake, fake, None, fake, fake, fake, None)
+        assert (st == -5) == (need > 8 << 20)
 
 
 def _status(fn, *args):
