@@ -123,6 +123,21 @@ __device__ inline float row_sum16(float v) {
   return v;
 }
 
+template <int N>
+__device__ inline double dpp_row_ror64(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, 0x120 + N, 0xf, 0xf, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), 0x120 + N, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+__device__ inline double row_sum16(double v) {
+  v += dpp_row_ror64<8>(v);
+  v += dpp_row_ror64<4>(v);
+  v += dpp_row_ror64<2>(v);
+  v += dpp_row_ror64<1>(v);
+  return v;
+}
+
 // Inclusive prefix sums over the lanes of every row of 16 lanes (row shifts, zeros shifted in), and
 // over lanes 0 .. 31 and 32 .. 63 (the total of an even row joins the row behind it).
 __device__ inline int row_prefix_sum16(int v) {

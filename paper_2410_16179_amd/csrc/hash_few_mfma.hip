@@ -12,11 +12,11 @@
 // -fl(mu.W_j) (magicpig_prepare_centering, once per sequence: the mean is frozen).
 //
 // Bit-exactness: as in hash_keys_mfma.hip a projection with |acc| <= kGamma (|x| + |mu|) max|W_j|
-// is re-evaluated exactly.  Here the re-evaluation never leaves the compute unit: the vector and
-// the projector column sit in the wavefront's registers, the two lanes that hold each write them
-// to LDS, every lane forms the exact float64 products of two elements (the centering vector was
-// staged in LDS at the start), a butterfly adds them, and what float64 cannot decide goes to the
-// exact accumulator (exact_dot.h).  The owning lane patches its bit before the word is stored,
+// is re-evaluated exactly.  Here the re-evaluation never leaves the compute unit: the vectors and
+// the projector columns sit in the wavefronts' registers and are copied to LDS (the centering vectors
+// were put there at the start), sixteen lanes per projection form the exact float64 products of eight
+// elements each, rotations inside the row add them, and what float64 cannot decide goes to the exact
+// accumulator (exact_dot.h).  The owning lane patches its bit before the word is stored,
 // so there is no list, no overflow and no atomic.
 #include "mp_common.h"
 #include "exact_dot.h"
@@ -109,10 +109,20 @@ __global__ __launch_bounds__(256) void prep_centering_kernel(const float* mu_all
   thr[((((int64_t)unit * Wd * P + wp) * 2 + tau) * 2 + eta) * 16 + r] = c;
 }
 
+// LDS of a workgroup besides the static arrays: the vectors (two tiles of queries, or one tile of keys
+// and their 32 centering vectors), and per wavefront its two A tiles and the list of its projections
+// that are being re-evaluated.
+constexpr int kFewList = 256;                              // entries per wavefront
+constexpr size_t kFewVectorBytes = 8 * 1024 + 32 * kHeadDim * sizeof(float), kFewTileBytes = 2 * 8 * 64 * sizeof(uint4);
+static size_t few_lds(int P) { return kFewVectorBytes + (size_t)P * (kFewTileBytes + kFewList * sizeof(uint16_t)); }
+
 __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
+  extern __shared__ uint4 few_mem[];
+  uint4* sB = few_mem;                                     // [vector tile][k-step][lane]
+  float (*sMu)[kHeadDim] = reinterpret_cast<float (*)[kHeadDim]>(few_mem + 8 * 64);   // (keys: there is no second tile)
+  uint4* sA = few_mem + kFewVectorBytes / 16 + (threadIdx.x >> 6) * (2 * 8 * 64);     // [tile][k-step][lane]
+  uint16_t* list = reinterpret_cast<uint16_t*>(few_mem + kFewVectorBytes / 16 + a.P * (2 * 8 * 64)) + (threadIdx.x >> 6) * kFewList;
   __shared__ uint32_t sTail[16][32];                       // plane words of the last table group, [plane][key]
-  __shared__ float sMu[32][kHeadDim];                      // centering vectors of the 32 keys of a key group
-  __shared__ uint4 sX[8][16], sW[8][16];                   // per wavefront: a vector / a projector column being re-evaluated
   __shared__ long long sLimbs[8][kLimbs];
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -147,11 +157,12 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
   } else {
     const int r = grp * 32 + kap;
     ok[0] = r < a.n_krows;
-    const int64_t rr = ok[0] ? r : 0;
-    unit = rr / a.n_keys;
-    key = first_key + rr % a.n_keys;
-    rp[0] = reinterpret_cast<const uint16_t*>(a.Kc) + (unit / a.n_kv_heads) * a.stride_b +
-            (unit % a.n_kv_heads) * a.stride_h + key * a.stride_n;
+    // (at most 128 key vectors: 32-bit divisions)
+    const uint32_t rr = ok[0] ? (uint32_t)r : 0u, nk = (uint32_t)a.n_keys, hk = (uint32_t)a.n_kv_heads;
+    unit = rr / nk;
+    key = first_key + rr % nk;
+    rp[0] = reinterpret_cast<const uint16_t*>(a.Kc) + (int64_t)((uint32_t)unit / hk) * a.stride_b +
+            (int64_t)((uint32_t)unit % hk) * a.stride_h + key * a.stride_n;
     rp[1] = rp[0];
   }
   const bool key8 = is_key && a.kv_fp8;                    // the key rows are e4m3 bytes (wave-uniform)
@@ -198,7 +209,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
       const int r = grp * 32 + kk;
       if (r < a.n_krows)
         reinterpret_cast<float4*>(sMu[kk])[piece] =
-            reinterpret_cast<const float4*>(a.mu + (int64_t)(r / a.n_keys) * kHeadDim)[piece];
+            reinterpret_cast<const float4*>(a.mu + (int64_t)((uint32_t)r / (uint32_t)a.n_keys) * kHeadDim)[piece];
     }
   }
   const float wmax = __uint_as_float(a.header[3]);
@@ -274,64 +285,101 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
   const uint32_t vmask = b_my < a.K ? tmask : 0u;
   fl[0] &= vmask;
   fl[1] &= two ? vmask : 0u;
-  // the centering vectors of a key group are staged by the whole workgroup; a wavefront's own
-  // accumulator cells only need the wavefront's own writes to have landed
-  if (centered) __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __builtin_amdgcn_wave_barrier();
-
-  // ---- exact re-evaluation of the flagged projections, one at a time, in LDS and registers ----
-  uint64_t has = __ballot((fl[0] | fl[1]) != 0u);
-  while (has) {
-    const int src = __ffsll((unsigned long long)has) - 1;                    // wave-uniform
-    const uint32_t f0 = __builtin_amdgcn_readlane(fl[0], src), f1 = __builtin_amdgcn_readlane(fl[1], src);
-    const int bt = f0 ? 0 : 1;
-    const int beta = __ffs(f0 ? f0 : f1) - 1;
-    const int el = 31 - beta, tau = el >> 4, r = el & 15;
-    const int hsrc = src >> 5, kap0 = src & 31;
-    const int rho = 8 * (r >> 2) + 4 * hsrc + (r & 3);                        // tile row of the projection
+  // ---- exact re-evaluation of the flagged projections, from LDS, four at a time ----
+  // The vectors go to LDS, a k-step or two per wavefront, and the A tiles of a wavefront that has
+  // flagged something; its flags become a list, and sixteen lanes take an entry, eight elements each.
+  // (One at a time - the two lanes that hold the vector and the two that hold the column wrote them to
+  // LDS, the wavefront formed two products per lane - an entry cost 0.7 us, and a group of 32 keys has up to
+  // eight of them in a wavefront.)
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt)
-      if (tt == tau && kap == rho) {
+  for (int s = 0; s < 8; ++s) {
+    if (s % a.P != wave) continue;
+    sB[s * 64 + lane] = __builtin_bit_cast(uint4, B[0][s]);
+    if (two) sB[(8 + s) * 64 + lane] = __builtin_bit_cast(uint4, B[1][s]);
+  }
+  __syncthreads();
+  if (__ballot((fl[0] | fl[1]) != 0u)) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) sW[wave][s * 2 + hh] = __builtin_bit_cast(uint4, A[tt][s]);
+    for (int tau = 0; tau < 2; ++tau)
+#pragma unroll
+      for (int s = 0; s < 8; ++s) sA[(tau * 8 + s) * 64 + lane] = __builtin_bit_cast(uint4, A[tau][s]);
+    do {
+      // entry: owner lane | vector tile << 6 | bit << 7 (| result << 15)
+      const int mine = __popc(fl[0]) + __popc(fl[1]);
+      const int incl = half_prefix_sum32(mine);
+      const int low = __builtin_amdgcn_readlane(incl, 31), cnt_all = low + __builtin_amdgcn_readlane(incl, 63);
+      const int pos0 = incl - mine + (hh ? low : 0);
+      const int cnt = cnt_all < kFewList ? cnt_all : kFewList;
+      int pos = pos0;
+#pragma unroll
+      for (int bt = 0; bt < 2; ++bt)
+        for (uint32_t f = fl[bt]; f && pos < kFewList; f &= f - 1) list[pos++] = (uint16_t)(lane | bt << 6 | (__ffs(f) - 1) << 7);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      const int slot = lane >> 4, sl = lane & 15;
+      for (int i0 = 0; i0 < cnt; i0 += 4) {
+        const bool on = i0 + slot < cnt;
+        const int e = list[on ? i0 + slot : i0];
+        const int el = 31 - (e >> 7 & 31), r = el & 15, hsrc = e >> 5 & 1, kap0 = e & 31;
+        const int rho = 8 * (r >> 2) + 4 * hsrc + (r & 3);                    // tile row of the projection
+        // elements 8 sl .. 8 sl + 7: k-step sl / 2, lane half sl % 2
+        const int at16 = (sl >> 1) * 64 + (sl & 1) * 32;
+        const uint4 xr = sB[(e >> 6 & 1) * (8 * 64) + at16 + kap0], wr = sA[(el >> 4) * (8 * 64) + at16 + rho];
+        const uint32_t xu[4] = {xr.x, xr.y, xr.z, xr.w}, wu[4] = {wr.x, wr.y, wr.z, wr.w};
+        float mv[8];
+        if (centered) {
+          const float4 m0 = *reinterpret_cast<const float4*>(&sMu[kap0][sl * 8]), m1 = *reinterpret_cast<const float4*>(&sMu[kap0][sl * 8 + 4]);
+          mv[0] = m0.x; mv[1] = m0.y; mv[2] = m0.z; mv[3] = m0.w; mv[4] = m1.x; mv[5] = m1.y; mv[6] = m1.z; mv[7] = m1.w;
+        }
+        double t = 0.0, g = 0.0;
+#pragma unroll
+        for (int d = 0; d < 8; ++d) {
+          const double x = (double)__uint_as_float(d & 1 ? xu[d >> 1] & 0xffff0000u : xu[d >> 1] << 16);
+          const double w64 = (double)__uint_as_float(d & 1 ? wu[d >> 1] & 0xffff0000u : wu[d >> 1] << 16);
+          const double pr = x * w64;                                          // exact
+          t += pr;
+          g += fabs(pr);
+          if (centered) {
+            const double m = (double)mv[d] * w64;                             // exact
+            t -= m;
+            g += fabs(m);
+          }
+        }
+        t = row_sum16(t);
+        g = row_sum16(g);
+        bool bit = t >= 0.0;
+        // (what float64 cannot decide, one at a time)
+        for (uint64_t pending = __ballot(on && sl == 0 && g > 0.0 && fabs(t) <= kF64Slack * g); pending; pending &= pending - 1) {
+          const int at = __ffsll((unsigned long long)pending) - 1;
+          const int pe = __builtin_amdgcn_readlane(e, at), pel = 31 - (pe >> 7 & 31), pr = pel & 15;
+          const uint4* pw = sA + (pel >> 4) * (8 * 64) + 8 * (pr >> 2) + 4 * (pe >> 5 & 1) + (pr & 3);
+          const uint4* px = sB + (pe >> 6 & 1) * (8 * 64) + (pe & 31);
+          auto elem = [](const uint4* base, int d) {
+            const uint16_t v = reinterpret_cast<const uint16_t*>(base + (d >> 4) * 64 + (d >> 3 & 1) * 32)[d & 7];
+            return (double)__uint_as_float((uint32_t)v << 16);
+          };
+          const bool rb = exact_sign_nonneg_wave(
+              sLimbs[wave], [&](int d) { return elem(px, d); }, [&](int d) { return elem(pw, d); },
+              [&](int d) { return centered ? (double)sMu[pe & 31][d] : 0.0; }, centered);
+          if (lane == at) bit = rb;
+        }
+        if (on && sl == 0 && bit) list[i0 + slot] = (uint16_t)(e | 0x8000);
       }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      // the owners take their bits back
+      pos = pos0;
 #pragma unroll
-    for (int bb = 0; bb < 2; ++bb)
-      if (bb == bt && kap == kap0) {
-#pragma unroll
-        for (int s = 0; s < 8; ++s) sX[wave][s * 2 + hh] = __builtin_bit_cast(uint4, B[bb][s]);
-      }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    const uint16_t* xs16 = reinterpret_cast<const uint16_t*>(sX[wave]);
-    const uint16_t* ws16 = reinterpret_cast<const uint16_t*>(sW[wave]);
-    auto xv = [&](int d) { return (double)__uint_as_float((uint32_t)xs16[d] << 16); };
-    auto wv = [&](int d) { return (double)__uint_as_float((uint32_t)ws16[d] << 16); };
-    auto mv = [&](int d) { return centered ? (double)sMu[kap0][d] : 0.0; };
-    const double w0 = wv(lane), w1 = wv(lane + 64);
-    const double p0 = xv(lane) * w0, p1 = xv(lane + 64) * w1;                 // exact products
-    double t = p0 + p1, g = fabs(p0) + fabs(p1);
-    if (centered) {
-      const double m0 = mv(lane) * w0, m1 = mv(lane + 64) * w1;               // exact products
-      t -= m0 + m1;
-      g += fabs(m0) + fabs(m1);
-    }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-      t += __shfl_xor(t, o);
-      g += __shfl_xor(g, o);
-    }
-    bool bit = t >= 0.0;
-    if (g > 0.0 && fabs(t) <= kF64Slack * g) bit = exact_sign_nonneg_wave(sLimbs[wave], xv, wv, mv, centered);
-    if (lane == src) {
-      const uint32_t m = 1u << beta;
-      if (bt == 0) { fl[0] &= ~m; neg[0] = bit ? (neg[0] & ~m) : (neg[0] | m); }
-      else { fl[1] &= ~m; neg[1] = bit ? (neg[1] & ~m) : (neg[1] | m); }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    has = __ballot((fl[0] | fl[1]) != 0u);
+      for (int bt = 0; bt < 2; ++bt)
+        for (uint32_t f = fl[bt]; f && pos < kFewList; f &= f - 1) {
+          const uint32_t m = f & -f;
+          if (list[pos++] & 0x8000) neg[bt] &= ~m;
+          else neg[bt] |= m;
+          fl[bt] &= ~m;
+        }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+    } while (__ballot((fl[0] | fl[1]) != 0u));
   }
 
   // ---- store ----
@@ -418,8 +466,8 @@ hipError_t launch_hash_few(const HashFewArgs& a0, hipStream_t s, hipEvent_t star
   const int k_groups = (a.n_krows + 31) / 32;
   if (a.q_groups + k_groups <= 0) return hipSuccess;
   const dim3 grid((unsigned)a.Wd, (unsigned)(a.q_groups + k_groups)), block(64 * a.P);
-  if (start || stop) hipExtLaunchKernelGGL(hash_few_mfma_kernel, grid, block, 0, s, start, stop, 0, a);
-  else hipLaunchKernelGGL(hash_few_mfma_kernel, grid, block, 0, s, a);
+  if (start || stop) hipExtLaunchKernelGGL(hash_few_mfma_kernel, grid, block, few_lds(a.P), s, start, stop, 0, a);
+  else hipLaunchKernelGGL(hash_few_mfma_kernel, grid, block, few_lds(a.P), s, a);
   return hipGetLastError();
 }
 
