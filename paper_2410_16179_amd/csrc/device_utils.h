@@ -42,23 +42,26 @@ struct Frag {
   uint4 a, b;
 };
 
-// The rows of a decode step are read once: non-temporal loads.
-template <int ET>
+// NT: non-temporal loads (the rows of a decode step are read once).
+template <bool NT, class T>
+__device__ inline T load_hint(const T* p) {
+  if constexpr (NT) return __builtin_nontemporal_load(p);
+  else return *p;
+}
+template <int ET, bool NT = true>
 __device__ inline void frag_load(const void* base, int64_t elem, Frag& f) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
   if constexpr (ET == kFP8) {
     typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    const u32x2 a = __builtin_nontemporal_load(
-        reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(base) + elem));
+    const u32x2 a = load_hint<NT>(reinterpret_cast<const u32x2*>(reinterpret_cast<const uint8_t*>(base) + elem));
     f.a.x = a.x; f.a.y = a.y;
   } else if constexpr (ET == kFP32) {
     const u32x4* p = reinterpret_cast<const u32x4*>(reinterpret_cast<const float*>(base) + elem);
-    const u32x4 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);
+    const u32x4 a = load_hint<NT>(p), b = load_hint<NT>(p + 1);
     f.a = make_uint4(a.x, a.y, a.z, a.w);
     f.b = make_uint4(b.x, b.y, b.z, b.w);
   } else {
-    const u32x4 a = __builtin_nontemporal_load(
-        reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(base) + elem));
+    const u32x4 a = load_hint<NT>(reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(base) + elem));
     f.a = make_uint4(a.x, a.y, a.z, a.w);
   }
 }

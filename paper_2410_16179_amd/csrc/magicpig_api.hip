@@ -74,7 +74,7 @@ int check_strides(int64_t sb, int64_t sh, int64_t sn) {
   return MAGICPIG_OK;
 }
 
-constexpr int64_t kMeanRowsPerChunk = 256;
+constexpr int64_t kMeanRowsPerChunk = mp::kMeanChunkRows;
 constexpr int64_t kFewRows = 128;   // key vectors per call up to which magicpig_hash_keys takes the few-rows kernel
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -426,7 +426,6 @@ int magicpig_key_mean(const magicpig_params* p, const void* K_cache, float* mu_o
   a.is_fp32 = p->dtype == MAGICPIG_FP32;
   a.kv_fp8 = p->kv_dtype == MAGICPIG_KV_FP8_E4M3;
   a.n_kv_heads = p->n_kv_heads; a.units = p->batch * p->n_kv_heads; a.n = p->n_ctx;
-  a.rows_per_chunk = kMeanRowsPerChunk;
   a.nchunk = (int)((p->n_ctx + kMeanRowsPerChunk - 1) / kMeanRowsPerChunk);
   a.stride_b = p->k_stride_b; a.stride_h = p->k_stride_h; a.stride_n = p->k_stride_n;
   const hipError_t e = mp::launch_key_mean(a, reinterpret_cast<hipStream_t>(hip_stream));

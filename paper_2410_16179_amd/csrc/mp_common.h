@@ -175,9 +175,10 @@ struct HashFewArgs {
   int q_groups;                                                 // grid rows that take queries (64 each); the rest take keys (32 each)
 };
 
+constexpr int kMeanChunkRows = 256;   // rows a workgroup of the key mean sums
 struct MeanArgs {
   const void* Kc; float* mu; double* partial;
-  int is_fp32; int kv_fp8; int n_kv_heads; int units; int64_t n; int nchunk; int64_t rows_per_chunk;
+  int is_fp32; int kv_fp8; int n_kv_heads; int units; int64_t n; int nchunk;
   int64_t stride_b, stride_h, stride_n;
 };
 
