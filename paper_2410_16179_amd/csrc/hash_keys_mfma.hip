@@ -12,11 +12,13 @@
 //
 // Bit-exactness.  The hash bit is the sign of the exact sum  k.W_j - mu.W_j.  The MFMA
 // result acc ~ k.W_j - fl(mu.W_j) (the threshold enters as the initial accumulator) differs
-// from it by at most  bound_i = kGamma * (|k_i| + |mu|) * max_j |W_j|:  every bf16 product is
+// from it by at most  kGamma * (|k_i| max_j |W_j| + max_j |mu.W_j|):  every bf16 product is
 // exact in float32, the accumulation inside the matrix core loses at most kGamma of the sum of
-// magnitudes whatever its order and grouping (mp_common.h), and sum|terms| <= (|k_i| + |mu|) |W_j|
-// by Cauchy-Schwarz.
-// Elements with |acc| <= bound_i (a few in ten thousand) are listed in LDS and re-evaluated
+// magnitudes whatever its order and grouping (mp_common.h), the threshold is one term of that sum, and
+// the other terms' magnitudes sum to |k_i| |W_j| at most (Cauchy-Schwarz); the largest threshold is
+// that of the quad of tiles at hand.  (Bounding the threshold by |mu| |W_j|, as if it were summed here,
+// listed 1.4e-3 of the projections instead of 0.9e-3.)
+// Elements with |acc| below that bound are listed in LDS and re-evaluated
 // at the end of the workgroup in float64 with the exact fallback of exact_dot.h, which
 // patches the bit.  Pairs beyond the LDS list go to a global list and finish_hash_keys_kernel
 // (hash_direct.hip); if that overflows too, that kernel redoes the whole call in float64.
@@ -46,7 +48,7 @@ __host__ __device__ inline void tile_row_to_bit(int T, int rho, int* x, int* bet
 // of W for the recheck, largest column norm of the 16 rows.  One thread per (tile row, 8-element piece
 // of d).  The first also clears the counters the later kernels of the call add to.
 // The others, 256 projector columns of one (batch, KV head) each: initial accumulators -fl(mu.W_j) in
-// fragment order, the same sums in float64, |mu|.  A thread takes a column, neighbouring threads
+// fragment order and the same sums in float64.  A thread takes a column, neighbouring threads
 // neighbouring columns, so that W is read in whole lines as it is stored.  (As two launches, the second
 // reading the transposed copy row by row, they took 4.8 + 9.4 us.)
 __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int proj_blocks, int thr_blocks) {
@@ -92,16 +94,6 @@ __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int
   const int at = (int)blockIdx.x - proj_blocks;
   const int unit = at / thr_blocks;
   const float* mu = a.mu ? a.mu + (int64_t)unit * kHeadDim : nullptr;
-  if (at % thr_blocks == 0 && tid < 64) {
-    double ss = 0.0;
-    if (mu) {
-      const double m0 = (double)mu[tid], m1 = (double)mu[tid + 64];
-      ss = m0 * m0 + m1 * m1;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    if (tid == 0) a.munorm[unit] = (float)sqrt(ss) * 1.000001f;
-  }
   // column i of the whole table groups (32 K columns each), then the words that pad the last quad
   const int i = at % thr_blocks * 256 + tid;
   if (i >= a.ntiles * 32) return;
@@ -171,7 +163,6 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   const uint16_t* Kc = reinterpret_cast<const uint16_t*>(a.Kc);
   const int64_t ubase = (int64_t)(unit / a.n_kv_heads) * a.stride_b + (int64_t)(unit % a.n_kv_heads) * a.stride_h;
   bf16x8 B[2][8];
-  float bnd[2];
   int64_t key[2];
   bool key_ok[2];
 #pragma unroll
@@ -195,7 +186,6 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   // largest column norm of the projector (of every 16 tile rows; requested together with the keys)
   float wmax = 0.f;
   for (int i = lane; i < a.ntiles * 2; i += 64) wmax = fmaxf(wmax, a.rownorm[i]);
-  const float munorm = a.munorm[unit];
   float knorm[2];
 #pragma unroll
   for (int bt = 0; bt < 2; ++bt) {
@@ -223,10 +213,11 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   if (blockIdx.x == 0 && unit == 0 && blockIdx.z == 0 && tid == 0) *a.wmax_bits = __float_as_uint(wmax);   // statistics only
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  // flagged iff |acc| < bnd, bnd being just above the rigorous bound (so "<=" is covered)
+  // flagged iff |acc| < bnd = bnd0 + kGamma * largest threshold of the quad, just above the rigorous
+  // bound (so "<=" is covered); masked keys are never flagged
+  float bnd0[2];
 #pragma unroll
-  for (int bt = 0; bt < 2; ++bt)
-    bnd[bt] = key_ok[bt] ? (kGamma * (knorm[bt] + munorm) * wmax) * 1.000001f + 1e-30f : -1.f;
+  for (int bt = 0; bt < 2; ++bt) bnd0[bt] = key_ok[bt] ? (kGamma * knorm[bt] * wmax) * 1.000001f + 1e-30f : -INFINITY;
 
   // The four words a quad produces are stored one quad later, so that the wait for the
   // staged fragments at the end of a quad does not also wait for a store just issued.
@@ -287,6 +278,13 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
     stage_pair(gA + ((int64_t)q * 2 + 1) * 1024, sA1, tid, wave);
     if (more && tid < 128) stt = gThr[(q + 1) * 128 + tid];
 
+    float bnd[2];
+    {
+      const float t0 = fabsf(sThr[cur][lane]), t1 = fabsf(sThr[cur][64 + lane]);   // (padding rows: infinite)
+      const float most = wave_max(fmaxf(t0 < INFINITY ? t0 : 0.f, t1 < INFINITY ? t1 : 0.f));
+      bnd[0] = fmaf(kGamma * 1.000001f, most, bnd0[0]);
+      bnd[1] = fmaf(kGamma * 1.000001f, most, bnd0[1]);
+    }
     uint32_t wd[2][2];                                   // [pair][key tile] inverted bits, MSB first
     uint32_t fl[2][2];                                   // same bit positions: |acc| <= bound
 #pragma unroll

@@ -104,7 +104,6 @@ struct HashMfmaArgs {
   float* thr;                  // [units][ntiles][2][16] initial accumulators
   double* thr64;               // [units][K*L] mu.W_j in float64 (exact products, 128 roundings of 2^-53)
   float* magmu;                // [units][K*L] an upper bound of sum_d |mu_d W_dj|
-  float* munorm;               // [units]
   float* rownorm;              // [ntiles*2] largest norm among the projector columns behind 16 tile rows
   unsigned* wmax_bits;         // max column norm of W (float bits), kept for the statistics
   unsigned* list_count; int* overflow; unsigned* flagged_total;
