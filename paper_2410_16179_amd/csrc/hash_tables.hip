@@ -550,7 +550,12 @@ __global__ __launch_bounds__(1024) void table_lookup_kernel(AttnArgs a, TableArg
 // head marks every key it meets in a "seen" bitmap of the whole indexed range and, when it was
 // already marked, in a "seen twice" bitmap (both in LDS, a bit per key); the ballots are those
 // bitmaps.  No bucket is read more than once per head, whatever the context length.
-__global__ __launch_bounds__(1024) void table_lookup_bitmap_kernel(AttnArgs a, TableArgs tb) {
+// Bound by latency: two workgroups per compute unit (64 registers) so that 512 heads are one round, and
+// the entries of four buckets requested at once, up to 192 of each: at 131072 keys and K = 10 a bucket
+// holds 128 on average, and every second one made a wavefront wait for the rest of it when the first
+// request took 128.  (All buckets of a wavefront at once, 128 entries each, held 96 registers: one
+// workgroup per compute unit, 40 us at 512 heads x 131072 keys, (10,170).)
+__global__ __launch_bounds__(1024, 8) void table_lookup_bitmap_kernel(AttnArgs a, TableArgs tb) {
   extern __shared__ uint32_t bitmap[];                  // seen[nw], twice[nw]
   __shared__ uint32_t bstart[512], blen[512];
   __shared__ uint32_t qs[256];
@@ -578,37 +583,43 @@ __global__ __launch_bounds__(1024) void table_lookup_bitmap_kernel(AttnArgs a, T
     blen[t] = s1 - s0;
   }
   __syncthreads();
-  // wavefront v reads tables v, v+16, ...: up to 128 entries of each bucket are requested before
-  // any is used; longer buckets are finished in a loop
-  constexpr int kMaxB = 32;                             // L <= 512 tables over 16 wavefronts
-  uint32_t e0[kMaxB], e1[kMaxB];
+  // wavefront v reads tables v, v+16, ..., four at a time: up to 192 entries of each bucket are
+  // requested before any is used, and the first atomics (was the key seen before?) are issued
+  // together; longer buckets are finished in a loop
+  constexpr int kChunk = 4, kEntries = 3;
   const int nbk = (a.L - wave + 15) >> 4;
+  for (int k0 = 0; k0 < nbk; k0 += kChunk) {
+    uint32_t e[kChunk * kEntries], before[kChunk * kEntries];
 #pragma unroll
-  for (int k = 0; k < kMaxB; ++k) {
-    e0[k] = 0xffffffffu; e1[k] = 0xffffffffu;
-    if (k < nbk) {
-      const int t = wave + 16 * k;
-      const uint32_t len = blen[t];
-      const uint32_t* p = idxs + (int64_t)t * tb.n_cap + bstart[t];
-      if ((uint32_t)lane < len) e0[k] = p[lane];
-      if ((uint32_t)lane + 64 < len) e1[k] = p[lane + 64];
-    }
-  }
-  auto mark = [&](uint32_t key) {
-    if (key != 0xffffffffu) {
-      const uint32_t bit = 1u << (key & 31);
-      if (atomicOr(&seen[key >> 5], bit) & bit) atomicOr(&twice[key >> 5], bit);
-    }
-  };
+    for (int k = 0; k < kChunk; ++k) {
+      const int t = wave + 16 * (k0 + k);
+      const bool on = k0 + k < nbk;
+      const uint32_t len = on ? __builtin_amdgcn_readfirstlane(blen[t]) : 0u;
+      const uint32_t* p = idxs + (int64_t)(on ? t : 0) * tb.n_cap + (on ? __builtin_amdgcn_readfirstlane(bstart[t]) : 0u);
 #pragma unroll
-  for (int k = 0; k < kMaxB; ++k) {
-    if (k < nbk) {
-      mark(e0[k]);
-      mark(e1[k]);
-      const int t = wave + 16 * k;
-      if (blen[t] > 128) {
-        const uint32_t* p = idxs + (int64_t)t * tb.n_cap + bstart[t];
-        for (uint32_t j = 128 + lane; j < blen[t]; j += 64) mark(p[j]);
+      for (int j = 0; j < kEntries; ++j) {
+        e[k * kEntries + j] = 0xffffffffu;
+        if ((uint32_t)(lane + 64 * j) < len) e[k * kEntries + j] = p[lane + 64 * j];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kChunk * kEntries; ++i) {
+      before[i] = 0u;
+      if (e[i] != 0xffffffffu) before[i] = atomicOr(&seen[e[i] >> 5], 1u << (e[i] & 31));
+    }
+#pragma unroll
+    for (int i = 0; i < kChunk * kEntries; ++i)
+      if (before[i] >> (e[i] & 31) & 1u) atomicOr(&twice[e[i] >> 5], 1u << (e[i] & 31));
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) {
+      const int t = wave + 16 * (k0 + k);
+      if (k0 + k >= nbk) break;
+      const uint32_t len = __builtin_amdgcn_readfirstlane(blen[t]);
+      if (len <= 64 * kEntries) continue;
+      const uint32_t* p = idxs + (int64_t)t * tb.n_cap + __builtin_amdgcn_readfirstlane(bstart[t]);
+      for (uint32_t j = 64 * kEntries + lane; j < len; j += 64) {
+        const uint32_t key = p[j], bit = 1u << (key & 31);
+        if (atomicOr(&seen[key >> 5], bit) & bit) atomicOr(&twice[key >> 5], bit);
       }
     }
   }
