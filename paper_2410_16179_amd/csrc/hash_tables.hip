@@ -10,7 +10,7 @@
 //   the workspace; keys per bucket and window of 16384 keys), ht_offsets_kernel (fill levels of the
 //   buckets at the start of every window, bucket offsets) and ht_place_kernel (one window of one
 //   table per workgroup, sorted in LDS and copied out).  8 KV heads x 98304 keys at (10,150): 113 +
-//   15 + 175 us, against 1806 + 455 us of the first version (one workgroup per (unit, 16 tables)
+//   14 + 175 us, against 1806 + 455 us of the first version (one workgroup per (unit, 16 tables)
 //   walking every window, and a wavefront per piece in the copy).
 //   Without it, ht_build_kernel<false>: histogram of the codes of 32 (or fewer) tables in LDS ->
 //   offsets; ht_build_kernel<true>: second pass, scatters key indices to their buckets (every 4-byte
@@ -313,12 +313,17 @@ __global__ __launch_bounds__(256) void ht_offsets_kernel(TableArgs a) {
   if (t == 0 && unit == 0 && tid == 0) a.header[0] = (uint32_t)a.windows;
   uint32_t* cum = a.wincum + ((int64_t)unit * a.L + t) * a.windows * nb;
   for (int c = tid; c < nb; c += 256) {
+    // (eight windows are read before any is written back: the compiler cannot know that the places differ)
     uint32_t run = 0;
-#pragma unroll 8
-    for (int win = 0; win < a.windows; ++win) {
-      const uint32_t n_c = cum[(int64_t)win * nb + c];
-      cum[(int64_t)win * nb + c] = run;
-      run += n_c;
+    for (int w0 = 0; w0 < a.windows; w0 += 8) {
+      uint32_t n_c[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) n_c[i] = w0 + i < a.windows ? cum[(int64_t)(w0 + i) * nb + c] : 0u;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (w0 + i < a.windows) cum[(int64_t)(w0 + i) * nb + c] = run;
+        run += n_c[i];
+      }
     }
     tot[c] = run;
   }
