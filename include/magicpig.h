@@ -242,7 +242,7 @@ MAGICPIG_API int magicpig_sampled_attention_noalloc(const magicpig_params* param
  * start of every window (room for ceil(n_cap / 16384) windows).  A build with the large
  * workspace orders every bucket by window (keys of window 0 first, ...), which lets a decode
  * step read, for a range of keys, only the piece of a bucket that holds them; inside a
- * window's piece, and in buckets of the one-pass build, the order is unspecified.  Tables are
+ * window's piece, and in buckets of the build without workspace, the order is unspecified.  Tables are
  * rebuilt from the packed
  * key codes; they are not extended incrementally: keys appended after a build are found by
  * scanning their packed codes (see n_indexed below) until the next build. */

@@ -654,7 +654,7 @@ __global__ __launch_bounds__(1024, 8) void table_lookup_bitmap_kernel(AttnArgs a
 hipError_t launch_build_tables(const TableArgs& t, hipStream_t s) {
   if (t.units <= 0 || t.L <= 0) return hipSuccess;
   hipError_t e;
-  if (t.codes16 && t.n > 0) {
+  if (t.codes16) {
     // enough workspace for every key's code per table: buckets ordered by window
     const int T = ht_count_tables(t.K);
     const int64_t groups = (int64_t)(32 / T) * table_words(t.L);

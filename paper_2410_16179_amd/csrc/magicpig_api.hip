@@ -192,7 +192,7 @@ bool tables_supported(const magicpig_params* p) {
   return p->K <= 12 && (int64_t)p->batch * p->n_q_heads <= 65535;
 }
 
-// workspace of the two-pass table build: the code of every key in every table
+// workspace of the table build: the code of every key in every table
 struct BuildWs { size_t codes_off, total; int windows; };
 BuildWs ws_build_layout(const magicpig_params* p) {
   BuildWs w{};

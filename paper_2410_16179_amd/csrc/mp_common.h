@@ -228,7 +228,7 @@ struct TableArgs {
   int64_t n, n_cap, blocks_cap;   // n: keys [0, n) are in the tables
   // build with a large workspace: per-table codes of every key and, for every window of
   // kBuildWindow keys, the number of keys of each bucket in the windows before it
-  uint16_t* codes16;           // [units][L][n_cap] (workspace), or null (one-pass scatter)
+  uint16_t* codes16;           // [units][L][n_cap] (workspace), or null (keys scattered without it)
   uint32_t* wincum;            // [units][L][windows][2^K], part of the tables: with it the piece of a
                                // bucket that holds the keys of one window can be read alone
   int windows;
