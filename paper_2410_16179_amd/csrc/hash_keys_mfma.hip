@@ -12,11 +12,13 @@
 //
 // Bit-exactness.  The hash bit is the sign of the exact sum  k.W_j - mu.W_j.  The MFMA
 // result acc ~ k.W_j - fl(mu.W_j) (the threshold enters as the initial accumulator) differs
-// from it by at most  kGamma * (|k_i| max_j |W_j| + max_j |mu.W_j|):  every bf16 product is
-// exact in float32, the accumulation inside the matrix core loses at most kGamma of the sum of
-// magnitudes whatever its order and grouping (mp_common.h), the threshold is one term of that sum, and
-// the other terms' magnitudes sum to |k_i| |W_j| at most (Cauchy-Schwarz); the largest threshold is
-// that of the quad of tiles at hand.  (Bounding the threshold by |mu| |W_j|, as if it were summed here,
+// from it by at most  kGamma * (|k_i| max_j |W_j| + max_j |mu.W_j|) + kThresholdSlack |mu| max_j |W_j|:
+// every bf16 product is exact in float32, the accumulation inside the matrix core loses at most kGamma
+// of the sum of magnitudes whatever its order and grouping (mp_common.h), the threshold is one term of
+// that sum, and the other terms' magnitudes sum to |k_i| |W_j| at most (Cauchy-Schwarz); the largest
+// threshold is that of the quad of tiles at hand.  The threshold itself is a float64 sum of 128 exact
+// products: where they cancel, its error (127 roundings of 2^-53 of sum_d |mu_d W_dj| <= |mu| |W_j|) is
+// what remains of the last term.  (Bounding the threshold by |mu| |W_j|, as if it were summed here,
 // listed 1.4e-3 of the projections instead of 0.9e-3.)
 // Elements with |acc| below that bound are listed in LDS and re-evaluated
 // at the end of the workgroup in float64 with the exact fallback of exact_dot.h, which
@@ -51,6 +53,7 @@ __host__ __device__ inline void tile_row_to_bit(int T, int rho, int* x, int* bet
 // fragment order and the same sums in float64.  A thread takes a column, neighbouring threads
 // neighbouring columns, so that W is read in whole lines as it is stored.  (As two launches, the second
 // reading the transposed copy row by row, they took 4.8 + 9.4 us.)
+// The first of a (batch, KV head) also writes |mu|.
 __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int proj_blocks, int thr_blocks) {
   __shared__ float smax[4];
   const int tid = threadIdx.x;
@@ -94,6 +97,12 @@ __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int
   const int at = (int)blockIdx.x - proj_blocks;
   const int unit = at / thr_blocks;
   const float* mu = a.mu ? a.mu + (int64_t)unit * kHeadDim : nullptr;
+  if (mu && at % thr_blocks == 0 && tid < 64) {
+    double ss = (double)mu[tid] * (double)mu[tid] + (double)mu[tid + 64] * (double)mu[tid + 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+    if (tid == 0) a.munorm[unit] = (float)sqrt(ss) * 1.000001f;
+  }
   // column i of the whole table groups (32 K columns each), then the words that pad the last quad
   const int i = at % thr_blocks * 256 + tid;
   if (i >= a.ntiles * 32) return;
@@ -186,6 +195,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   // largest column norm of the projector (of every 16 tile rows; requested together with the keys)
   float wmax = 0.f;
   for (int i = lane; i < a.ntiles * 2; i += 64) wmax = fmaxf(wmax, a.rownorm[i]);
+  const float munorm = a.mu ? a.munorm[unit] : 0.f;
   float knorm[2];
 #pragma unroll
   for (int bt = 0; bt < 2; ++bt) {
@@ -217,7 +227,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   // bound (so "<=" is covered); masked keys are never flagged
   float bnd0[2];
 #pragma unroll
-  for (int bt = 0; bt < 2; ++bt) bnd0[bt] = key_ok[bt] ? (kGamma * knorm[bt] * wmax) * 1.000001f + 1e-30f : -INFINITY;
+  for (int bt = 0; bt < 2; ++bt) bnd0[bt] = key_ok[bt] ? ((kGamma * knorm[bt] + kThresholdSlack * munorm) * wmax) * 1.000001f + 1e-30f : -INFINITY;
 
   // The four words a quad produces are stored one quad later, so that the wait for the
   // staged fragments at the end of a quad does not also wait for a store just issued.

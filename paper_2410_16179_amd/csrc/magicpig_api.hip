@@ -86,7 +86,7 @@ size_t ws_mean(const magicpig_params* p) {
 }
 
 // key-hashing workspace (bf16, matrix cores):
-// [A fragments | W transposed | thresholds | thresholds in float64 | their magnitude sums | (unused) |
+// [A fragments | W transposed | thresholds | thresholds in float64 | their magnitude sums | |mu| |
 //  column norms | scalars | flagged-element list]
 struct HashWs { size_t afrag_off, wt_off, thr_off, thr64_off, magmu_off, munorm_off, rownorm_off, scalar_off, list_off, total; int ntiles; uint64_t list_cap; };
 HashWs ws_hash_layout(const magicpig_params* p) {
@@ -463,6 +463,7 @@ int magicpig_hash_keys(const magicpig_params* p, const void* K_cache, const floa
   m.thr = reinterpret_cast<float*>(wsb + wl.thr_off);
   m.thr64 = reinterpret_cast<double*>(wsb + wl.thr64_off);
   m.magmu = reinterpret_cast<float*>(wsb + wl.magmu_off);
+  m.munorm = reinterpret_cast<float*>(wsb + wl.munorm_off);
   m.rownorm = reinterpret_cast<float*>(wsb + wl.rownorm_off);
   m.wmax_bits = reinterpret_cast<unsigned*>(wsb + wl.scalar_off);
   m.list_count = m.wmax_bits + 1;

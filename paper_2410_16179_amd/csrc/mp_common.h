@@ -104,6 +104,7 @@ struct HashMfmaArgs {
   float* thr;                  // [units][ntiles][2][16] initial accumulators
   double* thr64;               // [units][K*L] mu.W_j in float64 (exact products, 128 roundings of 2^-53)
   float* magmu;                // [units][K*L] an upper bound of sum_d |mu_d W_dj|
+  float* munorm;               // [units] |mu| (written and read when there is a centering vector)
   float* rownorm;              // [ntiles*2] largest norm among the projector columns behind 16 tile rows
   unsigned* wmax_bits;         // max column norm of W (float bits), kept for the statistics
   unsigned* list_count; int* overflow; unsigned* flagged_total;
@@ -119,6 +120,9 @@ struct HashMfmaArgs {
 // kGamma * sum|terms| of the exact sum.  A fused 16-term block with truncating alignment gives
 // (16 + 2) * 8 * 2^-23 = 2^-15.8; 2^-15 leaves a factor of 1.8.
 constexpr float kGamma = 3.0517578125e-5f;
+// What a threshold mu.W_j, summed in float64 from exact products, may be off by, over |mu| |W_j|: 127 * 2^-53,
+// below 2^-46; 2^-44 leaves a factor of four.
+constexpr float kThresholdSlack = 5.684341886080802e-14f;
 
 // The projector in the form the few-vectors matrix-core hashing reads (magicpig_prepare_projector):
 // [256-byte header | fragments | transposed copy].  Header words: magic, K, L, float bits of the
