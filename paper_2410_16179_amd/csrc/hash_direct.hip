@@ -288,7 +288,7 @@ __global__ __launch_bounds__(512) void hash_rows_kernel(HashDirectArgs a0, HashD
       float q2 = fmaf(v.x, v.x, fmaf(v.y, v.y, fmaf(v.z, v.z, v.w * v.w)));
 #pragma unroll
       for (int o = 16; o >= 1; o >>= 1) q2 += __shfl_xor(q2, o);
-      if (i4 == 0) sxnorm[rr] = __builtin_sqrtf(q2);
+      if (i4 == 0) sxnorm[rr] = __builtin_sqrtf(q2 + kSquareSlack);
     }
   }
   __syncthreads();
@@ -296,7 +296,8 @@ __global__ __launch_bounds__(512) void hash_rows_kernel(HashDirectArgs a0, HashD
   // First a float32 pass: one fused multiply-add per term.  n roundings of relative size 2^-24
   // at most (n = 128 terms, 257 with a centering vector) give |sum32 - exact| <= n 2^-24 (1 +
   // small) * sum|terms| <= that factor * |x| |w| (Cauchy-Schwarz; with a centering vector
-  // (|x| + |mu|) |w|), plus what underflowing products lose, far below the absolute floor.  The
+  // (|x| + |mu|) |w|), plus what underflowing products lose, far below the absolute floor.  (kSquareSlack:
+  // what underflowing squares lose in the norms.)  The
   // norms are float32 sums of squares (relative error below 1e-5, inside the margin of kClose32
   // over the factor): a result beyond kClose32 |x| |w| has the exact sign.  The few columns with
   // a closer result (a few in ten thousand) are redone in float64, where every product of two
@@ -343,7 +344,7 @@ __global__ __launch_bounds__(512) void hash_rows_kernel(HashDirectArgs a0, HashD
       }
     }
   }
-  const float wnorm = __builtin_sqrtf(w2);
+  const float wnorm = __builtin_sqrtf(w2 + kSquareSlack);
   float m32[2] = {sxnorm[0] * wnorm, sxnorm[1] * wnorm};
   if (with_mu) {
     s32[0] += s32[1];                                    // one more rounding, inside the factor

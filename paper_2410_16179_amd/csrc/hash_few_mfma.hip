@@ -222,7 +222,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
 #pragma unroll
   for (int bt = 0; bt < 2; ++bt) {
     if (bt == 1 && !two) break;
-    float ss = 0.f;
+    float ss = kSquareSlack;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const uint4 raw = __builtin_bit_cast(uint4, B[bt][s]);
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
     }
     ss += __shfl_xor(ss, 32);                              // the other half of the row
     const float xnorm = sqrtf(ss) * 1.00002f;
-    bnd[bt] = ok[bt] ? (kGamma * (xnorm + munorm) * wmax) * 1.000001f + 1e-30f : -1.f;
+    bnd[bt] = ok[bt] ? (kGamma * (xnorm + munorm) * (wmax + kNormSlack)) * 1.000001f + 1e-30f : -1.f;
   }
 
   // ---- multiply ----

@@ -12,7 +12,8 @@
 // within kGammaF32 |x| |W_j| of the exact sum: one rounding of the difference, one of every product
 // (2^-24 each) and the accumulation of 128 products in any order and grouping, each step losing at
 // most 2^-23 of the running magnitude, 2^-16 + 2^-22.4 in all; 2^-15 leaves a factor of two.
-// (Cauchy-Schwarz over the terms; the floor added to it covers products below the normal range.)
+// (Cauchy-Schwarz over the terms; the floor added to it covers products below the normal range,
+// kSquareSlack what their squares lose in the norms.)
 // Results inside that bound are listed in LDS - the list holds every pair of the workgroup, so it
 // cannot overflow - and re-evaluated in float64 from exact products, and what float64 cannot decide
 // is summed exactly (exact_dot.h).
@@ -59,7 +60,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
 
     // ---- B operand: k - mu, lane half hh holds the elements 64 hh .. 64 hh + 63 ----
     float B[64];
-    float ss = 0.f;
+    float ss = kSquareSlack;
     {
       const float4* kr = reinterpret_cast<const float4*>(X + krow * a.stride_n + 64 * hh);
 #pragma unroll
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
       // 16 elements of the column are requested while the 16 before them are multiplied
       const uint32_t at = (uint32_t)(64 * hh * ncol + (col_ok ? j : 0));   // (128 * 8192 elements at most)
       float A[2][16];
-      float w2 = 0.f;
+      float w2 = kSquareSlack;
       f32x16 acc;
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[r] = 0.f;

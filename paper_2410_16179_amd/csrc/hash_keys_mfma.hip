@@ -123,7 +123,7 @@ __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int
     c = 0.0f - (float)th;                              // +0 when the threshold is zero
     // for the exact re-evaluation: the same sum in float64 and a float32 upper bound of its magnitude sum
     a.thr64[(int64_t)unit * ncol + i] = th;
-    a.magmu[(int64_t)unit * ncol + i] = (float)mg * 1.000001f;
+    a.magmu[(int64_t)unit * ncol + i] = mg > 0.0 ? (float)mg * 1.000001f + 2e-45f : 0.f;   // (2e-45: what the conversion loses below the normal range)
   }
   // word x, bit beta: tile 2 (x / 2) + el / 16, lane half x % 2, register el % 16, el = 31 - beta
   const int el = 31 - beta, T = 2 * (x >> 1) + (el >> 4);
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
     // |k|^2 by v_dot2_f32_bf16 (two exact products per instruction, float32 accumulation: the
     // relative error of the norm, below 1e-5, is inside the margin of kGamma)
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    float ss = 0.f;
+    float ss = kSquareSlack;
 #pragma unroll
     for (int s = 0; s < 8; ++s) {
       const uint4 raw = __builtin_bit_cast(uint4, B[bt][s]);
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
   // bound (so "<=" is covered); masked keys are never flagged
   float bnd0[2];
 #pragma unroll
-  for (int bt = 0; bt < 2; ++bt) bnd0[bt] = key_ok[bt] ? ((kGamma * knorm[bt] + kThresholdSlack * munorm) * wmax) * 1.000001f + 1e-30f : -INFINITY;
+  for (int bt = 0; bt < 2; ++bt) bnd0[bt] = key_ok[bt] ? ((kGamma * knorm[bt] + kThresholdSlack * munorm) * (wmax + kNormSlack)) * 1.000001f + 1e-30f : -INFINITY;
 
   // The four words a quad produces are stored one quad later, so that the wait for the
   // staged fragments at the end of a quad does not also wait for a store just issued.

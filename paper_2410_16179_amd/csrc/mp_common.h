@@ -120,6 +120,13 @@ struct HashMfmaArgs {
 // kGamma * sum|terms| of the exact sum.  A fused 16-term block with truncating alignment gives
 // (16 + 2) * 8 * 2^-23 = 2^-15.8; 2^-15 leaves a factor of 1.8.
 constexpr float kGamma = 3.0517578125e-5f;
+// The norms in these bounds are float32 square roots of float32 sums of 128 squares.  A square below the
+// normal range may lose all of itself, 2^-126 at most, 128 of them 2^-119: the sums start from 2^-118, or a
+// norm is raised by the root of that.  (Times the other norm this also covers inputs below the normal range
+// that the matrix core may take as zero; products below it are covered by a floor of 1e-30 on the bound.)
+constexpr float kSquareSlack = 3.0092655e-36f;             // 2^-118
+constexpr float kNormSlack = 1.7347235e-18f;               // 2^-59
+
 // What a threshold mu.W_j, summed in float64 from exact products, may be off by, over |mu| |W_j|: 127 * 2^-53,
 // below 2^-46; 2^-44 leaves a factor of four.
 constexpr float kThresholdSlack = 5.684341886080802e-14f;

@@ -69,13 +69,40 @@ __device__ inline void recheck_pairs(const HashMfmaArgs& a, long long* limb, uin
       magf += __shfl_xor(magf, o);
     }
     double mag = (double)(magf * 1.0001f);
+    // float32 products below 2^-126 are rounded to multiples of 2^-149, 1e-42 for 128 of them, or vanish: where
+    // all are about that small they are formed again in float64, exactly
+    double lost = 1e-42;
+    if (__ballot(on && magf < 1e-30f)) {
+      double s64 = 0.0, mag64 = 0.0;
+#pragma unroll
+      for (int p = 0; p < kPieces; ++p) {
+        const uint32_t ku[4] = {kraw[p].x, kraw[p].y, kraw[p].z, kraw[p].w};
+        const uint32_t wu[4] = {wraw[p].x, wraw[p].y, wraw[p].z, wraw[p].w};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const double p0 = (double)__uint_as_float(ku[t] << 16) * (double)__uint_as_float(wu[t] << 16);
+          const double p1 = (double)__uint_as_float(ku[t] & 0xffff0000u) * (double)__uint_as_float(wu[t] & 0xffff0000u);
+          s64 += p0;
+          s64 += p1;
+          mag64 += fabs(p0);
+          mag64 += fabs(p1);
+        }
+      }
+#pragma unroll
+      for (int o = LPP / 2; o > 0; o >>= 1) {
+        s64 += __shfl_xor(s64, o);
+        mag64 += __shfl_xor(mag64, o);
+      }
+      s = s64;
+      mag = mag64;
+      lost = 0.0;
+    }
     if (a.mu) {
       s -= a.thr64[unit * (a.K * a.L) + j];
       mag += (double)a.magmu[unit * (a.K * a.L) + j];
     }
     bool bit = s >= 0.0;
-    // (1e-42: float32 products below 2^-126 are rounded to multiples of 2^-149; 128 of them)
-    const bool unsure = on && sl == 0 && mag > 0.0 && fabs(s) <= kF64Slack * mag + 1e-42;
+    const bool unsure = on && sl == 0 && mag > 0.0 && fabs(s) <= kF64Slack * mag + lost;
     uint64_t pending = __ballot(unsure);
     while (pending) {
       const int src = __ffsll((unsigned long long)pending) - 1;

@@ -29,6 +29,18 @@ def _check_keys(oracle, rows, W, mu, K, L, dtype, kv=""):
     return want
 
 
+def _check_queries(oracle, rows, W, K, L, dtype):
+    want = oracle.hash_query(rows, W, K, L)
+    none = np.zeros((1, len(rows) // 8, 1, 128), np.float32)
+    s = Session(K=K, L=L, dtype=dtype, Kc=none, Vc=none, q=rows[None], W=W)
+    s.hash_query()
+    np.testing.assert_array_equal(s.query_table_codes()[0], want, err_msg="queries, plain projector")
+    s.prepare()
+    s.q_codes.fill_(0)
+    s.hash_query_prepared()
+    np.testing.assert_array_equal(s.query_table_codes()[0], want, err_msg="queries, prepared projector")
+
+
 @pytest.mark.parametrize("K,L", [(2, 3), (10, 150)])
 @pytest.mark.parametrize("dtype,kv,big,tiny", [("bf16", "", 2.0 ** 30, 2.0 ** -30), ("bf16", "fp8", 2.0 ** 50, 2.0 ** -8),
                                                ("fp32", "", 2.0 ** 30, 2.0 ** -30)])
@@ -45,3 +57,48 @@ def test_centering_vector_that_cancels(oracle, K, L, dtype, kv, big, tiny):
     rows[3::4, :2] = tiny / 2, tiny
     want = _check_keys(oracle, rows, W, mu, K, L, dtype, kv)
     assert (want[0] == 0).all() and (want[1] == (1 << K) - 1).all()
+
+
+def _near_hyperplanes(rng, W, n, scale):
+    """n float32 rows of about `scale` per element, each orthogonal to one column of W up to its own rounding."""
+    x = rng.standard_normal((n, 128))
+    w = W.astype(np.float64)[:, rng.integers(0, W.shape[1], n)].T
+    x -= w * ((x * w).sum(1) / (w * w).sum(1))[:, None]
+    return (scale * x).astype(np.float32)
+
+
+@pytest.mark.parametrize("xs,ws", [(2e-23, 1.0), (1e-25, 1.0), (2e-23, 1e8), (1.0, 2e-23), (1e9, 1e-24), (2e-23, 2e-23), (1e-19, 1e-19)])
+def test_float32_norms_below_the_normal_range(oracle, xs, ws):
+    # the squares of such elements underflow in float32: a bound from norms alone would be nothing
+    print(f"[case] tiny norms, float32, {xs} {ws}", flush=True)
+    K, L = 8, 20
+    rng = np.random.default_rng(5)
+    W = (ws * rng.standard_normal((128, K * L))).astype(np.float32)
+    rows = _near_hyperplanes(rng, W, 330, xs)
+    rows[7] = 0
+    _check_keys(oracle, rows, W, None, K, L, "fp32")
+    # the same distances to a centering vector of that size
+    mu = (4 * xs * rng.standard_normal(128)).astype(np.float32)
+    _check_keys(oracle, rows + mu, W, mu, K, L, "fp32")
+    _check_queries(oracle, rows[:40], W, K, L, "fp32")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("e,we", [(-75, 0), (-80, 30), (-60, -80), (0, -75), (-75, -75), (-10, 20)])
+def test_tiny_terms_that_a_large_pair_hides(oracle, dtype, e, we):
+    # two elements of 2^e that cancel, 120 of -2^(e-27) and one that is 60 times as large, so that the sum is
+    # -60 * 2^(e-27), or +60 * 2^(e-27), whatever a float32 sum in some order makes of it
+    print(f"[case] hidden terms {dtype} {e} {we}", flush=True)
+    K, L = 4, 40
+    W = np.full((128, K * L), 2.0 ** we, np.float32)
+    W[:, 1::2] *= -1
+    rng = np.random.default_rng(1)
+    rows = np.zeros((256, 128), np.float32)
+    for i in range(len(rows)):
+        at = rng.permutation(128)
+        sign = 1.0 if i & 1 else -1.0
+        rows[i, at[:2]] = 2.0 ** e, -(2.0 ** e)
+        rows[i, at[2:122]] = sign * 2.0 ** (e - 27)
+        rows[i, at[122]] = -sign * 60 * 2.0 ** (e - 27)
+    _check_keys(oracle, rows, W, None, K, L, dtype)
+    _check_queries(oracle, rows[:72], W, K, L, dtype)
