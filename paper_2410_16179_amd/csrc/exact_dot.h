@@ -23,7 +23,7 @@ __device__ inline void limb_add(long long* limb, double p) {
   const uint64_t bits = (uint64_t)__double_as_longlong(p);
   const int E = (int)((bits >> 52) & 0x7ff);
   uint64_t M = bits & ((1ull << 52) - 1);
-  if (E == 0) return;                       // zero (float64 subnormals cannot occur here)
+  if (E == 0 || E == 0x7ff) return;         // zero (float64 subnormals cannot occur here); not finite: no digit stands for it
   M |= 1ull << 52;
   int shift = E - 1075 + 298;               // p = M * 2^(E-1075); lowest possible bit is 2^-298
   if (shift < 0) { M >>= -shift; shift = 0; }   // the dropped bits are zero by construction

@@ -102,3 +102,29 @@ def test_tiny_terms_that_a_large_pair_hides(oracle, dtype, e, we):
         rows[i, at[122]] = -sign * 60 * 2.0 ** (e - 27)
     _check_keys(oracle, rows, W, None, K, L, dtype)
     _check_queries(oracle, rows[:72], W, K, L, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_rows_that_are_not_finite_leave_the_others_alone(oracle, dtype):
+    # the exact sums of the rows beside them (every third row cancels to nothing or nearly so) are untouched
+    print(f"[case] infinite rows {dtype}", flush=True)
+    K, L = 4, 40
+    rng = np.random.default_rng(3)
+    W = np.where(rng.random((128, K * L)) < 0.5, -1.0, 1.0).astype(np.float32)
+    W[1] = W[0]
+    rows = np.zeros((256, 128), np.float32)
+    rows[0::3, :3] = 2.0 ** 60, -(2.0 ** 60), 2.0 ** -60
+    rows[1::3] = rng.integers(-8, 9, (len(rows[1::3]), 128))
+    rows[2::3, 4] = np.inf
+    rows[2::6, 4] = -np.inf
+    ok = np.isfinite(rows).all(1)
+    want = oracle.hash_keys(rows[ok], W, None, K, L)
+    s = Session(K=K, L=L, dtype=dtype, Kc=rows[None, None], Vc=rows[None, None], q=np.zeros((1, 1, 128), np.float32), W=W)
+    s.hash_keys()
+    np.testing.assert_array_equal(s.key_table_codes()[0, 0][ok], want)
+    s.prepare()
+    for code in (s.hash_keys, s.hash_keys_prepared):
+        s.key_codes.fill_(0x5a5a5a5a)
+        for first in range(0, 256, 64):
+            code(first, 64)
+        np.testing.assert_array_equal(s.key_table_codes()[0, 0][ok], want)
