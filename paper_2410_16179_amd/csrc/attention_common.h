@@ -369,8 +369,35 @@ __device__ inline void request_head_vectors(const AttnArgs& a, int unit, int64_t
   }
 }
 
+// (output, max, sum) of the keys a wavefront attended; lane l holds elements 8 (l % 16) .. + 7 of the output.
+struct WavePartial {
+  float o[8], m, l;
+};
+__device__ inline void store_partial(const WavePartial& w, float* pp) {
+  const int lane = threadIdx.x & 63;
+  if (lane < 16) {
+    *reinterpret_cast<float4*>(pp + lane * 8) = make_float4(w.o[0], w.o[1], w.o[2], w.o[3]);
+    *reinterpret_cast<float4*>(pp + lane * 8 + 4) = make_float4(w.o[4], w.o[5], w.o[6], w.o[7]);
+  }
+  if (lane == 0) { pp[128] = w.m; pp[129] = w.l; }
+}
+// Takes the partial of another wavefront (stored at pp, in LDS) into w.
+__device__ inline void join_partial(WavePartial& w, const float* pp) {
+  const int sl = threadIdx.x & 15;
+  const float m1 = pp[128], m = fmaxf(w.m, m1);
+  if (m > -INFINITY) {                                     // (wave-uniform; otherwise neither attended a key)
+    const float4 a = *reinterpret_cast<const float4*>(pp + sl * 8), b = *reinterpret_cast<const float4*>(pp + sl * 8 + 4);
+    const float o1[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    const float s0 = __expf(w.m - m), s1 = __expf(m1 - m);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w.o[e] = s0 * w.o[e] + s1 * o1[e];
+    w.l = s0 * w.l + s1 * pp[129];
+    w.m = m;
+  }
+}
+
 // One wavefront attends the keys key_of(0) .. key_of(total - 1) of query head bh (KV unit
-// `unit`) and stores one (output[128], max, sum) partial at `pp`.  A quarter wavefront holds
+// `unit`).  A quarter wavefront holds
 // one 128-element row; all K and V rows of a batch (kIters rows per quarter wavefront) are
 // requested before any is used; q.k, q.(k-mu), |k-mu|^2 are reduced over the 16 lanes of a
 // row; the inclusion probability and the logit q.k/sqrt(d) - log u are evaluated once per key
@@ -378,8 +405,8 @@ __device__ inline void request_head_vectors(const AttnArgs& a, int unit, int64_t
 // online max/sum softmax accumulates the weighted V rows.
 // ET: element type of the K / V caches (kBF16, kFP32, or kFP8 with bf16 queries).
 template <int ET, int kIters, class KeyOf>
-__device__ inline void gather_estimate_wave(const AttnArgs& a, int unit, int64_t bh, int total, int n_sampled,
-                                            const HeadVectors<ET == kFP32>& hv, KeyOf key_of, float* pp) {
+__device__ inline WavePartial gather_estimate_wave(const AttnArgs& a, int unit, int64_t bh, int total, int n_sampled,
+                                                   const HeadVectors<ET == kFP32>& hv, KeyOf key_of) {
   static_assert(kIters >= 1 && kIters <= 16, "one lane of a quarter wavefront per row of a batch");
   constexpr bool FP32 = ET == kFP32;
   const int lane = threadIdx.x & 63;
@@ -486,16 +513,16 @@ __device__ inline void gather_estimate_wave(const AttnArgs& a, int unit, int64_t
       for (int e = 0; e < 8; ++e) o[e] += wv * vv[e];
     }
   }
+  WavePartial w;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     o[e] += __shfl_xor(o[e], 16);
     o[e] += __shfl_xor(o[e], 32);
+    w.o[e] = o[e];
   }
-  if (lane < 16) {
-    *reinterpret_cast<float4*>(pp + sl * 8) = make_float4(o[0], o[1], o[2], o[3]);
-    *reinterpret_cast<float4*>(pp + sl * 8 + 4) = make_float4(o[4], o[5], o[6], o[7]);
-  }
-  if (lane == 0) { pp[128] = m_run; pp[129] = l_run; }
+  w.m = m_run;
+  w.l = l_run;
+  return w;
 }
 
 }  // namespace mp

@@ -118,9 +118,8 @@ size_t ws_hash_for(const magicpig_params* p, int64_t n_keys) {
 }
 
 // decode workspace: [partials | ballots]
-struct AttnWs { size_t partial_off, masks_off, total; int nranges, nscan, f_nranges, f_wave_blocks, f_parts, f_touch; int64_t n_static; };
-// `bytes`: what there is for the partials (the size queries ask with no bound).
-AttnWs ws_attention_layout(const magicpig_params* p, size_t bytes = SIZE_MAX) {
+struct AttnWs { size_t partial_off, masks_off, total; int nranges, nscan, f_nranges, f_wave_blocks, f_touch; int64_t n_static; };
+AttnWs ws_attention_layout(const magicpig_params* p) {
   AttnWs w{};
   const int64_t nblk = mp::key_blocks(p->n_ctx);
   const size_t heads = (size_t)p->batch * p->n_q_heads;
@@ -134,17 +133,17 @@ AttnWs ws_attention_layout(const magicpig_params* p, size_t bytes = SIZE_MAX) {
   // The one-launch scan + gather: one workgroup per run of 4 wave_blocks key blocks.
   const int64_t units = (int64_t)p->batch * p->n_kv_heads;
   auto runs = [&](int wb) { return (nblk + 4 * wb - 1) / (4 * wb); };
-  // Least scratch that a step is promised to run with: runs of the shortest length whose workgroups
-  // fit a round of 780, or of 24 blocks.
+  // Partials per head that there is room for: those of the other forms, and of runs of the shortest length
+  // whose workgroups fit a round of 780, or of 24 blocks.
   int wb0 = 1;
   const int64_t fits = mp::kFusedFill + mp::kFusedFill / 64;
   while (wb0 < mp::kFusedWaveBlocks && units * runs(wb0) > fits) ++wb0;
-  size_t least = (size_t)(runs(wb0) > w.nranges ? runs(wb0) : w.nranges);
-  if ((size_t)lg > least) least = (size_t)lg;
-  const size_t per = heads * mp::kPartialStride * sizeof(float);   // one partial of every head
-  // Length of the runs.  (a) The shortest whose workgroups are resident at once, three per compute unit
-  // (kFusedFill, give or take a dozen): a second, mostly empty round starts late and ends last.  (b) If
-  // there is none, or a KV head has one query head (its gather is the work of one or two wavefronts:
+  int64_t most = runs(wb0) > w.nranges ? runs(wb0) : w.nranges;
+  if (lg > most) most = lg;
+  // Length of the runs, from the sizes alone and with no more partials than that, so that the result of a step
+  // does not depend on the scratch it is given.  (a) The shortest whose workgroups are resident at once, three
+  // per compute unit (kFusedFill, give or take a dozen): a second, mostly empty round starts late and ends last.
+  // (b) If there is none, or a KV head has one query head (its gather is the work of one or two wavefronts:
   // short runs), four per compute unit, with the kernel compiled for that.  (c) Otherwise the rounds are
   // many: the compute unit that gets most blocks takes longest, r workgroups of 4 wb blocks and about
   // two blocks' worth of time besides for each (its gather).
@@ -156,32 +155,21 @@ AttnWs ws_attention_layout(const magicpig_params* p, size_t bytes = SIZE_MAX) {
   const int G = p->n_q_heads / p->n_kv_heads;
   const int64_t all = 4 * mp::kNumCU;
   int wb = 1;
-  while (wb < mp::kFusedWaveBlocks && units * runs(wb) > (G == 1 ? all : fits)) ++wb;
+  while (wb < mp::kFusedWaveBlocks && (units * runs(wb) > (G == 1 ? all : fits) || runs(wb) > most)) ++wb;
   if (units * runs(wb) > fits && units * runs(wb) <= all) {
-    while (wb > 1 && units * runs(wb - 1) <= all) --wb;
+    while (wb > 1 && units * runs(wb - 1) <= all && runs(wb - 1) <= most) --wb;
   } else if (units * runs(wb) > all) {
     int64_t best = INT64_MAX;
     for (int v = 1; v <= mp::kFusedWaveBlocks; ++v) {
       const int64_t r = (units * runs(v) + mp::kNumCU - 1) / mp::kNumCU, cost = r * (4 * v + 2);
-      if (cost <= best) { best = cost; wb = v; }           // (equal: fewer partials)
+      if (runs(v) <= most && cost <= best) { best = cost; wb = v; }           // (equal: fewer partials)
     }
   }
   w.f_wave_blocks = wb;
-  w.f_parts = mp::scan_parts(mp::tuned_tables(p->K, p->L) ? p->K : 0, G);
-  // More partials than the promised scratch holds only where there is room for them, and where the call
-  // with the library's own scratch has it too (its result is the same bit for bit).
-  const size_t want = (size_t)runs(wb) * w.f_parts * per, own = MAGICPIG_STATIC_SCRATCH_BYTES;
-  if (want > bytes || (want > own && least * per <= own)) {
-    w.f_wave_blocks = wb0;
-    w.f_parts = 1;
-  }
-  w.f_touch = units * runs(w.f_wave_blocks) > fits;
-  w.f_nranges = (int)runs(w.f_wave_blocks);
-  size_t most = (size_t)w.f_nranges * w.f_parts;
-  if (least > most) most = least;
-  if (bytes != SIZE_MAX) most = least;
+  w.f_touch = units * runs(wb) > fits;
+  w.f_nranges = (int)runs(wb);
   w.partial_off = 0;
-  w.masks_off = align256(per * most);
+  w.masks_off = align256(heads * (size_t)most * mp::kPartialStride * sizeof(float));
   w.total = w.masks_off + align256(heads * (size_t)nblk * sizeof(uint64_t));
   return w;
 }
@@ -323,7 +311,7 @@ int run_attention_impl(const magicpig_params* p, const void* q, const void* K_ca
   if (!aligned16(q) || !aligned16(K_cache) || !aligned16(V_cache) || !aligned16(key_codes) || !aligned16(tables) ||
       !aligned16(q_codes) || !aligned16(out) || !aligned16(workspace) || (mu && !aligned16(mu)))
     return MAGICPIG_INVALID_ARG;
-  const AttnWs wl = ws_attention_layout(p, use_static_scratch ? (size_t)MAGICPIG_STATIC_SCRATCH_BYTES : workspace_bytes);
+  const AttnWs wl = ws_attention_layout(p);
   if (use_static_scratch) {
     // everything above ran without a GPU call; the library's own scratch replaces the workspace
     if (wl.masks_off > (size_t)MAGICPIG_STATIC_SCRATCH_BYTES) return MAGICPIG_SCRATCH_TOO_SMALL;
@@ -338,7 +326,7 @@ int run_attention_impl(const magicpig_params* p, const void* q, const void* K_ca
   a.partial = reinterpret_cast<float*>(wsb + wl.partial_off); a.out = out;
   a.masks = reinterpret_cast<uint64_t*>(wsb + wl.masks_off);
   a.nranges = wl.nranges; a.nscan = wl.nscan; a.n_static = wl.n_static;
-  a.f_nranges = wl.f_nranges; a.f_wave_blocks = wl.f_wave_blocks; a.f_parts = wl.f_parts; a.f_touch = wl.f_touch;
+  a.f_nranges = wl.f_nranges; a.f_wave_blocks = wl.f_wave_blocks; a.f_touch = wl.f_touch;
   a.dbg_counts = dbg_counts; a.dbg_cand = dbg_cand; a.dbg_ncand = dbg_ncand; a.dbg_cand_cap = dbg_cand_cap;
   a.dbg_stride = p->n_ctx; a.n_dev = p->n_ctx_dev;
   a.is_fp32 = p->dtype == MAGICPIG_FP32;

@@ -215,10 +215,9 @@ struct AttnArgs {
   int nranges;               // partials per head: nscan runs of kRangeBlocks key blocks + static runs
   int nscan;                 // runs of kRangeBlocks key blocks per head
   int64_t n_static;          // keys in the static set T
-  // scan and gather in one launch: one workgroup, and f_parts partials per head, for every run of
-  // 4 * f_wave_blocks key blocks (f_wave_blocks: key blocks per wavefront, 1 .. kFusedWaveBlocks;
-  // f_parts: wavefronts that share a head's keys, 1 or 2)
-  int f_nranges, f_wave_blocks, f_parts;
+  // scan and gather in one launch: one workgroup, and one partial per head, for every run of
+  // 4 * f_wave_blocks key blocks (f_wave_blocks: key blocks per wavefront, 1 .. kFusedWaveBlocks)
+  int f_nranges, f_wave_blocks;
   int f_touch;               // 1: more than three workgroups per compute unit (wavefronts touch the rows of the keys of their last block)
   // lookup + gather in one launch: slices of the indexed range; the first lg_app_runs of them
   // also take a run of 16 appended key blocks each
@@ -257,17 +256,6 @@ constexpr int kFusedWaveBlocks = 6;           // most key blocks a wavefront sca
 constexpr int kFusedBlocks = 4 * kFusedWaveBlocks;        // most key blocks per workgroup
 constexpr int kFusedFill = 768;               // workgroups of it that are resident at once (3 per compute unit)
 constexpr int kFusedIters = 8;             // its gather batch: rows per quarter wavefront
-
-// Table sets that the scan is compiled for (K, ceil(L/32) and the last group's tables known); the others
-// go through one form laid out for 1, 2, 4 or 8 heads per KV head.
-inline bool tuned_tables(int K, int L) {
-  return (K == 10 && (L == 150 || L == 170 || L == 220)) || (K == 9 && L == 120) || (K == 8 && L == 75) || (K == 11 && L == 300);
-}
-// Most wavefronts that share the keys of a run and head in the one-launch scan + gather (KT, HT: compile-time
-// K, 0 for the form for any, and the heads that form is laid out for): two where a workgroup serves
-// one head.  Measured for the kernel with its merge: 32 KV heads x 20011 keys, (9,110), 34.1 -> 32.5 us; 8 x
-// 60000, (8,90), 27.8 -> 26.9; four wavefronts, or two heads shared by two each, gained nothing.
-constexpr int scan_parts(int KT, int HT) { return KT == 0 && HT == 1 ? 2 : 1; }
 
 // host-side launchers (defined next to their kernels)
 hipError_t launch_finish_hash_keys(const HashMfmaArgs& m, const HashDirectArgs& a, hipStream_t s);

@@ -111,13 +111,20 @@ __global__ __launch_bounds__(512) void gather_estimate_kernel(AttnArgs a) {
   }
   float* pp = a.partial + (bh * a.nranges + range) * kPartialStride;
   if (!is_static) {
-    gather_estimate_wave<ET, kGatherIters<ET>>(a, unit, bh, total, total, hv,
-                               [&](int cc) { return blk0 * kBlockKeys + (int64_t)list[cc]; }, pp);
+    store_partial(gather_estimate_wave<ET, kGatherIters<ET>>(a, unit, bh, total, total, hv,
+                               [&](int cc) { return blk0 * kBlockKeys + (int64_t)list[cc]; }), pp);
   } else {
-    gather_estimate_wave<ET, kGatherIters<ET>>(a, unit, bh, total, 0, hv,
-                               [&](int cc) { return static_key(a, c, static_first + cc); }, pp);
+    store_partial(gather_estimate_wave<ET, kGatherIters<ET>>(a, unit, bh, total, 0, hv,
+                               [&](int cc) { return static_key(a, c, static_first + cc); }), pp);
   }
 }
+
+// Wavefronts that share the keys of a run and head in the one-launch scan + gather (KT, HT: compile-time K, 0
+// for the form for any, and the heads that form is laid out for): two where a workgroup serves one head.
+// They join their partials in LDS.  Measured with the merge, (9,110): 32 KV heads x 20011 keys one wavefront
+// 34.1 us, two 31.3 (32.1 with a partial each); one KV head x 100000 keys 18.2 (22.8 with a partial each: the
+// merge of 782 partials is one workgroup's work).  Four wavefronts, or two heads shared by two each, gained nothing.
+template <int KT, int HT> constexpr int kScanParts = KT == 0 && HT == 1 ? 2 : 1;
 
 // Scan and gather in one launch (the whole context is scanned, no hash tables): a workgroup of
 // four wavefronts compares a run of up to kFusedBlocks = 24 consecutive code blocks with the G
@@ -140,7 +147,7 @@ __global__ __launch_bounds__(512) void gather_estimate_kernel(AttnArgs a) {
 // at once; workgroups that start late end last).  The keys of the static set T are dealt over
 // the runs of their KV head (key j to run j mod runs) and join the gather batches there, so
 // they cost neither workgroups nor batches nor partials of their own.
-// One partial per (head, run).
+// One partial per (head, run); where two wavefronts share a head's keys (kScanParts) they join theirs in LDS.
 // DBG: with the debug outputs (counts, candidate lists).
 // KT, WDT, LT: see scan_blocks; KT = 0: any K and L, WDT = the heads scan_block_any is laid out for.
 // ET: element type of the caches (kBF16, kFP32, or kFP8 with bf16 queries).
@@ -229,9 +236,8 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  const int parts = scan_parts(KT, WDT) > 1 ? ga.f_parts : 1;   // wavefronts that share a head's candidates
-  const int part = wave & (parts - 1);
-  for (int h = wave / parts; h < G; h += 4 / parts) {
+  constexpr int parts = kScanParts<KT, WDT>;
+  auto attend = [&](int h, int part) {                     // share `part` of the keys of head h
     HeadVectors<FP32> hv;
     request_head_vectors<FP32>(ga, unit, head0 + h, hv);
     // the four wavefronts' keys of head h, one after the other: candidate cc is entry cc - s_w of
@@ -246,15 +252,27 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
     // this wavefront's share: candidates lo .. lo + mine - 1
     const int share = (all + parts - 1) / parts, lo = part * share;
     const int mine = parts == 1 ? all : (all - lo < share ? (all > lo ? all - lo : 0) : share);
-    gather_estimate_wave<ET, kIt>(ga, unit, head0 + h, mine, total - lo, hv,
-                                    [&](int cl) {
-                                      const int cc = cl + lo;
-                                      if (cc >= total) return static_key(ga, c, run + (int64_t)(cc - total) * nruns);
-                                      const int w = (cc >= s1) + (cc >= s2) + (cc >= s3);
-                                      const int first = w == 0 ? 0 : (w == 1 ? s1 : (w == 2 ? s2 : s3));
-                                      return blk0 * kBlockKeys + (int64_t)segh[w * kSeg + cc - first];
-                                    },
-                                    ga.partial + (((head0 + h) * ga.f_nranges + run) * parts + part) * kPartialStride);
+    return gather_estimate_wave<ET, kIt>(ga, unit, head0 + h, mine, total - lo, hv, [&](int cl) {
+      const int cc = cl + lo;
+      if (cc >= total) return static_key(ga, c, run + (int64_t)(cc - total) * nruns);
+      const int w = (cc >= s1) + (cc >= s2) + (cc >= s3);
+      const int first = w == 0 ? 0 : (w == 1 ? s1 : (w == 2 ? s2 : s3));
+      return blk0 * kBlockKeys + (int64_t)segh[w * kSeg + cc - first];
+    });
+  };
+  auto place = [&](int h) { return ga.partial + ((head0 + h) * ga.f_nranges + run) * kPartialStride; };
+  if constexpr (parts == 1) {
+    for (int h = wave; h < G; h += 4) store_partial(attend(h, 0), place(h));
+  } else {                                                 // one head
+    __shared__ float joined[kPartialStride];
+    WavePartial wp;
+    if (wave < parts) wp = attend(0, wave);
+    if (wave == 1) store_partial(wp, joined);
+    __syncthreads();
+    if (wave == 0) {
+      join_partial(wp, joined);
+      store_partial(wp, place(0));
+    }
   }
 #pragma unroll
   for (int l = 0; l < 2 * kLines; ++l) asm volatile("" ::"v"(touched[l]));
@@ -381,7 +399,7 @@ static void launch_scan_gather_as(const AttnArgs& a, dim3 grid, hipStream_t s, h
 
 template <int KT, int WDT, int LT>
 static void launch_scan_gather_for(const AttnArgs& a, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
-  constexpr int W = KT == 0 && scan_parts(KT, WDT) == 1 ? 8 : WDT;   // (debug outputs of any K and L: one form for all)
+  constexpr int W = KT == 0 && kScanParts<KT, WDT> == 1 ? 8 : WDT;   // (debug outputs of any K and L: one form for all)
   const bool dbg = a.dbg_counts || a.dbg_cand;
   if (a.is_fp32) {
     if (dbg) launch_scan_gather_as<KT, W, LT, kFP32, true>(a, grid, s, start, stop);
@@ -458,7 +476,7 @@ hipError_t launch_sampled_attention(const AttnArgs& a, const TableArgs* tables, 
     if ((e = launch_scan_gather(a, s, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr)) != hipSuccess) return e;
     if (ev && (e = hipEventRecord(ev[2], s)) != hipSuccess) return e;
     AttnArgs b = a;
-    b.nranges = a.f_nranges * a.f_parts;
+    b.nranges = a.f_nranges;
     if ((e = launch_merge(b, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr)) != hipSuccess) return e;
     return hipGetLastError();
   }
