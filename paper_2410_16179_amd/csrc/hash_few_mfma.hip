@@ -110,18 +110,22 @@ __global__ __launch_bounds__(256) void prep_centering_kernel(const float* mu_all
 }
 
 // LDS of a workgroup besides the static arrays: the vectors (two tiles of queries, or one tile of keys
-// and their 32 centering vectors), and per wavefront its two A tiles and the list of its projections
-// that are being re-evaluated.
+// and their 32 centering vectors), and per wavefront one or both of its A tiles and the list of its
+// projections that are being re-evaluated.
 constexpr int kFewList = 256;                              // entries per wavefront
-constexpr size_t kFewVectorBytes = 8 * 1024 + 32 * kHeadDim * sizeof(float), kFewTileBytes = 2 * 8 * 64 * sizeof(uint4);
-static size_t few_lds(int P) { return kFewVectorBytes + (size_t)P * (kFewTileBytes + kFewList * sizeof(uint16_t)); }
+constexpr int kTilePieces = 8 * 64;                        // 16-byte pieces of a tile (of the projector or of vectors)
+static size_t few_lds(const HashFewArgs& a, int held_tiles) {
+  return a.vector_bytes + (size_t)a.P * (held_tiles * kTilePieces * sizeof(uint4) + kFewList * sizeof(uint16_t));
+}
 
+// HELD: A tiles of a wavefront that LDS holds at once, 1 or 2.
+template <int HELD>
 __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
   extern __shared__ uint4 few_mem[];
   uint4* sB = few_mem;                                     // [vector tile][k-step][lane]
-  float (*sMu)[kHeadDim] = reinterpret_cast<float (*)[kHeadDim]>(few_mem + 8 * 64);   // (keys: there is no second tile)
-  uint4* sA = few_mem + kFewVectorBytes / 16 + (threadIdx.x >> 6) * (2 * 8 * 64);     // [tile][k-step][lane]
-  uint16_t* list = reinterpret_cast<uint16_t*>(few_mem + kFewVectorBytes / 16 + a.P * (2 * 8 * 64)) + (threadIdx.x >> 6) * kFewList;
+  float (*sMu)[kHeadDim] = reinterpret_cast<float (*)[kHeadDim]>(few_mem + kTilePieces);   // (keys: there is no second tile)
+  uint4* sA = few_mem + a.vector_bytes / 16 + (threadIdx.x >> 6) * (HELD * kTilePieces);   // [tile][k-step][lane]
+  uint16_t* list = reinterpret_cast<uint16_t*>(few_mem + a.vector_bytes / 16 + a.P * HELD * kTilePieces) + (threadIdx.x >> 6) * kFewList;
   __shared__ uint32_t sTail[16][32];                       // plane words of the last table group, [plane][key]
   __shared__ long long sLimbs[8][kLimbs];
   const int tid = threadIdx.x;
@@ -213,6 +217,15 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
     }
   }
   const float wmax = __uint_as_float(a.header[3]);
+  // the vectors to LDS, for the same: wavefront v writes the k-steps v, v + P, ...
+  uint32_t my_steps = 0;
+  for (int s = wave; s < 8; s += a.P) my_steps |= 1u << s;
+#pragma unroll
+  for (int s = 0; s < 8; ++s) {
+    if (!(my_steps >> s & 1)) continue;
+    sB[s * 64 + lane] = __builtin_bit_cast(uint4, B[0][s]);
+    if (two) sB[(8 + s) * 64 + lane] = __builtin_bit_cast(uint4, B[1][s]);
+  }
 
   // ---- error bound per vector: kGamma (|x| + |mu|) max|W_j| ----
   // (|x|^2 by v_dot2_f32_bf16, two exact products per instruction, float32 accumulation: the
@@ -286,26 +299,25 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
   fl[0] &= vmask;
   fl[1] &= two ? vmask : 0u;
   // ---- exact re-evaluation of the flagged projections, from LDS, four at a time ----
-  // The vectors go to LDS, a k-step or two per wavefront, and the A tiles of a wavefront that has
-  // flagged something; its flags become a list, and sixteen lanes take an entry, eight elements each.
+  // The vectors are in LDS, the A tiles of a wavefront that has flagged something go there; its flags become
+  // a list, and sixteen lanes take an entry, eight elements each.
   // (One at a time - the two lanes that hold the vector and the two that hold the column wrote them to
   // LDS, the wavefront formed two products per lane - an entry cost 0.7 us, and a group of 32 keys has up to
   // eight of them in a wavefront.)
-#pragma unroll
-  for (int s = 0; s < 8; ++s) {
-    if (s % a.P != wave) continue;
-    sB[s * 64 + lane] = __builtin_bit_cast(uint4, B[0][s]);
-    if (two) sB[(8 + s) * 64 + lane] = __builtin_bit_cast(uint4, B[1][s]);
-  }
   __syncthreads();
-  if (__ballot((fl[0] | fl[1]) != 0u)) {
+  // (tile 0 of the wavefront holds bits 31 .. 16 of a plane word, tile 1 the others)
+#pragma unroll 1
+  for (int tile0 = 0; tile0 < 2; tile0 += HELD) {
+    const uint32_t held = HELD == 2 ? ~0u : (tile0 == 0 ? 0xffff0000u : 0x0000ffffu);
+    if (!__ballot(((fl[0] | fl[1]) & held) != 0u)) continue;
 #pragma unroll
-    for (int tau = 0; tau < 2; ++tau)
-#pragma unroll
-      for (int s = 0; s < 8; ++s) sA[(tau * 8 + s) * 64 + lane] = __builtin_bit_cast(uint4, A[tau][s]);
+    for (int s = 0; s < 8; ++s) {
+      sA[s * 64 + lane] = __builtin_bit_cast(uint4, HELD == 2 || tile0 == 0 ? A[0][s] : A[1][s]);
+      if (HELD == 2) sA[kTilePieces + s * 64 + lane] = __builtin_bit_cast(uint4, A[1][s]);
+    }
     do {
       // entry: owner lane | vector tile << 6 | bit << 7 (| result << 15)
-      const int mine = __popc(fl[0]) + __popc(fl[1]);
+      const int mine = __popc(fl[0] & held) + __popc(fl[1] & held);
       const int incl = half_prefix_sum32(mine);
       const int low = __builtin_amdgcn_readlane(incl, 31), cnt_all = low + __builtin_amdgcn_readlane(incl, 63);
       const int pos0 = incl - mine + (hh ? low : 0);
@@ -313,7 +325,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
       int pos = pos0;
 #pragma unroll
       for (int bt = 0; bt < 2; ++bt)
-        for (uint32_t f = fl[bt]; f && pos < kFewList; f &= f - 1) list[pos++] = (uint16_t)(lane | bt << 6 | (__ffs(f) - 1) << 7);
+        for (uint32_t f = fl[bt] & held; f && pos < kFewList; f &= f - 1) list[pos++] = (uint16_t)(lane | bt << 6 | (__ffs(f) - 1) << 7);
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
       __builtin_amdgcn_wave_barrier();
       const int slot = lane >> 4, sl = lane & 15;
@@ -324,7 +336,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
         const int rho = 8 * (r >> 2) + 4 * hsrc + (r & 3);                    // tile row of the projection
         // elements 8 sl .. 8 sl + 7: k-step sl / 2, lane half sl % 2
         const int at16 = (sl >> 1) * 64 + (sl & 1) * 32;
-        const uint4 xr = sB[(e >> 6 & 1) * (8 * 64) + at16 + kap0], wr = sA[(el >> 4) * (8 * 64) + at16 + rho];
+        const uint4 xr = sB[(e >> 6 & 1) * kTilePieces + at16 + kap0], wr = sA[((el >> 4) - tile0) * kTilePieces + at16 + rho];
         const uint32_t xu[4] = {xr.x, xr.y, xr.z, xr.w}, wu[4] = {wr.x, wr.y, wr.z, wr.w};
         float mv[8];
         if (centered) {
@@ -352,8 +364,8 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
         for (uint64_t pending = __ballot(on && sl == 0 && g > 0.0 && fabs(t) <= kF64Slack * g); pending; pending &= pending - 1) {
           const int at = __ffsll((unsigned long long)pending) - 1;
           const int pe = __builtin_amdgcn_readlane(e, at), pel = 31 - (pe >> 7 & 31), pr = pel & 15;
-          const uint4* pw = sA + (pel >> 4) * (8 * 64) + 8 * (pr >> 2) + 4 * (pe >> 5 & 1) + (pr & 3);
-          const uint4* px = sB + (pe >> 6 & 1) * (8 * 64) + (pe & 31);
+          const uint4* pw = sA + ((pel >> 4) - tile0) * kTilePieces + 8 * (pr >> 2) + 4 * (pe >> 5 & 1) + (pr & 3);
+          const uint4* px = sB + (pe >> 6 & 1) * kTilePieces + (pe & 31);
           auto elem = [](const uint4* base, int d) {
             const uint16_t v = reinterpret_cast<const uint16_t*>(base + (d >> 4) * 64 + (d >> 3 & 1) * 32)[d & 7];
             return (double)__uint_as_float((uint32_t)v << 16);
@@ -371,7 +383,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
       pos = pos0;
 #pragma unroll
       for (int bt = 0; bt < 2; ++bt)
-        for (uint32_t f = fl[bt]; f && pos < kFewList; f &= f - 1) {
+        for (uint32_t f = fl[bt] & held; f && pos < kFewList; f &= f - 1) {
           const uint32_t m = f & -f;
           if (list[pos++] & 0x8000) neg[bt] &= ~m;
           else neg[bt] |= m;
@@ -379,7 +391,7 @@ __global__ __launch_bounds__(512) void hash_few_mfma_kernel(HashFewArgs a) {
         }
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
       __builtin_amdgcn_wave_barrier();
-    } while (__ballot((fl[0] | fl[1]) != 0u));
+    } while (__ballot(((fl[0] | fl[1]) & held) != 0u));
   }
 
   // ---- store ----
@@ -466,8 +478,18 @@ hipError_t launch_hash_few(const HashFewArgs& a0, hipStream_t s, hipEvent_t star
   const int k_groups = (a.n_krows + 31) / 32;
   if (a.q_groups + k_groups <= 0) return hipSuccess;
   const dim3 grid((unsigned)a.Wd, (unsigned)(a.q_groups + k_groups)), block(64 * a.P);
-  if (start || stop) hipExtLaunchKernelGGL(hash_few_mfma_kernel, grid, block, few_lds(a.P), s, start, stop, 0, a);
-  else hipLaunchKernelGGL(hash_few_mfma_kernel, grid, block, few_lds(a.P), s, a);
+  a.vector_bytes = (a.n_krows > 0 && a.mu ? 8 + 16 : 16) * 1024;
+  // Both A tiles at once, unless there are more workgroups than compute units and the room for one tile lets
+  // more of them share one: the registers allow eight wavefronts, that is 8 / P workgroups.  32768 queries,
+  // (8,75): 36.8 us with both tiles, 25.7 with one; with few workgroups the second pass over the flags costs more.
+  const bool one = (int64_t)grid.x * grid.y > kNumCU && (a.P == 1 || a.P == 2 || a.P == 4);
+  const size_t lds = few_lds(a, one ? 1 : 2);
+  auto go = [&](auto kernel) {
+    if (start || stop) hipExtLaunchKernelGGL(kernel, grid, block, lds, s, start, stop, 0, a);
+    else hipLaunchKernelGGL(kernel, grid, block, lds, s, a);
+  };
+  if (one) go(hash_few_mfma_kernel<1>);
+  else go(hash_few_mfma_kernel<2>);
   return hipGetLastError();
 }
 

@@ -183,6 +183,7 @@ struct HashFewArgs {
   int64_t stride_b, stride_h, stride_n;
   int K, L, Wd, P, NQ, NW;
   int q_groups;                                                 // grid rows that take queries (64 each); the rest take keys (32 each)
+  int vector_bytes;                                             // of the kernel's LDS, filled by launch_hash_few
 };
 
 constexpr int kMeanChunkRows = 256;   // rows a workgroup of the key mean sums

@@ -3,6 +3,7 @@ form of the hashing against the oracle, bit for bit."""
 import numpy as np
 import pytest
 
+from paper_2410_16179_amd import workloads as wl
 from tests.gpu_helpers import Session
 
 pytestmark = pytest.mark.gpu
@@ -128,3 +129,34 @@ def test_rows_that_are_not_finite_leave_the_others_alone(oracle, dtype):
         for first in range(0, 256, 64):
             code(first, 64)
         np.testing.assert_array_equal(s.key_table_codes()[0, 0][ok], want)
+
+
+@pytest.mark.parametrize("K,L,heads,group", [(2, 40, 5, 8), (4, 33, 16, 4), (8, 75, 32, 2), (10, 40, 8, 8), (1, 70, 3, 8),
+                                             (8, 416, 128, 8), (4, 416, 128, 8), (2, 512, 128, 8)])
+def test_many_flagged_projections_of_a_few_vectors(oracle, K, L, heads, group):
+    # keys that are their centering vector or next to it, queries whose large terms cancel: a wavefront lists more
+    # than the 256 entries it has room for at once; with 128 heads there are more workgroups than compute units
+    print(f"[case] flagged K={K} L={L} heads={heads} group={group}", flush=True)
+    rng = np.random.default_rng(K * L + heads)
+    W = rng.integers(-3, 4, (128, K * L)).astype(np.float32)
+    W[1] = W[0]
+    mu = rng.integers(-200, 201, (heads, 128)).astype(np.float32)
+    keys = mu.copy()
+    keys[1::4, 5] += 1
+    keys[2::4, 9] -= 1
+    keys[3::4] += rng.integers(-2, 3, keys[3::4].shape)
+    q = rng.integers(-2, 3, (heads * group, 128)).astype(np.float32)
+    hot = q[:: 12 if heads == 128 else 5]
+    hot[:] = 0
+    hot[:, :3] = 2.0 ** 60, -(2.0 ** 60), 1
+    Kc = wl.store(keys, "bf16")[None, :, None]
+    s = Session(K=K, L=L, dtype="bf16", Kc=Kc, Vc=Kc, q=q[None], W=W)
+    s.set_mu(mu[None])
+    s.prepare()
+    s.q_codes.fill_(0)
+    s.key_codes.fill_(0x5a5a5a5a)
+    s.hash_keys_prepared(0, 1, q_codes=s.q_codes)
+    np.testing.assert_array_equal(s.query_table_codes()[0], oracle.hash_query(q, W, K, L))
+    got = s.key_table_codes()[0, :, 0]
+    for h in range(heads):
+        np.testing.assert_array_equal(got[h], oracle.hash_keys(Kc[0, h], W, mu[h], K, L)[0])
