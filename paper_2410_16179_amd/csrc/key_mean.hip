@@ -17,7 +17,7 @@ __global__ __launch_bounds__(256) void key_mean_partial_kernel(MeanArgs a) {
   const int64_t r1 = r0 + kMeanChunkRows < a.n ? r0 + kMeanChunkRows : a.n;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   if (r1 - r0 == kMeanChunkRows) {
-    // a whole chunk: all of a thread's rows are requested before any is added
+    // a whole chunk: unrolled, so that as many of a thread's rows as 64 registers hold are on their way at once
     Frag f[kMeanChunkRows / 16];
 #pragma unroll
     for (int j = 0; j < kMeanChunkRows / 16; ++j) frag_load<ET, NT>(a.Kc, base + (r0 + rl + 16 * j) * a.stride_n + cg * 8, f[j]);
@@ -29,6 +29,7 @@ __global__ __launch_bounds__(256) void key_mean_partial_kernel(MeanArgs a) {
       for (int e = 0; e < 8; ++e) acc[e] += v[e];
     }
   } else {
+#pragma unroll 4
     for (int64_t i = r0 + rl; i < r1; i += 16) {
       float v[8];
       load8<ET>(a.Kc, base + i * a.stride_n + cg * 8, v);
@@ -46,27 +47,33 @@ __global__ __launch_bounds__(256) void key_mean_partial_kernel(MeanArgs a) {
   }
 }
 
-// Sums the chunk partials of 16 elements of one (batch, KV head) in a fixed order: 64 groups of 16
-// lanes take every 64th chunk (independent loads), the four groups of a wavefront are added by
-// rotations, LDS joins the wavefronts.  (One workgroup per unit, 48 chunks one after the other per
-// thread at 98304 keys, took 7.5 us; this 4.6.)
-constexpr int kMeanCols = 16;
+// Sums the chunk partials of COLS elements of one (batch, KV head) in a fixed order: 1024 / COLS groups of COLS
+// lanes take every (1024 / COLS)-th chunk (independent loads), the groups of a wavefront are added by
+// rotations, LDS joins the rest.  Many chunks need many groups (8 KV heads x 384 chunks, 48 one after the other
+// per thread with COLS = 128: 7.5 us; 16: 4.6); with few, one workgroup per unit is enough and eight are launches
+// of idle threads (the call, 512 units x 2 chunks: 16 19.4 us, 128 13.1).
+template <int COLS>
 __global__ __launch_bounds__(1024) void key_mean_final_kernel(MeanArgs a) {
-  __shared__ double red[16][kMeanCols];
+  constexpr int kGroups = 1024 / COLS, kRows = COLS < 64 ? 16 : kGroups;
+  __shared__ double red[kRows][COLS];
   const int unit = blockIdx.x;
-  const int d = threadIdx.x & (kMeanCols - 1), grp = threadIdx.x / kMeanCols;
-  const int col = blockIdx.y * kMeanCols + d;
+  const int d = threadIdx.x & (COLS - 1), grp = threadIdx.x / COLS;
+  const int col = blockIdx.y * COLS + d;
   double s = 0.0;
 #pragma unroll 4
-  for (int c = grp; c < a.nchunk; c += 64) s += a.partial[((int64_t)unit * a.nchunk + c) * kHeadDim + col];
-  s += __shfl_xor(s, 16);
-  s += __shfl_xor(s, 32);
-  if ((threadIdx.x & 63) < kMeanCols) red[threadIdx.x >> 6][d] = s;
+  for (int c = grp; c < a.nchunk; c += kGroups) s += a.partial[((int64_t)unit * a.nchunk + c) * kHeadDim + col];
+  if constexpr (COLS < 64) {
+#pragma unroll
+    for (int o = COLS; o < 64; o <<= 1) s += __shfl_xor(s, o);
+    if ((threadIdx.x & 63) < COLS) red[threadIdx.x >> 6][d] = s;
+  } else {
+    red[grp][d] = s;
+  }
   __syncthreads();
   if (grp == 0) {
     double t = 0.0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) t += red[r][d];
+    for (int r = 0; r < kRows; ++r) t += red[r][d];
     a.mu[(int64_t)unit * kHeadDim + col] = a.n > 0 ? (float)(t / (double)a.n) : 0.f;
   }
 }
@@ -87,7 +94,9 @@ hipError_t launch_key_mean(const MeanArgs& a, hipStream_t s) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(key_mean_final_kernel, dim3((unsigned)a.units, kHeadDim / kMeanCols), dim3(1024), 0, s, a);
+  // (32 chunks: four per thread, which the loop requests together)
+  if (a.nchunk <= 32) hipLaunchKernelGGL(key_mean_final_kernel<kHeadDim>, dim3((unsigned)a.units), dim3(1024), 0, s, a);
+  else hipLaunchKernelGGL(key_mean_final_kernel<16>, dim3((unsigned)a.units, kHeadDim / 16), dim3(1024), 0, s, a);
   return hipGetLastError();
 }
 
