@@ -371,7 +371,11 @@ static hipError_t launch_scan(const AttnArgs& a, hipStream_t s, hipEvent_t start
   MP_TUNED(10, 150) MP_TUNED(9, 120) MP_TUNED(10, 170) MP_TUNED(8, 75) MP_TUNED(10, 220) MP_TUNED(11, 300)
 #undef MP_TUNED
   const dim3 grid((unsigned)((nscanned + 3) / 4), (unsigned)(a.B * a.Hkv), layers);
-  launch_timed(collision_scan_kernel<0, 8, 0, 1>, grid, block, s, start, stop, a);
+  const int per = a.Hq / a.Hkv / (int)layers;            // heads of a wavefront
+  if (per == 1) launch_timed(collision_scan_kernel<0, 1, 0, 1>, grid, block, s, start, stop, a);
+  else if (per == 2) launch_timed(collision_scan_kernel<0, 2, 0, 1>, grid, block, s, start, stop, a);
+  else if (per <= 4) launch_timed(collision_scan_kernel<0, 4, 0, 1>, grid, block, s, start, stop, a);
+  else launch_timed(collision_scan_kernel<0, 8, 0, 1>, grid, block, s, start, stop, a);
   return hipGetLastError();
 }
 

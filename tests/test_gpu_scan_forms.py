@@ -8,7 +8,7 @@ import torch
 
 from paper_2410_16179_amd import binding as mp
 from paper_2410_16179_amd import workloads as wl
-from tests.gpu_helpers import TOL, rel_err
+from tests.gpu_helpers import TOL, Session, rel_err
 from tests.test_gpu_parity import run_case
 
 pytestmark = pytest.mark.gpu
@@ -80,3 +80,25 @@ def test_the_step_does_not_depend_on_the_scratch(oracle, b, hq, hkv, n, K, L, sh
         ref = oracle.decode_step(q[i, h].float().cpu().numpy()[None, None], Kh[None, None], Vh[None, None], W.float().cpu().numpy(),
                                  K, L, mu=mu[u].cpu().numpy()[None, None])
         assert rel_err(outs[0][i, h][None], ref["out"][0]) <= TOL
+
+
+@pytest.mark.parametrize("G,K,L,n", [(1, 9, 110, 2240), (2, 10, 300, 2177), (3, 8, 90, 2240), (5, 9, 100, 2200), (8, 11, 33, 2240)])
+def test_appended_keys_scanned_on_their_own(oracle, G, K, L, n):
+    # 33 or more key blocks behind the tables of 32 (batch, KV head) units: the scan alone, each layout of it
+    print(f"[case] appended scan G={G} K={K} L={L} n={n}", flush=True)
+    w = wl.Workload("appended", 8, 4 * G, 4, n, K, L, "bf16", (8,))
+    data = wl.generate(w)
+    s = Session(K=K, L=L, dtype="bf16", Kc=data["K"], Vc=data["V"], q=data["q"], W=data["W"])
+    s.set_mu(data["K"].mean(2))
+    s.hash_keys()
+    s.hash_query()
+    scan = s.attend()
+    s.build_tables(64)
+    res = s.attend(tables=True, with_counts=False)
+    np.testing.assert_array_equal(res["ncand"], scan["ncand"])
+    for b in range(8):
+        for h in range(4 * G):
+            np.testing.assert_array_equal(res["S"][b][h], scan["S"][b][h])
+    assert rel_err(res["out"], scan["out"]) <= 1e-5
+    ref = oracle.decode_step(data["q"], data["K"], data["V"], data["W"], K, L, mu=data["K"].mean(2), heads=[(7, 4 * G - 1)])
+    np.testing.assert_array_equal(res["S"][7][4 * G - 1], ref["S"][7][4 * G - 1])
