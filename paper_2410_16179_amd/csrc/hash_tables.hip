@@ -555,11 +555,16 @@ __global__ __launch_bounds__(1024) void table_lookup_kernel(AttnArgs a, TableArg
 // head marks every key it meets in a "seen" bitmap of the whole indexed range and, when it was
 // already marked, in a "seen twice" bitmap (both in LDS, a bit per key); the ballots are those
 // bitmaps.  No bucket is read more than once per head, whatever the context length.
-// Bound by latency: two workgroups per compute unit (64 registers) so that 512 heads are one round, and
-// the entries of four buckets requested at once, up to 192 of each: at 131072 keys and K = 10 a bucket
-// holds 128 on average, and every second one made a wavefront wait for the rest of it when the first
-// request took 128.  (All buckets of a wavefront at once, 128 entries each, held 96 registers: one
-// workgroup per compute unit, 40 us at 512 heads x 131072 keys, (10,170).)
+// Bound by latency and instruction count: two workgroups per compute unit (64 registers) so that 512 heads are
+// one round; the entries of kChunk buckets requested at once, up to 64 kEntries of each (at 131072 keys and
+// K = 10 a bucket holds 128 on average, and every second one made a wavefront wait for the rest of it when the
+// first request took 128); what a wavefront knows of its buckets sits in its lanes, and the slots of a chunk
+// that have no bucket are left by a branch (masked off instead, 11 buckets in slots of 16 took 9.8 us, with the
+// branch 7.2 in slots of 8).  Kernel, us: all buckets of a wavefront at once, 128 entries each, 96 registers |
+// four at a time, 192 entries, descriptors in LDS | this: 256 heads x 4096 keys, (10,170) 8.7 | 11.0 | 7.2;
+// 256 x 60000, (10,170) 10.2 | 11.2 | 10.1; 256 x 20000, (10,512) 16.1 | 23.4 | 14.2; 512 x 100000, (10,150)
+// 24.8 | 18.0 | 16.4.
+template <int kChunk, int kEntries>
 __global__ __launch_bounds__(1024, 8) void table_lookup_bitmap_kernel(AttnArgs a, TableArgs tb) {
   extern __shared__ uint32_t bitmap[];                  // seen[nw], twice[nw]
   __shared__ uint32_t bstart[512], blen[512];
@@ -588,44 +593,51 @@ __global__ __launch_bounds__(1024, 8) void table_lookup_bitmap_kernel(AttnArgs a
     blen[t] = s1 - s0;
   }
   __syncthreads();
-  // wavefront v reads tables v, v+16, ..., four at a time: up to 192 entries of each bucket are
-  // requested before any is used, and the first atomics (was the key seen before?) are issued
+  // wavefront v reads tables v, v+16, ..., kChunk at a time: up to 64 kEntries entries of each bucket
+  // are requested before any is used, and the first atomics (was the key seen before?) are issued
   // together; longer buckets are finished in a loop
-  constexpr int kChunk = 4, kEntries = 3;
-  const int nbk = (a.L - wave + 15) >> 4;
+  const int nbk = (a.L - wave + 15) >> 4;                // at most 32: lane k holds what is known of bucket k
+  const uint32_t my_start = lane < nbk ? bstart[wave + 16 * lane] : 0u, my_len = lane < nbk ? blen[wave + 16 * lane] : 0u;
   for (int k0 = 0; k0 < nbk; k0 += kChunk) {
-    uint32_t e[kChunk * kEntries], before[kChunk * kEntries];
+    uint32_t e[kChunk][kEntries], before[kChunk][kEntries];
+    const int here = nbk - k0;                           // (wave-uniform)
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
-      const int t = wave + 16 * (k0 + k);
-      const bool on = k0 + k < nbk;
-      const uint32_t len = on ? __builtin_amdgcn_readfirstlane(blen[t]) : 0u;
-      const uint32_t* p = idxs + (int64_t)(on ? t : 0) * tb.n_cap + (on ? __builtin_amdgcn_readfirstlane(bstart[t]) : 0u);
 #pragma unroll
-      for (int j = 0; j < kEntries; ++j) {
-        e[k * kEntries + j] = 0xffffffffu;
-        if ((uint32_t)(lane + 64 * j) < len) e[k * kEntries + j] = p[lane + 64 * j];
-      }
+      for (int j = 0; j < kEntries; ++j) { e[k][j] = 0xffffffffu; before[k][j] = 0u; }
     }
-#pragma unroll
-    for (int i = 0; i < kChunk * kEntries; ++i) {
-      before[i] = 0u;
-      if (e[i] != 0xffffffffu) before[i] = atomicOr(&seen[e[i] >> 5], 1u << (e[i] & 31));
-    }
-#pragma unroll
-    for (int i = 0; i < kChunk * kEntries; ++i)
-      if (before[i] >> (e[i] & 31) & 1u) atomicOr(&twice[e[i] >> 5], 1u << (e[i] & 31));
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
-      const int t = wave + 16 * (k0 + k);
-      if (k0 + k >= nbk) break;
-      const uint32_t len = __builtin_amdgcn_readfirstlane(blen[t]);
-      if (len <= 64 * kEntries) continue;
-      const uint32_t* p = idxs + (int64_t)t * tb.n_cap + __builtin_amdgcn_readfirstlane(bstart[t]);
-      for (uint32_t j = 64 * kEntries + lane; j < len; j += 64) {
-        const uint32_t key = p[j], bit = 1u << (key & 31);
-        if (atomicOr(&seen[key >> 5], bit) & bit) atomicOr(&twice[key >> 5], bit);
-      }
+      if (k >= here) break;
+      const uint32_t len = __builtin_amdgcn_readlane(my_len, k0 + k);
+      const uint32_t* p = idxs + (int64_t)(wave + 16 * (k0 + k)) * tb.n_cap + __builtin_amdgcn_readlane(my_start, k0 + k);
+#pragma unroll
+      for (int j = 0; j < kEntries; ++j)
+        if ((uint32_t)(lane + 64 * j) < len) e[k][j] = p[lane + 64 * j];
+    }
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) {
+      if (k >= here) break;
+#pragma unroll
+      for (int j = 0; j < kEntries; ++j)
+        if (e[k][j] != 0xffffffffu) before[k][j] = atomicOr(&seen[e[k][j] >> 5], 1u << (e[k][j] & 31));
+    }
+#pragma unroll
+    for (int k = 0; k < kChunk; ++k) {
+      if (k >= here) break;
+#pragma unroll
+      for (int j = 0; j < kEntries; ++j)
+        if (before[k][j] >> (e[k][j] & 31) & 1u) atomicOr(&twice[e[k][j] >> 5], 1u << (e[k][j] & 31));
+    }
+  }
+  // (what is longer than the first request)
+  for (uint64_t f = __ballot(my_len > 64 * kEntries); f; f &= f - 1) {
+    const int k = __ffsll((unsigned long long)f) - 1;
+    const uint32_t len = __builtin_amdgcn_readlane(my_len, k);
+    const uint32_t* p = idxs + (int64_t)(wave + 16 * k) * tb.n_cap + __builtin_amdgcn_readlane(my_start, k);
+    for (uint32_t j = 64 * kEntries + lane; j < len; j += 64) {
+      const uint32_t key = p[j], bit = 1u << (key & 31);
+      if (atomicOr(&seen[key >> 5], bit) & bit) atomicOr(&twice[key >> 5], bit);
     }
   }
   __syncthreads();
@@ -922,8 +934,16 @@ hipError_t launch_table_lookup(const AttnArgs& a, const TableArgs& t, hipStream_
   const size_t bitmap_bytes = (size_t)nblk * 2 * 2 * sizeof(uint32_t);
   if (!a.dbg_counts && (a.tau == 1 || a.tau == 2) && bitmap_bytes <= 48 * 1024) {
     const dim3 grid((unsigned)((int64_t)a.B * a.Hq));
-    if (start || stop) hipExtLaunchKernelGGL(table_lookup_bitmap_kernel, grid, dim3(1024), bitmap_bytes, s, start, stop, 0, a, t);
-    else hipLaunchKernelGGL(table_lookup_bitmap_kernel, grid, dim3(1024), bitmap_bytes, s, a, t);
+    auto go = [&](auto kernel) {
+      if (start || stop) hipExtLaunchKernelGGL(kernel, grid, dim3(1024), bitmap_bytes, s, start, stop, 0, a, t);
+      else hipLaunchKernelGGL(kernel, grid, dim3(1024), bitmap_bytes, s, a, t);
+    };
+    // by the average bucket, so that few are longer than the first request (256 heads x 20000 keys, (10,300): 20 on
+    // average, <8, 1> 10.0 us, <8, 2> 12.2)
+    const int64_t average = t.n >> a.K;
+    if (average <= 40) go(table_lookup_bitmap_kernel<8, 1>);
+    else if (average <= 96) go(table_lookup_bitmap_kernel<8, 2>);
+    else go(table_lookup_bitmap_kernel<4, 3>);
     return hipGetLastError();
   }
   auto go = [&](auto kernel, int run_blocks) {
