@@ -36,13 +36,13 @@ __device__ inline void load_x8(const HashDirectArgs& a, int64_t idx, float (&v)[
   load8<FP32>(a.X, idx, v);
 }
 
-// One wavefront codes two vectors at a time: lanes 0..31 take tables 32w..32w+31 of the
+// One wavefront codes two keys at a time: lanes 0..31 take tables 32w..32w+31 of the
 // first, lanes 32..63 of the second; a ballot turns the 64 sign tests into two code words.
 __device__ inline void hash_direct(const HashDirectArgs& a, long long (*limbs)[kLimbs]) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
   const int half = lane >> 5, beta = lane & 31;
-  // workgroups walk the groups of eight vectors
+  // workgroups walk the groups of eight keys
   for (int64_t grp = blockIdx.x; grp * 8 < a.total_rows; grp += gridDim.x) {
   const int64_t row0 = (grp * 4 + wave) * 2;
   if (row0 >= a.total_rows) continue;
@@ -55,9 +55,8 @@ __device__ inline void hash_direct(const HashDirectArgs& a, long long (*limbs)[k
                         key * a.stride_n;
   const float* mu = a.mu ? a.mu + unit * kHeadDim : nullptr;
   const int ncol = a.K * a.L;
-  const int Wd = table_words(a.L);
 
-  // plane word x of this lane half's vector (tables 32w .. 32w+31, bit b)
+  // plane word x of this lane half's key (tables 32w .. 32w+31, bit b)
   auto plane = [&](int x) -> uint32_t {
     const int w = x / a.K, b = x % a.K;
     const int t = 32 * w + beta;
@@ -114,41 +113,29 @@ __device__ inline void hash_direct(const HashDirectArgs& a, long long (*limbs)[k
       pending &= pending - 1;
     }
     const uint64_t m = __ballot(bit && col_ok);
-    uint32_t word = half ? (uint32_t)(m >> 32) : (uint32_t)m;
-    if (a.query_layout && (w == Wd - 1) && (a.L & 31)) word |= ~0u << (a.L & 31);
-    return word;
+    return half ? (uint32_t)(m >> 32) : (uint32_t)m;
   };
   uint32_t* kdst = a.codes + (unit * a.blocks_cap + key / kBlockKeys) * (kBlockKeys * (int64_t)a.NW);
   auto store_key_word = [&](int x, uint32_t word) {
     if (beta == 0 && row_ok) kdst[slot_in_block(a.NW, x, (int)(key % kBlockKeys))] = word;
   };
-  // the items of a vector: its plane words, and for keys the densely packed last table group as one
-  const int xs = a.query_layout ? a.NQ : tail_begin(a.K, a.L);
-  const int nitems = a.query_layout ? a.NQ : xs + 1;
-  for (int it = 0; it < nitems; ++it) {
-    if (it < xs) {
-      const uint32_t word = plane(it);
-      if (a.query_layout) {
-        if (beta == 0 && row_ok) a.codes[row * a.NQ + it] = word;
-      } else {
-        store_key_word(it, word);
-      }
-    } else {                                             // keys: the K planes of the last group, packed
-      BitString bs;
-      int xo = xs;
-      for (int b = 0; b < a.K; ++b) {
-        uint32_t full;
-        if (bs.append(plane(xs + b), tail_tables(a.L), &full)) store_key_word(xo++, full);
-      }
-      if (bs.nbits > 0) store_key_word(xo, (uint32_t)bs.acc);
-    }
+  // the plane words below the last table group, and that group as one bit string
+  const int xs = tail_begin(a.K, a.L);
+  BitString bs;
+  int xo = xs;
+  for (int x = 0; x < a.NQ; ++x) {
+    const uint32_t word = plane(x);
+    uint32_t full;
+    if (x < xs) store_key_word(x, word);
+    else if (bs.append(word, tail_tables(a.L), &full)) store_key_word(xo++, full);
   }
+  if (bs.nbits > 0) store_key_word(xo, (uint32_t)bs.acc);
   }
 }
 
 // Behind the matrix-core key hashing: re-evaluates the pairs that did not fit a workgroup's own list
 // (normally none), or, if the global list overflowed too, codes every key of the call in float64.  As a
-// rule it reads two words and ends: one launch of few workgroups.
+// rule its workgroups read two words and end (4.8 us: 1024 of them, one per compute unit at a time).
 __global__ __launch_bounds__(256) void finish_hash_keys_kernel(HashMfmaArgs m, HashDirectArgs a) {
   __shared__ long long limbs[4][kLimbs];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;

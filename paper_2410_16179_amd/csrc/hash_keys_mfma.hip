@@ -49,11 +49,11 @@ __host__ __device__ inline void tile_row_to_bit(int T, int rho, int* x, int* bet
 // The first `proj_blocks` workgroups (16 tile rows each): A-operand fragments, transposed bf16 copy
 // of W for the recheck, largest column norm of the 16 rows.  One thread per (tile row, 8-element piece
 // of d).  The first also clears the counters the later kernels of the call add to.
-// The others, 256 projector columns of one (batch, KV head) each: initial accumulators -fl(mu.W_j) in
+// The next, 256 projector columns of one (batch, KV head) each: initial accumulators -fl(mu.W_j) in
 // fragment order and the same sums in float64.  A thread takes a column, neighbouring threads
 // neighbouring columns, so that W is read in whole lines as it is stored.  (As two launches, the second
 // reading the transposed copy row by row, they took 4.8 + 9.4 us.)
-// The first of a (batch, KV head) also writes |mu|.
+// With a centering vector `units` more, one |mu| each.
 __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int proj_blocks, int thr_blocks) {
   __shared__ float smax[4];
   const int tid = threadIdx.x;
@@ -95,14 +95,18 @@ __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int
     return;
   }
   const int at = (int)blockIdx.x - proj_blocks;
+  if (at >= thr_blocks * a.units) {
+    if (tid < 64) {
+      const float* mu = a.mu + (int64_t)(at - thr_blocks * a.units) * kHeadDim;
+      double ss = (double)mu[tid] * (double)mu[tid] + (double)mu[tid + 64] * (double)mu[tid + 64];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
+      if (tid == 0) a.munorm[at - thr_blocks * a.units] = (float)sqrt(ss) * 1.000001f;
+    }
+    return;
+  }
   const int unit = at / thr_blocks;
   const float* mu = a.mu ? a.mu + (int64_t)unit * kHeadDim : nullptr;
-  if (mu && at % thr_blocks == 0 && tid < 64) {
-    double ss = (double)mu[tid] * (double)mu[tid] + (double)mu[tid + 64] * (double)mu[tid + 64];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-    if (tid == 0) a.munorm[unit] = (float)sqrt(ss) * 1.000001f;
-  }
   // column i of the whole table groups (32 K columns each), then the words that pad the last quad
   const int i = at % thr_blocks * 256 + tid;
   if (i >= a.ntiles * 32) return;
@@ -361,6 +365,8 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
       if (__ballot(nfl != 0)) {
         unsigned pos = 0;
         if (nfl) pos = atomicAdd(&sCount, (unsigned)nfl);  // one reservation per lane and quad
+        int64_t gpos = -1;
+        const unsigned end = pos + (unsigned)nfl;
 #pragma unroll
         for (int pair = 0; pair < 2; ++pair) {
           const unsigned xw = (unsigned)(2 * (q * 2 + pair) + hh) << 5;   // code word of this lane half
@@ -375,9 +381,12 @@ __global__ __launch_bounds__(256, 3) void hash_keys_mfma_kernel(HashMfmaArgs a) 
               if (pos < kListCapLocal) {
                 sList[pos] = ent;
               } else {                                   // rare: the workgroup's list is full
-                const unsigned gpos = atomicAdd(a.list_count, 1u);
-                if (gpos < a.list_cap) a.list[gpos] = ent;
-                else *a.overflow = 1;
+                if (gpos < 0) {                          // (one reservation here too: entry by entry all lanes queue for the counter)
+                  gpos = atomicAdd(a.list_count, end - pos);
+                  if ((uint64_t)gpos + (end - pos) > a.list_cap) *a.overflow = 1;
+                }
+                if ((uint64_t)gpos < a.list_cap) a.list[gpos] = ent;
+                ++gpos;
               }
               ++pos;
             }
@@ -430,8 +439,8 @@ static int split_sweep(int64_t groups, int nquads, int tail_quad, int* begin) {
 
 hipError_t launch_hash_keys_mfma(const HashMfmaArgs& a, hipStream_t s) {
   const int proj_blocks = a.ntiles * 2, thr_blocks = (a.ntiles * 32 + 255) / 256;   // 16 tile rows, 256 columns each
-  hipLaunchKernelGGL(prep_hash_keys_kernel, dim3((unsigned)(proj_blocks + (int64_t)thr_blocks * a.units)), dim3(256), 0, s, a,
-                     proj_blocks, thr_blocks);
+  const int64_t prep_blocks = proj_blocks + (int64_t)thr_blocks * a.units + (a.mu ? a.units : 0);
+  hipLaunchKernelGGL(prep_hash_keys_kernel, dim3((unsigned)prep_blocks), dim3(256), 0, s, a, proj_blocks, thr_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int64_t first_blk = a.first_key / kBlockKeys;
@@ -441,7 +450,6 @@ hipError_t launch_hash_keys_mfma(const HashMfmaArgs& a, hipStream_t s) {
   HashMfmaArgs b = a;
   const int parts = split_sweep(groups, a.ntiles / 4, tail_begin(a.K, a.L) / 4, b.part_begin);
   hipLaunchKernelGGL(hash_keys_mfma_kernel, dim3((unsigned)((nblk + 3) / 4), (unsigned)a.units, (unsigned)parts), dim3(256), 0, s, b);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   return hipGetLastError();
 }
 
