@@ -65,16 +65,17 @@ __global__ __launch_bounds__(256) void ht_build_kernel(TableArgs a) {
   for (int64_t blk = wave; blk < nblk; blk += 4) {
     const int64_t key = blk * kBlockKeys + lane;
     const uint32_t* blkp = ucodes + blk * (kBlockKeys * (int64_t)a.NW);
-    uint32_t kw[16];
+    uint32_t kw[12];                                    // (tables take K <= 12)
 #pragma unroll
-    for (int b = 0; b < 16; ++b) kw[b] = b < a.K ? load_plane_word(blkp, a.NW, a.K, a.L, w * a.K + b, lane) : 0u;
+    for (int b = 0; b < 12; ++b) kw[b] = b < a.K ? load_plane_word(blkp, a.NW, a.K, a.L, w * a.K + b, lane) : 0u;
     if (key < a.n) {
-      for (int bb = 0; bb < tpp; ++bb) {
+      const int here = a.L - 32 * w - beta0 < tpp ? a.L - 32 * w - beta0 : tpp;
+#pragma unroll 4
+      for (int bb = 0; bb < here; ++bb) {
         const int beta = beta0 + bb;
-        if (32 * w + beta >= a.L) break;
         uint32_t code = 0;
 #pragma unroll
-        for (int b = 0; b < 16; ++b) code |= ((kw[b] >> beta) & 1u) << b;
+        for (int b = 0; b < 12; ++b) code |= ((kw[b] >> beta) & 1u) << b;
         const uint32_t pos = atomicAdd(&hist[bb * nb + code], 1u);
         if (SCATTER) idxs[(int64_t)(32 * w + beta) * a.n_cap + pos] = (uint32_t)key;
       }
