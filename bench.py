@@ -333,7 +333,7 @@ def main():
         for s_ in sets:
             s_["tables"] = mp.alloc_tables(params)
         b0, b1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        bws = mp.alloc_table_build_workspace(params)          # room for the two-pass build
+        bws = mp.alloc_table_build_workspace(params)          # room for the build that orders buckets by window
         mp.magicpig_build_tables(params, sets[0]["codes"], sets[0]["tables"], bws)     # warm-up
         torch.cuda.synchronize()
         b0.record()

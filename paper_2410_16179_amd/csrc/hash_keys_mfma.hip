@@ -53,7 +53,7 @@ __host__ __device__ inline void tile_row_to_bit(int T, int rho, int* x, int* bet
 // fragment order and the same sums in float64.  A thread takes a column, neighbouring threads
 // neighbouring columns, so that W is read in whole lines as it is stored.  (As two launches, the second
 // reading the transposed copy row by row, they took 4.8 + 9.4 us.)
-// With a centering vector `units` more, one |mu| each.
+// With a centering vector units / 4 more, |mu| of four each.
 __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int proj_blocks, int thr_blocks) {
   __shared__ float smax[4];
   const int tid = threadIdx.x;
@@ -96,12 +96,11 @@ __global__ __launch_bounds__(256) void prep_hash_keys_kernel(HashMfmaArgs a, int
   }
   const int at = (int)blockIdx.x - proj_blocks;
   if (at >= thr_blocks * a.units) {
-    if (tid < 64) {
-      const float* mu = a.mu + (int64_t)(at - thr_blocks * a.units) * kHeadDim;
-      double ss = (double)mu[tid] * (double)mu[tid] + (double)mu[tid + 64] * (double)mu[tid + 64];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o);
-      if (tid == 0) a.munorm[at - thr_blocks * a.units] = (float)sqrt(ss) * 1.000001f;
+    const int unit = (at - thr_blocks * a.units) * 4 + (tid >> 6), lane = tid & 63;
+    if (unit < a.units) {
+      const float* mu = a.mu + (int64_t)unit * kHeadDim;
+      const float ss = wave_sum(fmaf(mu[lane], mu[lane], mu[lane + 64] * mu[lane + 64])) + kSquareSlack;
+      if (lane == 0) a.munorm[unit] = sqrtf(ss) * 1.00002f;   // (infinite beyond 1.8e19: everything is then listed)
     }
     return;
   }
@@ -146,7 +145,7 @@ __device__ inline void stage_pair(const uint4* gpair, uint4* stage, int tid, int
         (__attribute__((address_space(3))) void*)(stage + i * 256 + wave * 64), 16, 0, 0);
 }
 
-// Three workgroups per compute unit: 152 registers, 46 KB of LDS (two 16 KB stages, the list).
+// Three workgroups per compute unit: 166 registers, 46 KB of LDS (two 16 KB stages, the list).
 // With stages of four tiles (80 KB, two workgroups per compute unit) the kernel was 10 % slower:
 // a workgroup goes through its phases (load and norm the keys, sweep, queue, re-evaluate) one
 // after the other, and a third resident workgroup fills more of the gaps.
@@ -439,7 +438,7 @@ static int split_sweep(int64_t groups, int nquads, int tail_quad, int* begin) {
 
 hipError_t launch_hash_keys_mfma(const HashMfmaArgs& a, hipStream_t s) {
   const int proj_blocks = a.ntiles * 2, thr_blocks = (a.ntiles * 32 + 255) / 256;   // 16 tile rows, 256 columns each
-  const int64_t prep_blocks = proj_blocks + (int64_t)thr_blocks * a.units + (a.mu ? a.units : 0);
+  const int64_t prep_blocks = proj_blocks + (int64_t)thr_blocks * a.units + (a.mu ? (a.units + 3) / 4 : 0);
   hipLaunchKernelGGL(prep_hash_keys_kernel, dim3((unsigned)prep_blocks), dim3(256), 0, s, a, proj_blocks, thr_blocks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

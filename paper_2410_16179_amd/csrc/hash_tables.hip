@@ -918,14 +918,9 @@ hipError_t launch_lookup_gather(const AttnArgs& a0, const TableArgs& t, int nsli
   a.lg_nslices = nslices;
   a.lg_app_runs = appended_runs;                       // <= nslices
   const dim3 grid((unsigned)nslices, (unsigned)((int64_t)a.B * a.Hq));
-  // the scan of the appended keys has the same tuned forms as collision_scan_kernel
-  if (a.K == 10 && a.L == 150) launch_lookup_gather_for<10, 5, 22>(a, t, grid, s, start, stop);
-  else if (a.K == 9 && a.L == 120) launch_lookup_gather_for<9, 4, 24>(a, t, grid, s, start, stop);
-  else if (a.K == 10 && a.L == 170) launch_lookup_gather_for<10, 6, 10>(a, t, grid, s, start, stop);
-  else if (a.K == 8 && a.L == 75) launch_lookup_gather_for<8, 3, 11>(a, t, grid, s, start, stop);
-  else if (a.K == 10 && a.L == 220) launch_lookup_gather_for<10, 7, 28>(a, t, grid, s, start, stop);
-  else if (a.K == 11 && a.L == 300) launch_lookup_gather_for<11, 10, 12>(a, t, grid, s, start, stop);
-  else launch_lookup_gather_for<0, 0, 0>(a, t, grid, s, start, stop);
+#define MP_TUNED(KT, LL) if (a.K == KT && a.L == LL) launch_lookup_gather_for<KT, words_of(LL), tail_of(LL)>(a, t, grid, s, start, stop); else
+  MP_TUNED_TABLES(MP_TUNED) launch_lookup_gather_for<0, 0, 0>(a, t, grid, s, start, stop);
+#undef MP_TUNED
   return hipGetLastError();
 }
 

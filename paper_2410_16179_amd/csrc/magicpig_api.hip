@@ -102,7 +102,7 @@ HashWs ws_hash_layout(const magicpig_params* p) {
   w.magmu_off = w.thr64_off + align256(units * (size_t)p->K * p->L * sizeof(double));
   w.munorm_off = w.magmu_off + align256(units * (size_t)p->K * p->L * sizeof(float));
   w.rownorm_off = w.munorm_off + align256(units * sizeof(float));
-  w.scalar_off = w.rownorm_off + align256((size_t)w.ntiles * 32 * sizeof(float));
+  w.scalar_off = w.rownorm_off + align256((size_t)w.ntiles * 2 * sizeof(float));
   w.list_off = w.scalar_off + 256;
   // room for one flagged element in 512 (a few in ten thousand are expected), at least 64K
   const uint64_t elems = (uint64_t)units * (uint64_t)p->n_cap * (uint64_t)(p->K * p->L);

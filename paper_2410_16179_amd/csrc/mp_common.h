@@ -239,7 +239,7 @@ struct TableArgs {
   int64_t n, n_cap, blocks_cap;   // n: keys [0, n) are in the tables
   // build with a large workspace: per-table codes of every key and, for every window of
   // kBuildWindow keys, the number of keys of each bucket in the windows before it
-  uint16_t* codes16;           // [units][L][n_cap] (workspace), or null (keys scattered without it)
+  uint16_t* codes16;           // [units][L][64 blocks_cap] (workspace), or null (keys scattered without it)
   uint32_t* wincum;            // [units][L][windows][2^K], part of the tables: with it the piece of a
                                // bucket that holds the keys of one window can be read alone
   int windows;
@@ -257,6 +257,11 @@ constexpr int kFusedWaveBlocks = 6;           // most key blocks a wavefront sca
 constexpr int kFusedBlocks = 4 * kFusedWaveBlocks;        // most key blocks per workgroup
 constexpr int kFusedFill = 768;               // workgroups of it that are resident at once (3 per compute unit)
 constexpr int kFusedIters = 8;             // its gather batch: rows per quarter wavefront
+
+// Table sets (K, L) that the scans are compiled for; any other goes through their form for any.
+#define MP_TUNED_TABLES(X) X(10, 150) X(9, 120) X(10, 170) X(8, 75) X(10, 220) X(11, 300)
+constexpr int words_of(int L) { return (L + 31) / 32; }
+constexpr int tail_of(int L) { return L - 32 * (words_of(L) - 1); }
 
 // host-side launchers (defined next to their kernels)
 hipError_t launch_finish_hash_keys(const HashMfmaArgs& m, const HashDirectArgs& a, hipStream_t s);

@@ -33,7 +33,7 @@ __device__ inline void recheck_pairs(const HashMfmaArgs& a, long long* limb, uin
     const int64_t xoff = (int64_t)ub * a.stride_b + (int64_t)uh * a.stride_h + k * a.stride_n;
     // Products of two bf16 values are exact in float32; they are added in float64 (at most 128
     // roundings of 2^-53 of the magnitude sum) and the centering term mu.W_j comes ready-made in
-    // float64 from the threshold kernel, with the same kind of error on its own magnitude sum:
+    // float64 from the preparing launch, with the same kind of error on its own magnitude sum:
     // |s - exact| < 2^-45 (sum|k w| + sum|mu w|).  The magnitude sums are float32 upper bounds.
     uint4 kraw[kPieces], wraw[kPieces];
 #pragma unroll

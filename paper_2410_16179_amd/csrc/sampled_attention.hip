@@ -364,11 +364,10 @@ static hipError_t launch_scan(const AttnArgs& a, hipStream_t s, hipEvent_t start
   const dim3 grid_t((unsigned)((nscanned + 4 * kBPW - 1) / (4 * kBPW)), (unsigned)(a.B * a.Hkv), layers);
 #define MP_TUNED(KT, LL)                                                                            \
   if (a.K == KT && a.L == LL) {                                                                     \
-    launch_timed(collision_scan_kernel<KT, (LL + 31) / 32, LL - 32 * ((LL + 31) / 32 - 1), kBPW>,  \
-                 grid_t, block, s, start, stop, a);                                                 \
+    launch_timed(collision_scan_kernel<KT, words_of(LL), tail_of(LL), kBPW>, grid_t, block, s, start, stop, a);  \
     return hipGetLastError();                                                                       \
   }
-  MP_TUNED(10, 150) MP_TUNED(9, 120) MP_TUNED(10, 170) MP_TUNED(8, 75) MP_TUNED(10, 220) MP_TUNED(11, 300)
+  MP_TUNED_TABLES(MP_TUNED)
 #undef MP_TUNED
   const dim3 grid((unsigned)((nscanned + 3) / 4), (unsigned)(a.B * a.Hkv), layers);
   const int per = a.Hq / a.Hkv / (int)layers;            // heads of a wavefront
@@ -419,19 +418,15 @@ static void launch_scan_gather_for(const AttnArgs& a, dim3 grid, hipStream_t s, 
 
 static hipError_t launch_scan_gather(const AttnArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 grid((unsigned)a.f_nranges, (unsigned)(a.B * a.Hkv));
-  if (a.K == 10 && a.L == 150) launch_scan_gather_for<10, 5, 22>(a, grid, s, start, stop);
-  else if (a.K == 9 && a.L == 120) launch_scan_gather_for<9, 4, 24>(a, grid, s, start, stop);
-  else if (a.K == 10 && a.L == 170) launch_scan_gather_for<10, 6, 10>(a, grid, s, start, stop);
-  else if (a.K == 8 && a.L == 75) launch_scan_gather_for<8, 3, 11>(a, grid, s, start, stop);
-  else if (a.K == 10 && a.L == 220) launch_scan_gather_for<10, 7, 28>(a, grid, s, start, stop);   // App. E (K, L) study
-  else if (a.K == 11 && a.L == 300) launch_scan_gather_for<11, 10, 12>(a, grid, s, start, stop);
-  else {                                                   // any other: by the heads that share a KV head
+#define MP_TUNED(KT, LL) if (a.K == KT && a.L == LL) launch_scan_gather_for<KT, words_of(LL), tail_of(LL)>(a, grid, s, start, stop); else
+  MP_TUNED_TABLES(MP_TUNED) {                              // any other: by the heads that share a KV head
     const int G = a.Hq / a.Hkv;
     if (G == 1) launch_scan_gather_for<0, 1, 0>(a, grid, s, start, stop);
     else if (G == 2) launch_scan_gather_for<0, 2, 0>(a, grid, s, start, stop);
     else if (G <= 4) launch_scan_gather_for<0, 4, 0>(a, grid, s, start, stop);
     else launch_scan_gather_for<0, 8, 0>(a, grid, s, start, stop);
   }
+#undef MP_TUNED
   return hipGetLastError();
 }
 

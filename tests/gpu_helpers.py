@@ -144,7 +144,7 @@ class Session:
 
     def build_tables(self, n_indexed=None, big_workspace=True):
         """Tables over the keys [0, n_indexed) (default: all); later keys are left to the scan.
-        big_workspace: the two-pass build (codes per table in the workspace) or the one-pass scatter."""
+        big_workspace: the build ordered by window (codes per table in the workspace) or the scatter without it."""
         self.n_indexed = self.n if n_indexed is None else n_indexed
         self.tables = mp.alloc_tables(self.params)
         pb = mp.make_params(n_ctx=self.n_indexed, **self._pkw)

@@ -316,7 +316,7 @@ def test_append_keys_with_frozen_mean(oracle):
 
 
 def test_both_table_builds_give_the_same_buckets(oracle):
-    # 40000 keys: three windows of the two-pass build, the last one partial; (9,120) has 32 tables per pass
+    # 40000 keys: three windows of the build with a workspace, the last one partial; (9,120) has 32 tables per pass
     for cfg, n in (("C2", 40000), ("C4", 20011)):
         w = wl.scaled(wl.CONFIGS[cfg], batch=1, n_ctx=n, n_q_heads=8, n_kv_heads=2)
         data = wl.generate(w)
@@ -327,7 +327,7 @@ def test_both_table_builds_give_the_same_buckets(oracle):
         by_scan = s.attend(debug=False)["out"]
         s.build_tables(big_workspace=False)
         off1, idx1 = s.table_buckets()
-        assert s.table_windows()[0] == 0                         # one-pass build: buckets in no order
+        assert s.table_windows()[0] == 0                         # built without workspace: buckets in no order
         by_unordered_tables = s.attend(debug=False, tables=True)["out"]
         s.build_tables(big_workspace=True)
         off2, idx2 = s.table_buckets()
@@ -532,6 +532,8 @@ def test_matrix_core_key_hashing_on_adversarial_rows(oracle):
         s.hash_keys()
         st = mp.hash_keys_stats(s.params, s.ws)
         print(f"   adversarial rows, centering {use_mu}: {st}", flush=True)
+        if use_mu:                               # more than the workgroups' own lists hold, less than the global one
+            assert st["spilled"] > 0 and not st["overflowed"]
         ref = oracle.hash_keys(Kc[0, 0], W, mu[0, 0] if use_mu else None, K, L)
         np.testing.assert_array_equal(s.key_table_codes()[0, 0], ref)
         s.hash_query()
