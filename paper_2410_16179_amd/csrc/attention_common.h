@@ -396,45 +396,77 @@ __device__ inline void join_partial(WavePartial& w, const float* pp) {
   }
 }
 
+// Sums over the 16 lanes of a row, several values at once: a step folds two values into one (half of the
+// lanes keep either), so that eight values take 25 operations, where eight sums in all lanes take 32 and eight
+// more to pick one each.  fold_rows<8> joins two values, <4> two results of that, <2> two of those; the
+// last_fold of the one value left is, in lane sl, the sum of value row_value<8>(sl), or row_value<4> of four
+// values joined by <8> and <4>.
+template <int CTRL>
+__device__ inline float dpp_lane(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, false));
+}
+template <int BIT>
+__device__ inline float fold_rows(float even, float odd, int sl) {
+  constexpr int kCtrl = BIT == 8 ? 0x140 : (BIT == 4 ? 0x141 : 0x4e);   // mirror of 16, mirror of 8, lane ^ 2
+  const bool hi = (sl & BIT) != 0;
+  return (hi ? odd : even) + dpp_lane<kCtrl>(hi ? even : odd);
+}
+template <int N>
+__device__ inline float last_fold(float v) {
+  if (N == 4) v += dpp_lane<0x4e>(v);
+  return v + dpp_lane<0xb1>(v);                            // lane ^ 1
+}
+template <int N>
+__device__ inline int row_value(int sl) {
+  static_assert(N == 4 || N == 8, "");
+  return sl >> 3 | (sl >> 1 & 2) | (N == 8 ? sl << 1 & 4 : 0);
+}
+constexpr int row_lane(int n) { return (n & 1) << 3 | (n & 2) << 1 | (n & 4) >> 1; }   // a lane whose value is n
+
+// What a wavefront has attended so far: an online max / sum softmax.  Quarter wavefronts hold rows of their
+// own: o is the sum over this quarter's rows.
+struct GatherState {
+  float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, m = -INFINITY, l = 0.f;
+};
+
 // One wavefront attends the keys key_of(0) .. key_of(total - 1) of query head bh (KV unit
 // `unit`).  A quarter wavefront holds
 // one 128-element row; all K and V rows of a batch (kIters rows per quarter wavefront) are
-// requested before any is used; q.k, q.(k-mu), |k-mu|^2 are reduced over the 16 lanes of a
-// row; the inclusion probability and the logit q.k/sqrt(d) - log u are evaluated once per key
+// requested before any is used; q.k and |k-mu|^2 are reduced over the 16 lanes of a
+// row, all rows of the batch at once; the inclusion probability and the logit q.k/sqrt(d) - log u are
+// evaluated once per key
 // (the first n_sampled keys only: the keys behind them, static ones, enter with u = 1); an
 // online max/sum softmax accumulates the weighted V rows.
 // ET: element type of the K / V caches (kBF16, kFP32, or kFP8 with bf16 queries).
-template <int ET, int kIters, class KeyOf>
-__device__ inline WavePartial gather_estimate_wave(const AttnArgs& a, int unit, int64_t bh, int total, int n_sampled,
-                                                   const HeadVectors<ET == kFP32>& hv, KeyOf key_of) {
-  static_assert(kIters >= 1 && kIters <= 16, "one lane of a quarter wavefront per row of a batch");
+// FULL: total is a multiple of the batch, 4 kIters keys.
+template <int ET, int kIters, bool FULL, class KeyOf>
+__device__ inline void gather_estimate_keys(GatherState& st, const AttnArgs& a, int unit, int total, int n_sampled,
+                                            const HeadVectors<ET == kFP32>& hv, KeyOf key_of) {
   constexpr bool FP32 = ET == kFP32;
   const int lane = threadIdx.x & 63;
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const int qd = lane >> 4, sl = lane & 15;
   const int64_t kbase = (int64_t)b * a.ks_b + (int64_t)g * a.ks_h + sl * 8;
   const int64_t vbase = (int64_t)b * a.vs_b + (int64_t)g * a.vs_h + sl * 8;
-  float o[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
 
   // row strides are below 2^31 elements (checked by the host): one 32 x 32 -> 64-bit
   // multiply-add per address
   const uint32_t ksn = (uint32_t)a.ks_n, vsn = (uint32_t)a.vs_n;
   for (int base = 0; base < total; base += 4 * kIters) {
     Frag kf[kIters], vf[kIters];
-    bool ok[kIters];
     // quarter-wavefront rounds of this batch that hold at least one row (wave-uniform): the
     // work of the others is skipped
-    const int rounds = (total - base + 3) >> 2;
+    const int here = total - base, rounds = FULL ? kIters : (here + 3) >> 2;
 #pragma unroll
     for (int it = 0; it < kIters; ++it) {
-      const int cc = base + it * 4 + qd;
-      ok[it] = cc < total;
-      if (it < rounds) {
-        const uint32_t idx = (uint32_t)key_of(ok[it] ? cc : base);
-        if (ok[it]) {
+      if (FULL) {
+        const uint32_t idx = (uint32_t)key_of(base + it * 4 + qd);
+        frag_load<ET>(a.Kc, kbase + (int64_t)((uint64_t)idx * ksn), kf[it]);
+        frag_load<ET>(a.Vc, vbase + (int64_t)((uint64_t)idx * vsn), vf[it]);
+      } else if (it < rounds) {
+        const bool ok = it * 4 + qd < here;
+        const uint32_t idx = (uint32_t)key_of(ok ? base + it * 4 + qd : base);
+        if (ok) {
           frag_load<ET>(a.Kc, kbase + (int64_t)((uint64_t)idx * ksn), kf[it]);
           frag_load<ET>(a.Vc, vbase + (int64_t)((uint64_t)idx * vsn), vf[it]);
         } else {
@@ -455,15 +487,11 @@ __device__ inline WavePartial gather_estimate_wave(const AttnArgs& a, int unit, 
     for (int e = 0; e < 8; ++e) { qq += qf[e] * qf[e]; qm += qf[e] * muf[e]; }
     const float qnorm = sqrtf(row_sum16(qq));
     const float qmu = row_sum16(qm);                       // q.(k - mu) = q.k - q.mu
-    // lane sl == it of quarter qd keeps candidate base + 4*it + qd
-    float my_dq = 0.f, my_nn = 0.f;
-    bool my_ok = false;
-#pragma unroll
-    for (int it = 0; it < kIters; ++it) {
-      if (it >= rounds) break;
+    auto row_dots = [&](int it, float& dq, float& nn) {      // this lane's share of q.k and |k-mu|^2
       float kv[8];
       frag_to_float<ET>(kf[it], kv);
-      float dq = 0.f, nn = 0.f;
+      dq = 0.f;
+      nn = 0.f;
       if constexpr (ET != kBF16) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) dq += qf[e] * kv[e];
@@ -481,48 +509,87 @@ __device__ inline WavePartial gather_estimate_wave(const AttnArgs& a, int unit, 
         const float kc = kv[e] - muf[e];
         nn += kc * kc;
       }
-      dq = row_sum16(dq);
-      nn = row_sum16(nn);
-      if (sl == it) { my_dq = dq; my_nn = nn; my_ok = ok[it]; }
+    };
+    // lane sl of quarter qd keeps candidate base + 4 * (row of this lane) + qd
+    float my_dq = 0.f, my_nn = 0.f;
+    if constexpr (FULL) {                                    // row row_value(sl): the first of the lanes that hold it
+      float dq2[2], nn2[2], dq4[2], nn4[2];                  // two and four rows joined
+#pragma unroll
+      for (int i = 0; i < kIters / 2; ++i) {
+        float dq[2], nn[2];
+        row_dots(2 * i, dq[0], nn[0]);
+        row_dots(2 * i + 1, dq[1], nn[1]);
+        dq2[i & 1] = fold_rows<8>(dq[0], dq[1], sl);
+        nn2[i & 1] = fold_rows<8>(nn[0], nn[1], sl);
+        if (i & 1) {
+          dq4[i >> 1] = fold_rows<4>(dq2[0], dq2[1], sl);
+          nn4[i >> 1] = fold_rows<4>(nn2[0], nn2[1], sl);
+        }
+      }
+      static_assert(kIters == 4 || kIters == 8, "the rows of a batch are joined two by two");
+      my_dq = last_fold<kIters>(kIters == 8 ? fold_rows<2>(dq4[0], dq4[kIters / 8], sl) : dq4[0]);
+      my_nn = last_fold<kIters>(kIters == 8 ? fold_rows<2>(nn4[0], nn4[kIters / 8], sl) : nn4[0]);
+    } else {                                                 // row sl
+#pragma unroll
+      for (int it = 0; it < kIters; ++it) {
+        if (it >= rounds) break;
+        float dq, nn;
+        row_dots(it, dq, nn);
+        dq = row_sum16(dq);
+        nn = row_sum16(nn);
+        if (sl == it) { my_dq = dq; my_nn = nn; }
+      }
     }
+    const int mine = 4 * (FULL ? row_value<kIters>(sl) : sl) + qd;
+    const bool mine_ok = FULL ? (sl & (16 / kIters - 1)) == 0 : sl < kIters && mine < here;
     const float my_dc = my_dq - qmu;
     float logit = -INFINITY;
-    if (sl < kIters && my_ok) {
+    if (mine_ok) {
       logit = my_dq * a.scale;
-      if (base + 4 * sl + qd < n_sampled && a.tau > 0) {   // this lane's key: base + 4*sl + qd
+      if (base + mine < n_sampled && a.tau > 0) {
         const float den = qnorm * sqrtf(my_nn);
         const float cosv = den > 0.f ? my_dc / den : 0.f;
         const float u = fmaxf(inclusion_probability(cosv, a), 1.17549435e-38f);
         logit -= __logf(u);
       }
     }
-    const float m_new = fmaxf(m_run, wave_max(logit));   // finite: the batch is not empty
-    const float alpha = __expf(m_run - m_new);           // m_run = -inf gives 0
+    const float m_new = fmaxf(st.m, wave_max(logit));    // finite: the batch is not empty
+    const float alpha = __expf(st.m - m_new);            // st.m = -inf gives 0
     const float wgt = logit > -INFINITY ? __expf(logit - m_new) : 0.f;
-    l_run = l_run * alpha + wave_sum(wgt);
-    m_run = m_new;
+    st.l = st.l * alpha + wave_sum(wgt);
+    st.m = m_new;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] *= alpha;
+    for (int e = 0; e < 8; ++e) st.o[e] *= alpha;
 #pragma unroll
     for (int it = 0; it < kIters; ++it) {
-      if (it >= rounds) break;
-      const float wv = row_bcast16(wgt, it);               // the weight of this quarter wavefront's row
+      if (!FULL && it >= rounds) break;
+      const float wv = row_bcast16(wgt, FULL ? row_lane(it) : it);     // the weight of this quarter wavefront's row
       float vv[8];
       frag_to_float<ET>(vf[it], vv);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += wv * vv[e];
+      for (int e = 0; e < 8; ++e) st.o[e] += wv * vv[e];
     }
   }
+}
+__device__ inline WavePartial finish_gather(const GatherState& st) {
   WavePartial w;
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    o[e] += __shfl_xor(o[e], 16);
-    o[e] += __shfl_xor(o[e], 32);
-    w.o[e] = o[e];
+    float o = st.o[e];
+    o += __shfl_xor(o, 16);
+    o += __shfl_xor(o, 32);
+    w.o[e] = o;
   }
-  w.m = m_run;
-  w.l = l_run;
+  w.m = st.m;
+  w.l = st.l;
   return w;
+}
+template <int ET, int kIters, class KeyOf>
+__device__ inline WavePartial gather_estimate_wave(const AttnArgs& a, int unit, int total, int n_sampled,
+                                                   const HeadVectors<ET == kFP32>& hv, KeyOf key_of) {
+  GatherState st;
+  gather_estimate_keys<ET, kIters, false>(st, a, unit, total, n_sampled, hv, key_of);
+  return finish_gather(st);
 }
 
 }  // namespace mp

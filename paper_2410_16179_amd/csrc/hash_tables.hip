@@ -895,7 +895,7 @@ __global__ __launch_bounds__(1024) void lookup_gather_kernel(AttnArgs a, TableAr
   // static keys slot, slot + slots, ... ride along behind the sampled ones
   const int slots = a.lg_nslices * 16, slot = slice * 16 + wave;
   const int nst = static_share(cx, slot, slots);
-  const WavePartial wp = gather_estimate_wave<ET, (FP32 ? 4 : 8)>(a, unit, bh, n_sampled + nst, n_sampled, hv, [&](int cc) {
+  const WavePartial wp = gather_estimate_wave<ET, (FP32 ? 4 : 8)>(a, unit, n_sampled + nst, n_sampled, hv, [&](int cc) {
     if (cc >= n_sampled) return static_key(a, cx, slot + (int64_t)(cc - n_sampled) * slots);
     return (cc < in_slice ? wave_key0 : app_blk * kBlockKeys) + (int64_t)list[cc];
   });

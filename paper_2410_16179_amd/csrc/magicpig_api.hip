@@ -118,15 +118,16 @@ size_t ws_hash_for(const magicpig_params* p, int64_t n_keys) {
 }
 
 // decode workspace: [partials | ballots]
-struct AttnWs { size_t partial_off, masks_off, total; int nranges, nscan, f_nranges, f_wave_blocks, f_touch; int64_t n_static; };
+struct AttnWs { size_t partial_off, masks_off, total; int nranges, f_nranges, f_wave_blocks, f_touch; int64_t n_static; };
 AttnWs ws_attention_layout(const magicpig_params* p) {
   AttnWs w{};
   const int64_t nblk = mp::key_blocks(p->n_ctx);
   const size_t heads = (size_t)p->batch * p->n_q_heads;
-  w.nscan = (int)((nblk + mp::kRangeBlocks - 1) / mp::kRangeBlocks);
   const int64_t st = (int64_t)p->n_sink + p->n_local;
   w.n_static = st < p->n_ctx ? st : p->n_ctx;
-  w.nranges = w.nscan + (int)((w.n_static + mp::kStaticPerRange - 1) / mp::kStaticPerRange);
+  // room for the separate gather (which takes one partial per run of kRangeBlocks key blocks or more): one for every
+  // kRangeBlocks key blocks, and one for every 32 static keys
+  w.nranges = (int)((nblk + mp::kRangeBlocks - 1) / mp::kRangeBlocks + (w.n_static + 31) / 32);
   // lookup + gather in one launch: 16 partials per slice
   const int lg = (int)((nblk + mp::kLgSliceBlocks - 1) / mp::kLgSliceBlocks) * 16;
 
@@ -325,7 +326,7 @@ int run_attention_impl(const magicpig_params* p, const void* q, const void* K_ca
   char* wsb = reinterpret_cast<char*>(workspace);
   a.partial = reinterpret_cast<float*>(wsb + wl.partial_off); a.out = out;
   a.masks = reinterpret_cast<uint64_t*>(wsb + wl.masks_off);
-  a.nranges = wl.nranges; a.nscan = wl.nscan; a.n_static = wl.n_static;
+  a.nranges = wl.nranges; a.n_static = wl.n_static;
   a.f_nranges = wl.f_nranges; a.f_wave_blocks = wl.f_wave_blocks; a.f_touch = wl.f_touch;
   a.dbg_counts = dbg_counts; a.dbg_cand = dbg_cand; a.dbg_ncand = dbg_ncand; a.dbg_cand_cap = dbg_cand_cap;
   a.dbg_stride = p->n_ctx; a.n_dev = p->n_ctx_dev;

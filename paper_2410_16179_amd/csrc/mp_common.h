@@ -213,13 +213,13 @@ struct AttnArgs {
   const int64_t* n_dev;
   int64_t blk_begin;         // first key block the collision scan covers (blocks before it: table lookup)
   int64_t ks_b, ks_h, ks_n, vs_b, vs_h, vs_n;
-  int nranges;               // partials per head: nscan runs of kRangeBlocks key blocks + static runs
-  int nscan;                 // runs of kRangeBlocks key blocks per head
+  int nranges;               // partials per head (set by the launcher of a form; 0: no keys)
   int64_t n_static;          // keys in the static set T
   // scan and gather in one launch: one workgroup, and one partial per head, for every run of
   // 4 * f_wave_blocks key blocks (f_wave_blocks: key blocks per wavefront, 1 .. kFusedWaveBlocks)
   int f_nranges, f_wave_blocks;
   int f_touch;               // 1: more than three workgroups per compute unit (wavefronts touch the rows of the keys of their last block)
+  int g_run_blocks;          // the separate gather: key blocks per wavefront, a multiple of kRangeBlocks
   // lookup + gather in one launch: slices of the indexed range; the first lg_app_runs of them
   // also take a run of 16 appended key blocks each
   int lg_nslices, lg_app_runs;
@@ -247,8 +247,7 @@ struct TableArgs {
 constexpr int kBuildWindow = 16384;   // keys one workgroup places into the buckets of one table
 
 constexpr int kPartialStride = 132;   // 128 output elements, running max, running sum, pad
-constexpr int kRangeBlocks = 16;      // key blocks per gather wavefront (1024 keys)
-constexpr int kStaticPerRange = 32;   // static (sink / local) keys per gather wavefront
+constexpr int kRangeBlocks = 16;      // key blocks whose ballots a gather wavefront expands at a time (1024 keys)
 constexpr int kLgWaveBlocks = 16;     // lookup + gather in one launch: key blocks per wavefront,
 constexpr int kLgSliceBlocks = 16 * kLgWaveBlocks;   // and per workgroup (16 wavefronts): one build window
 static_assert(kLgSliceBlocks * kBlockKeys == kBuildWindow, "a lookup slice is a window of the table build");

@@ -65,58 +65,71 @@ __global__ __launch_bounds__(256) void collision_scan_kernel(AttnArgs a) {
 // rows per quarter wavefront and batch of the stand-alone gather: 32 K and 32 V rows in flight
 template <int ET> constexpr int kGatherIters = ET == kFP32 ? 4 : 8;
 
-// One wavefront = one (query head, run of kRangeBlocks key blocks).  blockDim = 64 * G:
-// the G wavefronts of a workgroup serve the G heads of one KV head on the same run.
+// One wavefront = one (query head, run of g_run_blocks key blocks).  blockDim = 64 * G:
+// the G wavefronts of a workgroup serve the G heads of one KV head on the same run.  The ballots of
+// sixteen blocks at a time are expanded into an index list in LDS by a prefix sum; full batches of rows are taken
+// from its front, and what is left waits for the next sixteen blocks.  The keys of the static set T are
+// dealt over the runs (key j to run j mod runs) and join the last batch.
+// Bound by the rows it gathers (random 256-byte rows) and by the vector unit.  512 heads x 131072 keys, (10,170), 1.3
+// million rows: 152 us (643 MB at 4.2 TB/s, vector unit 73 % busy) with a wavefront for each 1024 keys, about 20 of the 32
+// rows of a batch and workgroups of their own for T; now 122 us (5.3 TB/s): the estimator's arithmetic, once per
+// batch, serves 32 rows, full batches need no masks, and the 16-lane sums of a batch are taken together.
+// Four wavefronts per SIMD (128 registers; at 141, three, it was 40 % slower).
 template <int ET>
-__global__ __launch_bounds__(512) void gather_estimate_kernel(AttnArgs a) {
+__global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
   constexpr bool FP32 = ET == kFP32;
-  __shared__ uint16_t lists[8][kRangeBlocks * kBlockKeys];
+  constexpr int kIt = kGatherIters<ET>, kBatch = 4 * kIt;
+  __shared__ uint16_t lists[8][kRangeBlocks * kBlockKeys + kBatch];
   const Ctx c = resolve_context(a);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const int unit = blockIdx.y, range = blockIdx.x;
+  const int unit = blockIdx.y, run = blockIdx.x;
   const int b = unit / a.Hkv, g = unit % a.Hkv;
   const int G = a.Hq / a.Hkv;
   const int64_t bh = (int64_t)b * a.Hq + (int64_t)g * G + wave;
   const int64_t nblk = key_blocks(c.n);
-  const int64_t blk0 = (int64_t)range * kRangeBlocks;
+  const int64_t blk0 = (int64_t)run * a.g_run_blocks;
   uint16_t* list = lists[wave];
   HeadVectors<FP32> hv;
   request_head_vectors<FP32>(a, unit, bh, hv);
-
-  // Ranges below nscan cover 16 key blocks of sampled keys; the ranges after them cover the
-  // static set T (sink + local window), kStaticPerRange keys each, taken exactly (u = 1).
-  const bool is_static = range >= a.nscan;
-  int total;
-  int64_t static_first = 0;
-  if (!is_static) {
-    // ---- expand the scan's ballots into an index list (wavefront prefix sum) ----
-    uint64_t m = 0;
-    if (lane < kRangeBlocks && blk0 + lane < nblk) m = a.masks[bh * nblk + blk0 + lane];
+  const int nruns = gridDim.x, nst = static_share(c, run, nruns);
+  const uint64_t* masks = a.masks + bh * nblk;
+  auto ballots = [&](int at) {                             // lane i < 16: block blk0 + at + i
+    return lane < kRangeBlocks && at < a.g_run_blocks && blk0 + at + lane < nblk ? masks[blk0 + at + lane] : 0ull;
+  };
+  GatherState st;
+  int have = 0;                                            // keys in the list
+  uint64_t next = ballots(0);
+#pragma unroll 1
+  for (int at = 0; at < a.g_run_blocks; at += kRangeBlocks) {
+    uint64_t m = next;
+    next = ballots(at + kRangeBlocks);
     const int pc = __popcll(m);
     static_assert(kRangeBlocks <= 16, "the ballots of a range are summed over one row of 16 lanes");
     const int incl = row_prefix_sum16(pc);
-    total = __builtin_amdgcn_readlane(incl, kRangeBlocks - 1);
-    int pos = incl - pc;
+    int pos = have + incl - pc;
     while (m) {
       const int bit = __ffsll((unsigned long long)m) - 1;
-      list[pos++] = (uint16_t)(lane * kBlockKeys + bit);
+      list[pos++] = (uint16_t)((at + lane) * kBlockKeys + bit);
       m &= m - 1;
     }
+    have += __builtin_amdgcn_readlane(incl, kRangeBlocks - 1);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
-  } else {
-    static_first = (int64_t)(range - a.nscan) * kStaticPerRange;
-    const int64_t left = c.n_static - static_first;
-    total = (int)(left < kStaticPerRange ? left : kStaticPerRange);
+    const int full = have / kBatch * kBatch, left = have - full;
+    if (full > 0)
+      gather_estimate_keys<ET, kIt, true>(st, a, unit, full, full, hv, [&](int cc) { return blk0 * kBlockKeys + (int64_t)list[cc]; });
+    const uint16_t k = lane < left ? list[full + lane] : (uint16_t)0;   // fewer than a batch are left: to the front
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    if (lane < left) list[lane] = k;
+    have = left;
   }
-  float* pp = a.partial + (bh * a.nranges + range) * kPartialStride;
-  if (!is_static) {
-    store_partial(gather_estimate_wave<ET, kGatherIters<ET>>(a, unit, bh, total, total, hv,
-                               [&](int cc) { return blk0 * kBlockKeys + (int64_t)list[cc]; }), pp);
-  } else {
-    store_partial(gather_estimate_wave<ET, kGatherIters<ET>>(a, unit, bh, total, 0, hv,
-                               [&](int cc) { return static_key(a, c, static_first + cc); }), pp);
-  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+  __builtin_amdgcn_wave_barrier();
+  gather_estimate_keys<ET, kIt, false>(st, a, unit, have + nst, have, hv, [&](int cc) {
+    return cc < have ? blk0 * kBlockKeys + (int64_t)list[cc] : static_key(a, c, run + (int64_t)(cc - have) * nruns);
+  });
+  store_partial(finish_gather(st), a.partial + (bh * a.nranges + run) * kPartialStride);
 }
 
 // Wavefronts that share the keys of a run and head in the one-launch scan + gather (KT, HT: compile-time K, 0
@@ -252,7 +265,7 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
     // this wavefront's share: candidates lo .. lo + mine - 1
     const int share = (all + parts - 1) / parts, lo = part * share;
     const int mine = parts == 1 ? all : (all - lo < share ? (all > lo ? all - lo : 0) : share);
-    return gather_estimate_wave<ET, kIt>(ga, unit, head0 + h, mine, total - lo, hv, [&](int cl) {
+    return gather_estimate_wave<ET, kIt>(ga, unit, mine, total - lo, hv, [&](int cl) {
       const int cc = cl + lo;
       if (cc >= total) return static_key(ga, c, run + (int64_t)(cc - total) * nruns);
       const int w = (cc >= s1) + (cc >= s2) + (cc >= s3);
@@ -416,6 +429,15 @@ static void launch_scan_gather_for(const AttnArgs& a, dim3 grid, hipStream_t s, 
   }
 }
 
+// Key blocks of a gather wavefront, in pieces of kRangeBlocks.  A wavefront that takes several pieces fills its
+// batches of rows (a piece samples about 20 keys of a batch's 32 at 2 %), asks for the next piece's ballots early
+// and leaves one partial; but ten wavefronts per compute unit have to remain.  Measured (us per step through
+// tables, pieces 1 | 2 | 3 | 4 | 8): 512 heads x 131072 keys, (10,170), - | 181 | - | 166.5 |
+// 161.8 (16: 162.5); (10,150): 512 x 32768 62.9 | 59.6 | 59.3 | 58.2 | 58.0; 128 x 65536
+// 43.6 | 42.4 | 42.5 | 43.1 | 47.4; 64 x 98304 42.4 | 40.6 | 39.2 | 40.6 | 48.6; 256 x 20000, (9,120), 46.0 | 45.6 | 45.5 | 49.5 | 60.8.
+constexpr int64_t kGatherWaves = 10 * kNumCU;
+constexpr int64_t kMaxGatherPieces = 8;
+
 static hipError_t launch_scan_gather(const AttnArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 grid((unsigned)a.f_nranges, (unsigned)(a.B * a.Hkv));
 #define MP_TUNED(KT, LL) if (a.K == KT && a.L == LL) launch_scan_gather_for<KT, words_of(LL), tail_of(LL)>(a, grid, s, start, stop); else
@@ -479,12 +501,18 @@ hipError_t launch_sampled_attention(const AttnArgs& a, const TableArgs* tables, 
     if ((e = launch_merge(b, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr)) != hipSuccess) return e;
     return hipGetLastError();
   }
-  const dim3 grid((unsigned)a.nranges, (unsigned)(a.B * a.Hkv)), block(64 * (a.Hq / a.Hkv));
-  if (a.is_fp32) launch_timed(gather_estimate_kernel<kFP32>, grid, block, s, nullptr, ev ? ev[2] : nullptr, a);
-  else if (a.kv_fp8) launch_timed(gather_estimate_kernel<kFP8>, grid, block, s, nullptr, ev ? ev[2] : nullptr, a);
-  else launch_timed(gather_estimate_kernel<kBF16>, grid, block, s, nullptr, ev ? ev[2] : nullptr, a);
+  AttnArgs b = a;                                          // (no more partials than a.nranges, for which there is room)
+  const int64_t nblk = key_blocks(a.n);
+  int64_t pieces = heads * ((nblk + kRangeBlocks - 1) / kRangeBlocks) / kGatherWaves;
+  pieces = pieces < 1 ? 1 : (pieces > kMaxGatherPieces ? kMaxGatherPieces : pieces);
+  b.g_run_blocks = (int)pieces * kRangeBlocks;
+  b.nranges = (int)((nblk + b.g_run_blocks - 1) / b.g_run_blocks);
+  const dim3 grid((unsigned)b.nranges, (unsigned)(a.B * a.Hkv)), block(64 * (a.Hq / a.Hkv));
+  if (a.is_fp32) launch_timed(gather_estimate_kernel<kFP32>, grid, block, s, nullptr, ev ? ev[2] : nullptr, b);
+  else if (a.kv_fp8) launch_timed(gather_estimate_kernel<kFP8>, grid, block, s, nullptr, ev ? ev[2] : nullptr, b);
+  else launch_timed(gather_estimate_kernel<kBF16>, grid, block, s, nullptr, ev ? ev[2] : nullptr, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return launch_merge(a, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr);
+  return launch_merge(b, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr);
 }
 
 }  // namespace mp
