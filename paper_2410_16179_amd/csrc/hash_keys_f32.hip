@@ -1,7 +1,7 @@
 // SimHash coding of cached float32 keys on the matrix cores (Sec. 4.3 "Hash function selection").
 //
-// A workgroup codes 32 keys of one (batch, KV head) against the 32 K projector columns of one table
-// group; a wavefront takes every fourth tile of 32 neighbouring columns (v_mfma_f32_32x32x2_f32: A
+// A workgroup codes 32 or 64 keys of one (batch, KV head) against the 32 K projector columns of one table
+// group; each of its K wavefronts takes a tile of 32 neighbouring columns (v_mfma_f32_32x32x2_f32: A
 // operand = columns, B operand = keys, so an accumulator register holds one (column, key) pair with
 // lane % 32 = key).  W is read as it is stored, row by row, 128 contiguous bytes per half wavefront,
 // from L2: the call needs no workspace and no pass over W before it.  The sign bits of a key come out
@@ -18,9 +18,11 @@
 // cannot overflow - and re-evaluated in float64 from exact products, and what float64 cannot decide
 // is summed exactly (exact_dot.h).
 //
-// 4096 keys x 600 columns (one head, (8,75)): 24.6 us, a chain of latencies (two tiles of 64 dependent
-// matrix instructions per wavefront are 4 us of it); the first version, a float64 dot product per lane
-// with the columns of neighbouring lanes K elements apart, took 1038 us.
+// A chain of latencies, so all 64 elements of a lane's column are requested at once, together with the keys, which
+// wait in LDS (16 at a time, the next ones requested while those before them are multiplied, cost a round trip to
+// L2 each).  4096 keys x 600 columns (one head, (8,75)): 24.6 us with four wavefronts, two tiles each and the
+// keys in registers, 19.3 now.  8 x 2048 keys x 1500 columns: the call 115 us, 102 now (6.7 GFLOP: 43 us at the rate of the
+// instruction).
 #include "mp_common.h"
 #include "exact_dot.h"
 #include "device_utils.h"
@@ -30,108 +32,128 @@ namespace mp {
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 constexpr float kGammaF32 = 3.0517578125e-5f;             // 2^-15
-constexpr int kTileKeys = 32;
+constexpr int kKeyRow = kHeadDim + 4;                      // floats of a key's row in LDS (16 lanes' 16-byte pieces on 64 banks)
 
-__global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a, uint32_t tiles, uint32_t jobs) {
+// LDS of a workgroup: the keys, the list of pairs to re-evaluate and the accumulators of the exact sums, by K wavefronts
+static size_t hash_f32_lds(int K, int keys) {
+  return (size_t)K * kLimbs * sizeof(long long) + keys * kKeyRow * sizeof(float) + (size_t)K * 32 * keys * sizeof(uint16_t);
+}
+
+// KT: 32-key tiles of a workgroup.
+template <int KT>
+__global__ __launch_bounds__(1024, 4) void hash_keys_f32_kernel(HashDirectArgs a, uint32_t tiles, uint32_t jobs) {
+  constexpr int kTileKeys = 32 * KT;                      // keys of a workgroup
+  extern __shared__ long long lds[];
   __shared__ uint32_t colbits[16][kTileKeys];             // [32-column tile][key]: sign bits in column order
   __shared__ uint32_t plane[16][kTileKeys];               // last table group: its plane words
-  __shared__ uint16_t list[16 * 32 * kTileKeys];          // pairs to re-evaluate: column << 5 | key
+  __shared__ float norms[kTileKeys];
   __shared__ unsigned count;
-  __shared__ long long limbs[4][kLimbs];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, nthreads = blockDim.x;      // 64 K
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int kap = lane & 31, hh = lane >> 5;
   const int unit = blockIdx.y;
   const int K = a.K, ncol = a.K * a.L, Wd = table_words(a.L);
+  long long* limbs = lds + wave * kLimbs;
+  float* keys = reinterpret_cast<float*>(lds + K * kLimbs);   // [key][kKeyRow]: fl(k - mu)
+  uint16_t* list = reinterpret_cast<uint16_t*>(keys + kTileKeys * kKeyRow);   // column << 6 | key
   const int64_t first = a.first_key, last = a.first_key + a.n_keys;
   const int64_t ubase = (int64_t)(unit / a.n_kv_heads) * a.stride_b + (int64_t)(unit % a.n_kv_heads) * a.stride_h;
   const float* X = reinterpret_cast<const float*>(a.X) + ubase;
   const float* W = reinterpret_cast<const float*>(a.W);
   const float* mu = a.mu ? a.mu + (int64_t)unit * kHeadDim : nullptr;
-  if (lane < kLimbs) limbs[wave][lane] = 0;
+  if (lane < kLimbs) limbs[lane] = 0;
 
   for (uint32_t job = blockIdx.x; job < jobs; job += gridDim.x) {
     const int w = (int)(job / tiles);
     const int64_t key0 = (first / kTileKeys + (int64_t)(job % tiles)) * kTileKeys;
-    const int64_t key = key0 + kap;
-    const bool key_ok = key >= first && key < last;
-    const int64_t krow = key_ok ? key : first;            // (any valid row for masked lanes)
     if (tid == 0) count = 0;
 
-    // ---- B operand: k - mu, lane half hh holds the elements 64 hh .. 64 hh + 63 ----
-    float B[64];
-    float ss = kSquareSlack;
+    // ---- A operand: this lane's column of the wavefront's tile, lane half hh holds the elements 64 hh ..
+    // 64 hh + 63; half of them are requested here and travel together with the keys ----
+    const int tile = wave;
+    const int j = 32 * w * K + 32 * tile + kap;
+    const bool col_ok = j < ncol;
+    const uint32_t at = (uint32_t)(64 * hh * ncol + (col_ok ? j : 0));   // (128 * 8192 elements at most)
+    float A[64];
+    const float* wrow = W;
+#pragma unroll
+    for (int i = 0; i < 64; ++i) {
+      A[i] = wrow[at];
+      wrow += ncol;
+      asm volatile("" : "+s"(wrow));                       // (row addresses are worked out one by one: the registers are few)
+    }
+
+    // ---- B operand: k - mu, staged in LDS; sixteen lanes take a row ----
+    for (int p = tid; p < kTileKeys * 16; p += nthreads) {
+      const int row = p >> 4, c = (p & 15) * 8;
+      const int64_t rkey = key0 + row;
+      float v[8], m[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      load8<kFP32>(X, (rkey >= first && rkey < last ? rkey : first) * a.stride_n + c, v);   // (any valid row for masked keys)
+      if (mu) load8<kFP32>(mu, c, m);
+      float ss = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] -= m[e];
+        ss = fmaf(v[e], v[e], ss);
+      }
+      *reinterpret_cast<float4*>(keys + row * kKeyRow + c) = make_float4(v[0], v[1], v[2], v[3]);
+      *reinterpret_cast<float4*>(keys + row * kKeyRow + c + 4) = make_float4(v[4], v[5], v[6], v[7]);
+      ss = row_sum16(ss) + kSquareSlack;
+      if ((p & 15) == 0) norms[row] = sqrtf(ss) * 1.00002f;
+    }
+    __syncthreads();                                      // (count is clear, too)
+
     {
-      const float4* kr = reinterpret_cast<const float4*>(X + krow * a.stride_n + 64 * hh);
+      float w2 = kSquareSlack;
+      f32x16 acc[KT];
+#pragma unroll
+      for (int t = 0; t < KT; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+      const float4* brow = reinterpret_cast<const float4*>(keys + kap * kKeyRow + 64 * hh);
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const float4 v = kr[i];
-        B[4 * i] = v.x; B[4 * i + 1] = v.y; B[4 * i + 2] = v.z; B[4 * i + 3] = v.w;
-      }
-      if (mu) {
-        const float4* mr = reinterpret_cast<const float4*>(mu + 64 * hh);
+        float4 b4[KT];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float4 v = mr[i];
-          B[4 * i] -= v.x; B[4 * i + 1] -= v.y; B[4 * i + 2] -= v.z; B[4 * i + 3] -= v.w;
-          if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (a few at a time: the registers are few)
+        for (int t = 0; t < KT; ++t) b4[t] = brow[t * 32 * (kKeyRow / 4) + i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          w2 = fmaf(A[4 * i + e], A[4 * i + e], w2);
+#pragma unroll
+          for (int t = 0; t < KT; ++t) {
+            const float bv = e == 0 ? b4[t].x : (e == 1 ? b4[t].y : (e == 2 ? b4[t].z : b4[t].w));
+            acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(A[4 * i + e], bv, acc[t], 0, 0, 0);
+          }
         }
-      }
-#pragma unroll
-      for (int i = 0; i < 64; ++i) ss = fmaf(B[i], B[i], ss);
-    }
-    ss += __shfl_xor(ss, 32);
-    const float xnorm = sqrtf(ss) * 1.00002f;
-    __syncthreads();                                      // count is clear
-
-    for (int tile = wave; tile < K; tile += 4) {
-      const int j = 32 * w * K + 32 * tile + kap;         // this lane's column (A operand row)
-      const bool col_ok = j < ncol;
-      // 16 elements of the column are requested while the 16 before them are multiplied
-      const uint32_t at = (uint32_t)(64 * hh * ncol + (col_ok ? j : 0));   // (128 * 8192 elements at most)
-      float A[2][16];
-      float w2 = kSquareSlack;
-      f32x16 acc;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-      uint32_t step = (uint32_t)ncol;
-      asm volatile("" : "+s"(step));                       // (row offsets are worked out here, not kept across tiles)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) A[0][i] = (W + (uint32_t)i * step)[at];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        if (c < 3) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) A[(c + 1) & 1][i] = (W + (uint32_t)(16 * (c + 1) + i) * step)[at];
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          w2 = fmaf(A[c & 1][i], A[c & 1][i], w2);
-          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(A[c & 1][i], B[16 * c + i], acc, 0, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        if (i % 4 == 3) __builtin_amdgcn_sched_barrier(0);
       }
       w2 += __shfl_xor(w2, 32);
-      const float bound = key_ok ? kGammaF32 * xnorm * (sqrtf(wave_max(w2)) * 1.00002f) + 1e-30f : -1.f;
-      // register r: column 8 (r / 4) + 4 hh + r % 4 of the tile
-      uint32_t neg = 0, fl = 0;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        neg |= (uint32_t)(acc[r] < 0.f) << r;
-        fl |= (uint32_t)!(fabsf(acc[r]) > bound) << r;
-      }
+      const float wnorm = kGammaF32 * (sqrtf(wave_max(w2)) * 1.00002f);
+      const int left = ncol - (32 * w * K + 32 * tile);   // columns from the first of the tile on
+      const uint32_t real = left >= 32 ? ~0u : (left > 0 ? (1u << left) - 1u : 0u);
       auto spread = [&](uint32_t m) {
         return ((m & 0xfu) | (m & 0xf0u) << 4 | (m & 0xf00u) << 8 | (m & 0xf000u) << 12) << (4 * hh);
       };
-      const int left = ncol - (32 * w * K + 32 * tile);   // columns from the first of the tile on
-      const uint32_t real = left >= 32 ? ~0u : (left > 0 ? (1u << left) - 1u : 0u);
-      uint32_t bits = spread(~neg & 0xffffu);
-      bits |= __shfl_xor(bits, 32);
-      uint32_t close = key_ok ? spread(fl) & real : 0u;
-      if (hh == 0) colbits[tile][kap] = bits & real;
-      if (close) {
-        unsigned pos = atomicAdd(&count, (unsigned)__popc(close));
-        for (; close; close &= close - 1) list[pos++] = (uint16_t)((32 * tile + __ffs(close) - 1) << 5 | kap);
+#pragma unroll
+      for (int t = 0; t < KT; ++t) {
+        const int ek = 32 * t + kap;
+        const bool key_ok = key0 + ek >= first && key0 + ek < last;
+        const float bound = key_ok ? wnorm * norms[ek] + 1e-30f : -1.f;
+        // register r: column 8 (r / 4) + 4 hh + r % 4 of the tile
+        uint32_t neg = 0, fl = 0;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          neg |= (uint32_t)(acc[t][r] < 0.f) << r;
+          fl |= (uint32_t)!(fabsf(acc[t][r]) > bound) << r;
+        }
+        uint32_t bits = spread(~neg & 0xffffu);
+        bits |= __shfl_xor(bits, 32);
+        uint32_t close = key_ok ? spread(fl) & real : 0u;
+        if (hh == 0) colbits[tile][ek] = bits & real;
+        if (close) {
+          unsigned pos = atomicAdd(&count, (unsigned)__popc(close));
+          for (; close; close &= close - 1) list[pos++] = (uint16_t)((32 * tile + __ffs(close) - 1) << 6 | ek);
+        }
       }
     }
     __syncthreads();
@@ -140,10 +162,10 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
     const unsigned cnt = count;
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    for (unsigned i0 = wave * 4; i0 < cnt; i0 += 16) {
+    for (unsigned i0 = wave * 4; i0 < cnt; i0 += 4 * K) {
       const unsigned i = i0 + (ln >> 4);
       const bool on = i < cnt;
-      const int e = list[on ? i : i0], col = e >> 5, ek = e & 31, sl = ln & 15;
+      const int e = list[on ? i : i0], col = e >> 6, ek = e & 63, sl = ln & 15;
       const int j = 32 * w * K + col;
       const float* kr = X + (key0 + ek) * a.stride_n;
       float kv[8], wv[8], mv[8];
@@ -175,7 +197,7 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
         const int sj = __shfl(j, src), sk = __shfl(ek, src);
         const float* skr = X + (key0 + sk) * a.stride_n;
         const bool r = exact_sign_nonneg_wave(
-            limbs[wave], [&](int d) { return (double)skr[d]; }, [&](int d) { return (double)W[(int64_t)d * ncol + sj]; },
+            limbs, [&](int d) { return (double)skr[d]; }, [&](int d) { return (double)W[(int64_t)d * ncol + sj]; },
             [&](int d) { return mu ? (double)mu[d] : 0.0; }, mu != nullptr);
         if (lane == src) bit = r;
         pending &= pending - 1;
@@ -191,9 +213,10 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
     const bool tail = w == Wd - 1;
     int t0 = tid;
     asm volatile("" : "+v"(t0));                            // (nothing of this is kept in registers across jobs)
-    for (int item = t0; item < K * kTileKeys; item += 256) {
-      const int b = item >> 5, ek = item & 31;
+    for (int item = t0; item < K * kTileKeys; item += nthreads) {
+      const int b = item / kTileKeys, ek = item % kTileKeys;
       uint32_t word = 0;
+#pragma unroll 8
       for (int beta = 0, pos = b; beta < 32; ++beta, pos += K)
         word |= ((colbits[pos >> 5][ek] >> (pos & 31)) & 1u) << beta;
       if (tail) plane[b][ek] = word;
@@ -206,8 +229,8 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
     if (tail) {
       // the K planes of the last group as one bit string of tail_tables bits each
       const int Lt = tail_tables(a.L), xs = tail_begin(K, a.L), nt = a.NW - xs;
-      for (int item = t0; item < nt * kTileKeys; item += 256) {
-        const int ek = item & 31, e = item >> 5;
+      for (int item = t0; item < nt * kTileKeys; item += nthreads) {
+        const int ek = item % kTileKeys, e = item / kTileKeys;
         uint32_t word = 0;
         int b = 32 * e / Lt, at = 32 * e % Lt;            // plane and table of bit 32 e
         for (int have = 0; have < 32 && b < K; ++b, at = 0) {
@@ -225,11 +248,20 @@ __global__ __launch_bounds__(256, 3) void hash_keys_f32_kernel(HashDirectArgs a,
 
 // Keys [first_key, first_key + n_keys) of every unit (n_keys > 0).
 hipError_t launch_hash_keys_f32(const HashDirectArgs& a, int units, hipStream_t s) {
-  const int64_t tiles = (a.first_key + a.n_keys - 1) / kTileKeys - a.first_key / kTileKeys + 1;
-  const int64_t jobs = tiles * table_words(a.L);           // n_cap <= 2^31 keys: below 2^31
-  const int64_t most = (int64_t)1 << 22;                   // (gridDim.x * 256 threads below 2^32; the kernel walks the rest)
-  hipLaunchKernelGGL(hash_keys_f32_kernel, dim3((unsigned)(jobs < most ? jobs : most), (unsigned)units), dim3(256), 0, s, a,
-                     (uint32_t)tiles, (uint32_t)jobs);
+  auto go = [&](auto kernel, int keys) {
+    const int64_t tiles = (a.first_key + a.n_keys - 1) / keys - a.first_key / keys + 1;
+    const int64_t jobs = tiles * table_words(a.L);         // n_cap <= 2^31 keys: below 2^31
+    const int64_t most = (int64_t)1 << 21;                 // (gridDim.x * 1024 threads below 2^32; the kernel walks the rest)
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(jobs < most ? jobs : most), (unsigned)units), dim3(64 * a.K), hash_f32_lds(a.K, keys), s, a,
+                       (uint32_t)tiles, (uint32_t)jobs);
+  };
+  // 64 keys as soon as workgroups of 32 are more than one per compute unit: a projector element then serves two
+  // matrix instructions.  Mean and codes, us, 32 | 64 keys: 128 workgroups of 32 (1024 keys, (9,110)) 18.4 | 26.2; 256
+  // (4096, (16,64)) 23.2 | 33.0; 384 (4096, (8,75)) 24.0 | 23.2; 896 (8 x 501, (10,220)) 55.6 | 48.6; 2048 (4 x 4096,
+  // (4,100)) 42.5 | 41.9; 2560 (8 x 2048, (10,150)) 126.9 | 107.6.
+  const int64_t tiles32 = (a.first_key + a.n_keys - 1) / 32 - a.first_key / 32 + 1;
+  if (tiles32 * table_words(a.L) * units > kNumCU) go(hash_keys_f32_kernel<2>, 64);
+  else go(hash_keys_f32_kernel<1>, 32);
   return hipGetLastError();
 }
 
