@@ -225,21 +225,57 @@ __device__ inline void scan_blocks(const AttnArgs& a, const Ctx& c, int unit, in
   }
 }
 
+// The first words of a key block as scan_block_any takes them: groups of four, and the 1-3 words behind the last.
+// GT: heads the scan is laid out for.  AHEAD groups are in flight: eight where a wavefront compares each with four or
+// eight heads (step, 8 KV heads, four | eight groups: 32 heads x 98304 keys, (10,300) 102.0 | 81.1 us, 60000, (9,100) 39.9 | 36.6,
+// 4000 float32 keys, (10,200) 30.3 | 27.6), four with one or two, where the registers do more for the gather (32 KV heads x
+// 20011, (9,110) 39.9 | 41.3; 64 KV heads of two x 65536, e4m3, (9,75) 116.9 | 122.0).
+template <int GT> constexpr int kAnyAhead = GT >= 4 ? 8 : 4;
+typedef unsigned int CodeWords __attribute__((ext_vector_type(4)));
+template <int GT>
+struct AnyWords {
+  CodeWords group[kAnyAhead<GT>];
+  uint32_t rest[3];
+};
+__device__ inline CodeWords load_group(const uint32_t* blkp, int lane, int g) {
+  return __builtin_nontemporal_load(reinterpret_cast<const CodeWords*>(blkp + g * 256) + lane);
+}
+template <int GT>
+__device__ inline void load_rest(const uint32_t* blkp, int lane, int full, int rem, AnyWords<GT>& v) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (i < rem) v.rest[i] = __builtin_nontemporal_load(blkp + full * 256 + lane * rem + i);
+}
+template <int GT>
+__device__ inline void request_any(const AttnArgs& a, int unit, int64_t blk, int lane, AnyWords<GT>& ahead) {
+  constexpr int kAhead = kAnyAhead<GT>;
+  const uint32_t* blkp = a.kcodes + ((int64_t)unit * a.blocks_cap + blk) * (kBlockKeys * (int64_t)a.NW);
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i)
+    if (i < a.NW >> 2) ahead.group[i] = load_group(blkp, lane, i);
+  load_rest(blkp, lane, a.NW >> 2, a.NW & 3, ahead);
+}
+
 // Any K and L: one wavefront compares the 64-key code block blk < key_blocks(n) of KV unit `unit`
 // (lane = key) with the codes of the query heads h_begin .. h_begin + G - 1 of the unit, G <= GT, and
 // hands emit(h, blk, ballot) the sampled keys.  The words of a key are taken in the order they are
-// stored, 16 bytes per load with four loads in flight, and each is compared with all heads while it
+// stored, 16 bytes per load with several loads in flight, and each is compared with all heads while it
 // is in registers: diff collects the planes of a table group, and every K words the group's colliding
 // tables are counted.  The last group's planes are taken off its bit string as its words come in.
 // GT = 1, 2, 4, 8: heads the registers are laid out for (heads beyond G repeat the last one).
 // (The first version read every word anew for every head, one at a time: 32 KV heads of one query head,
-// 20011 keys, (9,110): scan_gather_kernel 54 us; now 30 us for 87 MB.)
+// 20011 keys, (9,110): scan_gather_kernel 54 us; now 29 us for 87 MB.  While a wavefront asked for the first words of a block
+// after the last of the block before: 32 heads x 98304 keys, (10,300), the step 105.3 us, now 81.1; 64 heads of 32 KV heads
+// x 30000, (10,120), 79.5, now 71.7.)
+// `ahead` holds the first words of the block (request_any); with `more` those of the block behind it are
+// requested as its places become free, so that a wavefront that takes several never waits for a first word.
 template <int GT, bool DBG, class Emit>
-__device__ inline void scan_block_any(const AttnArgs& a, const Ctx& c, int unit, int64_t blk, int lane, int h_begin, int G, Emit emit) {
-  typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline void scan_block_any(const AttnArgs& a, const Ctx& c, int unit, int64_t blk, int lane, int h_begin, int G,
+                                      AnyWords<GT>& ahead, bool more, Emit emit) {
+  constexpr int kAhead = kAnyAhead<GT>;
   const int K = a.K, NW = a.NW, NQ = a.NQ;
   const int xs = tail_begin(K, a.L), Lt = tail_tables(a.L);
-  const int full = NW >> 2, rem = NW & 3, groups = (NW + 3) >> 2;
+  const int full = NW >> 2, rem = NW & 3;
   const int64_t head0 = (int64_t)(unit / a.Hkv) * a.Hq + (int64_t)(unit % a.Hkv) * (a.Hq / a.Hkv) + h_begin;
   const uint32_t* blkp = a.kcodes + ((int64_t)unit * a.blocks_cap + blk) * (kBlockKeys * (int64_t)NW);
   // (wave-uniform and constant during the kernel: scalar loads, see scan_blocks)
@@ -251,16 +287,6 @@ __device__ inline void scan_block_any(const AttnArgs& a, const Ctx& c, int unit,
   for (int h = 0; h < GT; ++h) { diff[h] = 0u; cnt[h] = 0u; }
   uint64_t acc = 0;                                      // the last group's bit string: bits not taken yet
   int have = 0, plane = 0;                               // how many, and the plane of the group that comes next
-  auto load = [&](int g, u32x4& v) {
-    if (g < full) {
-      v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(blkp + g * 256) + lane);
-    } else if (g == full) {
-      const uint32_t* p = blkp + full * 256 + lane * rem;
-      if (rem > 0) v.x = __builtin_nontemporal_load(p);
-      if (rem > 1) v.y = __builtin_nontemporal_load(p + 1);
-      if (rem > 2) v.z = __builtin_nontemporal_load(p + 2);
-    }
-  };
   auto flush = [&]() {
     plane = 0;
 #pragma unroll
@@ -284,19 +310,15 @@ __device__ inline void scan_block_any(const AttnArgs& a, const Ctx& c, int unit,
       }
     }
   };
-  u32x4 v[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[i] = (u32x4)(0u);
-    load(i, v[i]);
-  }
+  const uint32_t* next = blkp + kBlockKeys * (int64_t)NW;
 #pragma unroll 1
-  for (int g = 0; g < groups; g += 4) {
+  for (int g = 0; g < full; g += kAhead) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (g + i >= groups) break;
-      const u32x4 cur = v[i];
-      load(g + i + 4, v[i]);
+    for (int i = 0; i < kAhead; ++i) {
+      if (g + i >= full) break;
+      const CodeWords cur = ahead.group[i];
+      const bool here = g + i + kAhead < full;
+      if (here || more) ahead.group[i] = load_group(here ? blkp : next, lane, here ? g + i + kAhead : i);
       const int x0 = 4 * (g + i);
       if (x0 + 4 <= xs) {                                // four planes: the queries' words in one go
         const uint32_t w4[4] = {cur.x, cur.y, cur.z, cur.w};
@@ -319,6 +341,10 @@ __device__ inline void scan_block_any(const AttnArgs& a, const Ctx& c, int unit,
       }
     }
   }
+#pragma unroll
+  for (int i = 0; i < 3; ++i)
+    if (i < rem) consume(4 * full + i, ahead.rest[i]);
+  if (more) load_rest(next, lane, full, rem, ahead);
   const uint32_t real = Lt >= 32 ? ~0u : (1u << Lt) - 1u;
   const uint64_t eligible = eligible_keys(a, c, blk, lane);
 #pragma unroll

@@ -21,7 +21,7 @@
 // A chain of latencies, so all 64 elements of a lane's column are requested at once, together with the keys, which
 // wait in LDS (16 at a time, the next ones requested while those before them are multiplied, cost a round trip to
 // L2 each).  4096 keys x 600 columns (one head, (8,75)): 24.6 us with four wavefronts, two tiles each and the
-// keys in registers, 19.3 now.  8 x 2048 keys x 1500 columns: the call 115 us, 102 now (6.7 GFLOP: 43 us at the rate of the
+// keys in registers, 19.3 now.  8 x 2048 keys x 1500 columns: mean and codes 120 us, 108 now (6.7 GFLOP: 43 us at the rate of the
 // instruction).
 #include "mp_common.h"
 #include "exact_dot.h"

@@ -740,8 +740,11 @@ __global__ __launch_bounds__(1024) void lookup_gather_kernel(AttnArgs a, TableAr
   if (slice < a.lg_app_runs && app_blk < key_blocks(cx.n)) {
     const int hg = (int)(bh % a.Hq) % G;
     auto emit = [&](int, int64_t, uint64_t m) { app_mask = m; };
-    if constexpr (KT == 0) scan_block_any<1, true>(a, cx, unit, app_blk, lane, hg, 1, emit);
-    else scan_blocks<KT, WDT, LT, 1, true>(a, cx, unit, app_blk, lane, hg, hg + 1, emit);
+    if constexpr (KT == 0) {
+      AnyWords<1> ahead;
+      request_any(a, unit, app_blk, lane, ahead);
+      scan_block_any<1, true>(a, cx, unit, app_blk, lane, hg, 1, ahead, false, emit);
+    } else scan_blocks<KT, WDT, LT, 1, true>(a, cx, unit, app_blk, lane, hg, hg + 1, emit);
   }
   if (tid < a.NQ) qs[tid] = qword;
   __syncthreads();

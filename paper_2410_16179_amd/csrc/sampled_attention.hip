@@ -58,8 +58,11 @@ __global__ __launch_bounds__(256) void collision_scan_kernel(AttnArgs a) {
   // grid layer z compares with its share of the heads
   const int per = (G + gridDim.z - 1) / gridDim.z, h0 = blockIdx.z * per, h1 = h0 + per < G ? h0 + per : G;
   if (h0 >= h1) return;
-  if constexpr (KT == 0) scan_block_any<WDT, true>(a, c, unit, blk0, lane, h0, h1 - h0, emit);
-  else scan_blocks<KT, WDT, LT, BPW, true>(a, c, unit, blk0, lane, h0, h1, emit);
+  if constexpr (KT == 0) {
+    AnyWords<WDT> ahead;
+    request_any(a, unit, blk0, lane, ahead);
+    scan_block_any<WDT, true>(a, c, unit, blk0, lane, h0, h1 - h0, ahead, false, emit);
+  } else scan_blocks<KT, WDT, LT, BPW, true>(a, c, unit, blk0, lane, h0, h1, emit);
 }
 
 // rows per quarter wavefront and batch of the stand-alone gather: 32 K and 32 V rows in flight
@@ -186,6 +189,9 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   const int64_t blk0 = (int64_t)run * run_blocks;
   int found = 0;                                           // lane h: keys of head h found so far by this wavefront
   uint64_t last_found = 0;                                 // keys of the wavefront's last block that some head samples
+  AnyWords<KT == 0 ? WDT : 1> ahead;                       // (any K and L only)
+  if constexpr (KT == 0)
+    if (blk0 + wave * wave_blocks < nblk) request_any(a, unit, blk0 + wave * wave_blocks, lane, ahead);
 #pragma unroll 1
   for (int j = 0; j < wave_blocks; ++j) {
     const int bi = wave * wave_blocks + j;
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
         }
         if (j == wave_blocks - 1) last_found |= m;
       };
-      if constexpr (KT == 0) scan_block_any<WDT, DBG>(a, c, unit, blk0 + bi, lane, 0, G, emit);
+      if constexpr (KT == 0) scan_block_any<WDT, DBG>(a, c, unit, blk0 + bi, lane, 0, G, ahead, j + 1 < wave_blocks && blk0 + bi + 1 < nblk, emit);
       else scan_blocks<KT, WDT, LT, 1, DBG>(a, c, unit, blk0 + bi, lane, 0, G, emit);
     }
   }
