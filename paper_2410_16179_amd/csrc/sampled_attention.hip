@@ -437,11 +437,12 @@ static void launch_scan_gather_for(const AttnArgs& a, dim3 grid, hipStream_t s, 
 
 // Key blocks of a gather wavefront, in pieces of kRangeBlocks.  A wavefront that takes several pieces fills its
 // batches of rows (a piece samples about 20 keys of a batch's 32 at 2 %), asks for the next piece's ballots early
-// and leaves one partial; but ten wavefronts per compute unit have to remain.  Measured (us per step through
-// tables, pieces 1 | 2 | 3 | 4 | 8): 512 heads x 131072 keys, (10,170), - | 181 | - | 166.5 |
+// and leaves one partial: as many pieces as bring all wavefronts into one round, sixteen per compute unit.
+// Measured (us per step through tables, pieces 1 | 2 | 3 | 4 | 8): 512 heads x 131072 keys, (10,170), - | 181 | - | 166.5 |
 // 161.8 (16: 162.5); (10,150): 512 x 32768 62.9 | 59.6 | 59.3 | 58.2 | 58.0; 128 x 65536
-// 43.6 | 42.4 | 42.5 | 43.1 | 47.4; 64 x 98304 42.4 | 40.6 | 39.2 | 40.6 | 48.6; 256 x 20000, (9,120), 46.0 | 45.6 | 45.5 | 49.5 | 60.8.
-constexpr int64_t kGatherWaves = 10 * kNumCU;
+// 43.6 | 42.4 | 42.5 | 43.1 | 47.4; 64 x 98304 42.4 | 40.6 | 39.2 | 40.6 | 48.6; 256 x 20000, (9,120), 46.0 | 45.6 | 45.5 | 49.5 |
+// 60.8; 512 x 30000, (9,100), six pieces (five runs, 1.25 workgroups per compute unit) 86.6, four 78.0.
+constexpr int64_t kGatherWaves = 16 * kNumCU;
 constexpr int64_t kMaxGatherPieces = 8;
 
 static hipError_t launch_scan_gather(const AttnArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
@@ -509,7 +510,7 @@ hipError_t launch_sampled_attention(const AttnArgs& a, const TableArgs* tables, 
   }
   AttnArgs b = a;                                          // (no more partials than a.nranges, for which there is room)
   const int64_t nblk = key_blocks(a.n);
-  int64_t pieces = heads * ((nblk + kRangeBlocks - 1) / kRangeBlocks) / kGatherWaves;
+  int64_t pieces = (heads * ((nblk + kRangeBlocks - 1) / kRangeBlocks) + kGatherWaves - 1) / kGatherWaves;
   pieces = pieces < 1 ? 1 : (pieces > kMaxGatherPieces ? kMaxGatherPieces : pieces);
   b.g_run_blocks = (int)pieces * kRangeBlocks;
   b.nranges = (int)((nblk + b.g_run_blocks - 1) / b.g_run_blocks);
