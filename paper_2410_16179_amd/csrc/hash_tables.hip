@@ -26,6 +26,7 @@
 //       keys were appended than the one-launch form takes.
 #include "attention_common.h"
 #include <hip/hip_ext.h>
+#include <type_traits>
 
 namespace mp {
 
@@ -231,7 +232,8 @@ __device__ inline void ht_count_blocks(const TableArgs& a, uint32_t* hist, int u
     for (int e = 0; e < 2; ++e)
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        pk[e][i] = __builtin_amdgcn_perm(i + 8 < K ? raw[e][(i + 8) % (4 * kGroups)] : 0u, i < K ? raw[e][i % (4 * kGroups)] : 0u, pick);
+        // (plane b as bit b + 2: the codes come out times four, byte offsets of the counters)
+        pk[e][i] = __builtin_amdgcn_perm(i + 6 < K ? raw[e][(i + 6) % (4 * kGroups)] : 0u, i >= 2 && i - 2 < K ? raw[e][(i + 4 * kGroups - 2) % (4 * kGroups)] : 0u, pick);
     planes_to_codes(pk[0]);
     planes_to_codes(pk[1]);
     if constexpr (T < 16) {                              // the T/2 words of this workgroup to the front
@@ -250,17 +252,18 @@ __device__ inline void ht_count_blocks(const TableArgs& a, uint32_t* hist, int u
     asm volatile("" : "+s"(left));
 #pragma unroll
     for (int j = 0; j < T / 2; ++j) {
+      const uint32_t c0 = pk[0][j], c1 = pk[1][j];
       if (j < left) {
-        uint32_t* h = hist + 2 * j * nb;
-        if (real0) atomicAdd(&h[pk[0][j] & 0xffffu], 1u);
-        if (real1) atomicAdd(&h[pk[1][j] & 0xffffu], 1u);
-        if (on) *reinterpret_cast<uint32_t*>(o) = __builtin_amdgcn_perm(pk[1][j], pk[0][j], 0x05040100u);
+        char* h = reinterpret_cast<char*>(hist + 2 * j * nb);
+        if (real0) atomicAdd(reinterpret_cast<uint32_t*>(h + (c0 & 0xffffu)), 1u);
+        if (real1) atomicAdd(reinterpret_cast<uint32_t*>(h + (c1 & 0xffffu)), 1u);
+        if (on) *reinterpret_cast<uint32_t*>(o) = __builtin_amdgcn_perm(c1, c0, 0x05040100u);
       }
       if (j + 8 < left) {
-        uint32_t* h = hist + (2 * j + 1) * nb;
-        if (real0) atomicAdd(&h[pk[0][j] >> 16], 1u);
-        if (real1) atomicAdd(&h[pk[1][j] >> 16], 1u);
-        if (on) *reinterpret_cast<uint32_t*>(o + 8 * row) = __builtin_amdgcn_perm(pk[1][j], pk[0][j], 0x07060302u);
+        char* h = reinterpret_cast<char*>(hist + (2 * j + 1) * nb);
+        if (real0) atomicAdd(reinterpret_cast<uint32_t*>(h + (c0 >> 16)), 1u);
+        if (real1) atomicAdd(reinterpret_cast<uint32_t*>(h + (c1 >> 16)), 1u);
+        if (on) *reinterpret_cast<uint32_t*>(o + 8 * row) = __builtin_amdgcn_perm(c1, c0, 0x07060302u);
       }
       o += row;
     }
@@ -366,10 +369,10 @@ __global__ __launch_bounds__(256) void ht_offsets_kernel(TableArgs a) {
 __global__ __launch_bounds__(1024, 8) void ht_place_kernel(TableArgs a) {
   extern __shared__ uint32_t lds[];
   const int nb = 1 << a.K;
-  uint32_t* cursor = lds;                                              // [2^K] next free slot of the bucket's piece
+  uint32_t* cursor = lds;                                              // [2^K] byte offset in `sorted` of the next free slot of the bucket's piece
   uint32_t* delta = lds + nb;                                          // [2^K] place in the index array - place in `sorted`
-  uint32_t* sorted = delta + nb;                                       // [kBuildWindow] bucket << 14 | key inside the window
-  static_assert(kBuildWindow == 1 << 14, "an entry holds 14 bits of key and up to 12 bits of bucket");
+  uint32_t* sorted = delta + nb;                                       // [kBuildWindow] bucket << 16 | key inside the window
+  static_assert(kBuildWindow == 1 << 14, "above 14 bits of key and two of zero an entry >> 14 is four times its bucket");
   __shared__ uint32_t wsum[16];
   const uint32_t id = linear_workgroup();
   const int win = (int)((id >> 3) % (uint32_t)a.windows);
@@ -419,37 +422,48 @@ __global__ __launch_bounds__(1024, 8) void ht_place_kernel(TableArgs a) {
   for (int j = 0; j < 4; ++j) {
     const int c = tid * per + j;
     if (j < per && c < nb) {
-      cursor[c] = at;
+      cursor[c] = 4 * at;
       delta[c] = base_c[j] - at;
       at += n_c[j];
     }
   }
   __syncthreads();
-  // counting sort of the window's keys
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    const int kb = (h * 1024 + tid) * 8;
-    const uint32_t u[4] = {raw[h].x, raw[h].y, raw[h].z, raw[h].w};
-    uint32_t pos[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t code = (u[e >> 1] >> (16 * (e & 1))) & 0xffffu;
-      if (kb + e < m) pos[e] = atomicAdd(&cursor[code], 1u);
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const uint32_t code = (u[e >> 1] >> (16 * (e & 1))) & 0xffffu;
-      if (kb + e < m) sorted[pos[e]] = (code << 14) | (uint32_t)(kb + e);
-    }
-  }
-  __syncthreads();
-  // copy out
+  // counting sort of the window's keys, and the sorted window copied out; whole windows need no masks
   uint32_t* idxs = a.indices + ut * a.n_cap;
+  auto place = [&](auto whole) {
+    constexpr bool kWhole = decltype(whole)::value;
+    char* cur = reinterpret_cast<char*>(cursor);
+    char* out = reinterpret_cast<char*>(sorted);
+    const char* del = reinterpret_cast<const char*>(delta);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int kb = (h * 1024 + tid) * 8;
+      const uint32_t u[4] = {raw[h].x, raw[h].y, raw[h].z, raw[h].w};
+      uint32_t code4[8], pos4[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        code4[e] = (e & 1) ? u[e >> 1] >> 16 : u[e >> 1] & 0xffffu;
+        if (kWhole || kb + e < m) pos4[e] = atomicAdd(reinterpret_cast<uint32_t*>(cur + code4[e]), 4u);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        if (kWhole || kb + e < m) *reinterpret_cast<uint32_t*>(out + pos4[e]) = (code4[e] << 14) | (uint32_t)(kb + e);
+    }
+    __syncthreads();
+    auto copy = [&](int i) {
+      const uint32_t e = sorted[i];
+      idxs[*reinterpret_cast<const uint32_t*>(del + (e >> 14)) + (uint32_t)i] = (uint32_t)k0 | (e & (kBuildWindow - 1));
+    };
+    if constexpr (kWhole) {
+#pragma unroll
+      for (int i = 0; i < kBuildWindow / 1024; ++i) copy(i * 1024 + tid);
+    } else {
 #pragma unroll 4
-  for (int i = tid; i < m; i += 1024) {
-    const uint32_t e = sorted[i];
-    idxs[delta[e >> 14] + (uint32_t)i] = (uint32_t)k0 + (e & (kBuildWindow - 1));
-  }
+      for (int i = tid; i < m; i += 1024) copy(i);
+    }
+  };
+  if (m == kBuildWindow) place(std::true_type{});
+  else place(std::false_type{});
 }
 
 template <int BITS>
