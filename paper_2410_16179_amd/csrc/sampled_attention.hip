@@ -165,9 +165,10 @@ template <int KT, int HT> constexpr int kScanParts = KT == 0 && HT == 1 ? 2 : 1;
 // they cost neither workgroups nor batches nor partials of their own.
 // One partial per (head, run); where two wavefronts share a head's keys (kScanParts) they join theirs in LDS.
 // DBG: with the debug outputs (counts, candidate lists).
+// ONE: a workgroup (grid layer z) serves one of the G heads (few keys, see launch_scan_gather_as).
 // KT, WDT, LT: see scan_blocks; KT = 0: any K and L, WDT = the heads scan_block_any is laid out for.
 // ET: element type of the caches (kBF16, kFP32, or kFP8 with bf16 queries).
-template <int KT, int WDT, int LT, int ET, bool DBG, int OCC>
+template <int KT, int WDT, int LT, int ET, bool DBG, int OCC, bool ONE = false>
 __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   constexpr bool FP32 = ET == kFP32;
   constexpr int kIt = FP32 ? (kFusedIters + 1) / 2 : kFusedIters;   // the same registers per batch
@@ -175,14 +176,16 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   // seg[h][w]: the keys of the run that head h samples among the blocks of wavefront w, in key
   // order (position in the run, 11 bits); seg_n[h][w]: how many.  Written while the blocks are
   // compared, so that nothing but the row gather is left to do after the last block.
-  __shared__ uint16_t seg[8][4][kSeg];
-  __shared__ int seg_n[8][4];
+  constexpr int kHeads = ONE ? 1 : 8;
+  __shared__ uint16_t seg[kHeads][4][kSeg];
+  __shared__ int seg_n[kHeads][4];
   const Ctx c = resolve_context(a);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int unit = blockIdx.y, run = blockIdx.x;
   const int nruns = gridDim.x;                             // = f_nranges
   const int G = a.Hq / a.Hkv;
   const int64_t head0 = (int64_t)(unit / a.Hkv) * a.Hq + (int64_t)(unit % a.Hkv) * G;
+  const int h0 = ONE ? blockIdx.z : 0, h1 = ONE ? h0 + 1 : G;   // heads of this workgroup
   const int64_t nblk = key_blocks(c.n);
   const int wave_blocks = a.f_wave_blocks;                 // 1 .. kFusedWaveBlocks key blocks per wavefront
   const int run_blocks = 4 * wave_blocks;
@@ -198,18 +201,18 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
     if (blk0 + bi < nblk) {
       auto emit = [&](int h, int64_t, uint64_t m) {
         if (m) {                                           // (wave-uniform)
-          const int at = __builtin_amdgcn_readlane(found, h);
+          const int at = __builtin_amdgcn_readlane(found, h - h0);
           const int below = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-          if ((m >> lane) & 1) seg[h][wave][at + below] = (uint16_t)(bi * kBlockKeys + lane);
-          if (lane == h) found = at + __popcll(m);
+          if ((m >> lane) & 1) seg[h - h0][wave][at + below] = (uint16_t)(bi * kBlockKeys + lane);
+          if (lane == h - h0) found = at + __popcll(m);
         }
         if (j == wave_blocks - 1) last_found |= m;
       };
-      if constexpr (KT == 0) scan_block_any<WDT, DBG>(a, c, unit, blk0 + bi, lane, 0, G, ahead, j + 1 < wave_blocks && blk0 + bi + 1 < nblk, emit);
-      else scan_blocks<KT, WDT, LT, 1, DBG>(a, c, unit, blk0 + bi, lane, 0, G, emit);
+      if constexpr (KT == 0) scan_block_any<WDT, DBG>(a, c, unit, blk0 + bi, lane, h0, h1 - h0, ahead, j + 1 < wave_blocks && blk0 + bi + 1 < nblk, emit);
+      else scan_blocks<KT, WDT, LT, 1, DBG>(a, c, unit, blk0 + bi, lane, h0, h1, emit);
     }
   }
-  if (lane < G) seg_n[lane][wave] = found;
+  if (lane < h1 - h0) seg_n[lane][wave] = found;
   // The gather reads its arguments from the kernel argument segment again, through a pointer the
   // compiler cannot trace back: otherwise it loads them all at the start of the kernel and keeps
   // them in scalar registers across the scan, whose query words then no longer fit (50 spills,
@@ -255,17 +258,17 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  constexpr int parts = kScanParts<KT, WDT>;
+  constexpr int parts = ONE ? 1 : kScanParts<KT, WDT>;    // (ONE: the same sums as a workgroup for G heads)
   auto attend = [&](int h, int part) {                     // share `part` of the keys of head h
     HeadVectors<FP32> hv;
     request_head_vectors<FP32>(ga, unit, head0 + h, hv);
     // the four wavefronts' keys of head h, one after the other: candidate cc is entry cc - s_w of
     // the last wavefront w whose first candidate s_w is not beyond cc
-    const int s1 = __builtin_amdgcn_readfirstlane(seg_n[h][0]);
-    const int s2 = s1 + __builtin_amdgcn_readfirstlane(seg_n[h][1]);
-    const int s3 = s2 + __builtin_amdgcn_readfirstlane(seg_n[h][2]);
-    const int total = s3 + __builtin_amdgcn_readfirstlane(seg_n[h][3]);
-    const uint16_t* segh = &seg[h][0][0];
+    const int s1 = __builtin_amdgcn_readfirstlane(seg_n[h - h0][0]);
+    const int s2 = s1 + __builtin_amdgcn_readfirstlane(seg_n[h - h0][1]);
+    const int s3 = s2 + __builtin_amdgcn_readfirstlane(seg_n[h - h0][2]);
+    const int total = s3 + __builtin_amdgcn_readfirstlane(seg_n[h - h0][3]);
+    const uint16_t* segh = &seg[h - h0][0][0];
     // static keys run, run + nruns, ... ride along behind the sampled ones
     const int all = total + static_share(c, run, nruns);
     // this wavefront's share: candidates lo .. lo + mine - 1
@@ -281,16 +284,16 @@ __global__ __launch_bounds__(256, OCC) void scan_gather_kernel(AttnArgs a) {
   };
   auto place = [&](int h) { return ga.partial + ((head0 + h) * ga.f_nranges + run) * kPartialStride; };
   if constexpr (parts == 1) {
-    for (int h = wave; h < G; h += 4) store_partial(attend(h, 0), place(h));
+    for (int h = h0 + wave; h < h1; h += 4) store_partial(attend(h, 0), place(h));
   } else {                                                 // one head
     __shared__ float joined[kPartialStride];
     WavePartial wp;
-    if (wave < parts) wp = attend(0, wave);
+    if (wave < parts) wp = attend(h0, wave);
     if (wave == 1) store_partial(wp, joined);
     __syncthreads();
     if (wave == 0) {
       join_partial(wp, joined);
-      store_partial(wp, place(0));
+      store_partial(wp, place(h0));
     }
   }
 #pragma unroll
@@ -415,8 +418,18 @@ template <int KT, int WDT, int LT, int ET, bool DBG>
 static void launch_scan_gather_as(const AttnArgs& a, dim3 grid, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 block(256);
   // (any K and L: 127 registers, four workgroups fit either way)
-  if (KT == 0 || a.f_touch) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 4>, grid, block, s, start, stop, a);
-  else if constexpr (KT != 0) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 3>, grid, block, s, start, stop, a);
+  constexpr int kOcc = KT == 0 ? 4 : 3;
+  const unsigned G = (unsigned)(a.Hq / a.Hkv);
+  // A workgroup for every head where few workgroups share the chip: a wavefront then compares its blocks with one
+  // head's code, not with G one after the other, and gathers for one head (of five to eight heads a wavefront
+  // gathers for two).  Measured, us per step, G heads a workgroup | one (workgroups of one head): 8 KV heads, G = 4: 2048 keys 18.96 | 16.65
+  // (256), 6144 18.3 | 17.5 (768), 10000 19.8 | 21.1 (1280); G = 8: 4000 25.3 | 20.65 (1024), 8000 25.2 | 26.0 (2048); G = 3: 10000
+  // 19.2 | 20.0 (960), 5000 18.65 | 17.9 (480); G = 2: 4096 17.9 | 16.8 (256); any K and L: G = 8, 2048 keys 27.5 | 20.7 (512), G = 4, 4096 20.8 | 19.5 (512).
+  const int64_t most = G > 4 ? 4 * kNumCU : (G == 4 ? 3 * kNumCU : 2 * kNumCU);
+  if (!DBG && G > 1 && (int64_t)grid.x * grid.y * G <= most)
+    launch_timed(scan_gather_kernel<KT, KT == 0 ? 1 : WDT, LT, ET, false, kOcc, true>, dim3(grid.x, grid.y, G), block, s, start, stop, a);
+  else if (KT == 0 || a.f_touch) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 4>, grid, block, s, start, stop, a);
+  else launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, kOcc>, grid, block, s, start, stop, a);
 }
 
 template <int KT, int WDT, int LT>
