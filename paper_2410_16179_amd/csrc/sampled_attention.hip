@@ -20,8 +20,7 @@
 //   One wavefront per (query head, run of key blocks): the sampled keys are an index list in
 //   LDS (gather_estimate_kernel expands the ballots by a wavefront prefix sum; scan_gather_kernel
 //   appends to the list while it compares); the static sink and local-window keys ride
-//   along in these batches, or, in gather_estimate_kernel, are taken 32 each by wavefronts of
-//   their own; rows are gathered four at a time (a quarter wavefront holds one 128-element row)
+//   along in these batches; rows are gathered four at a time (a quarter wavefront holds one 128-element row)
 //   with up to 32 K rows and 32 V rows in flight; q.k, q.(k-mu), |k-mu|^2 are reduced over
 //   the 16 lanes of a row, the inclusion probability u_i and the logit q.k/sqrt(d) - log u_i
 //   are evaluated once per candidate, and an online max/sum softmax accumulates the weighted
