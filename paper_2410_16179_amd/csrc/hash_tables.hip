@@ -10,7 +10,7 @@
 //   the workspace; keys per bucket and window of 16384 keys), ht_offsets_kernel (fill levels of the
 //   buckets at the start of every window, bucket offsets) and ht_place_kernel (one window of one
 //   table per workgroup, sorted in LDS and copied out).  8 KV heads x 98304 keys at (10,150): 105 +
-//   14 + 160 us, against 1806 + 455 us of the first version (one workgroup per (unit, 16 tables)
+//   14 + 166 us, against 1806 + 455 us of the first version (one workgroup per (unit, 16 tables)
 //   walking every window, and a wavefront per piece in the copy).
 //   Without it, ht_build_kernel<false>: histogram of the codes of 32 (or fewer) tables in LDS ->
 //   offsets; ht_build_kernel<true>: second pass, scatters key indices to their buckets (every 4-byte
@@ -363,9 +363,9 @@ __global__ __launch_bounds__(256) void ht_offsets_kernel(TableArgs a) {
 // bucket c goes to i + (first place of the bucket's piece in the index array - its place in the
 // sorted window).  Pieces are about 16 entries, so a wavefront store covers four or five of them; the
 // first version gave a wavefront one piece at a time (a quarter of the lanes at work, 455 us at 8 KV
-// heads x 98304 keys, (10,150); then 176 us with 24 vector instructions
-// per key; now 160 us, 18 per key and no masks in whole windows, for 790 MB read and written, 4.9 TB/s, the rate of a
-// large copy).  Two workgroups per compute unit (72 KB of LDS each at K = 10); the windows of a
+// heads x 98304 keys, (10,150); then 176 to 182 us with 24 vector
+// instructions per key; now 158 to 166 us, 18 per key and no masks in whole windows, for 790 MB read and written, 4.8 TB/s,
+// about the rate of a large copy).  Two workgroups per compute unit (72 KB of LDS each at K = 10); the windows of a
 // table run on one XCD, whose L2 joins the pieces of neighbouring windows into whole lines.
 __global__ __launch_bounds__(1024, 8) void ht_place_kernel(TableArgs a) {
   extern __shared__ uint32_t lds[];
