@@ -43,7 +43,9 @@ static size_t hash_f32_lds(int K, int keys) {
 template <int KT>
 __global__ __launch_bounds__(1024, 4) void hash_keys_f32_kernel(HashDirectArgs a, uint32_t tiles, uint32_t jobs) {
   constexpr int kTileKeys = 32 * KT;                      // keys of a workgroup
-  extern __shared__ long long lds[];
+  extern __shared__ __attribute__((aligned(16))) long long lds[];
+  // (the keys are written and read 16 bytes at a time: every row of them begins on such a boundary)
+  static_assert(kLimbs * sizeof(long long) % 16 == 0 && kKeyRow * sizeof(float) % 16 == 0, "");
   __shared__ uint32_t colbits[16][kTileKeys];             // [32-column tile][key]: sign bits in column order
   __shared__ uint32_t plane[16][kTileKeys];               // last table group: its plane words
   __shared__ float norms[kTileKeys];
