@@ -66,6 +66,8 @@ __global__ __launch_bounds__(256) void collision_scan_kernel(AttnArgs a) {
 
 // rows per quarter wavefront and batch of the stand-alone gather: 32 K and 32 V rows in flight
 template <int ET> constexpr int kGatherIters = ET == kFP32 ? 4 : 8;
+// entries of a wavefront's index list: fewer than a batch left over, and all keys of a piece
+template <int ET> constexpr int kGatherList = kRangeBlocks * kBlockKeys + 4 * kGatherIters<ET>;
 
 // One wavefront = one (query head, run of g_run_blocks key blocks).  blockDim = 64 * G:
 // the G wavefronts of a workgroup serve the G heads of one KV head on the same run.  The ballots of
@@ -76,12 +78,14 @@ template <int ET> constexpr int kGatherIters = ET == kFP32 ? 4 : 8;
 // million rows: 152 us (643 MB at 4.2 TB/s, vector unit 73 % busy) with a wavefront for each 1024 keys, about 20 of the 32
 // rows of a batch and workgroups of their own for T; now 122 us (5.3 TB/s): the estimator's arithmetic, once per
 // batch, serves 32 rows, full batches need no masks, and the 16-lane sums of a batch are taken together.
-// Four wavefronts per SIMD (128 registers; at 141, three, it was 40 % slower).
+// Four wavefronts per SIMD (128 registers; at 141, three, it was 40 % slower); the lists are as many as the workgroup has
+// wavefronts, so that sixteen fit a compute unit with few heads too (room for eight lists in a workgroup of one
+// wavefront: nine fitted; 512 heads of 512 KV heads x 16384 keys, (10,150), the step 40.3 us, now 36.6).
 template <int ET>
 __global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
   constexpr bool FP32 = ET == kFP32;
   constexpr int kIt = kGatherIters<ET>, kBatch = 4 * kIt;
-  __shared__ uint16_t lists[8][kRangeBlocks * kBlockKeys + kBatch];
+  extern __shared__ uint16_t lists[];                      // [heads of the workgroup][kGatherList<ET>]
   const Ctx c = resolve_context(a);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int unit = blockIdx.y, run = blockIdx.x;
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
   const int64_t bh = (int64_t)b * a.Hq + (int64_t)g * G + wave;
   const int64_t nblk = key_blocks(c.n);
   const int64_t blk0 = (int64_t)run * a.g_run_blocks;
-  uint16_t* list = lists[wave];
+  uint16_t* list = lists + wave * kGatherList<ET>;
   HeadVectors<FP32> hv;
   request_head_vectors<FP32>(a, unit, bh, hv);
   const int nruns = gridDim.x, nst = static_share(c, run, nruns);
@@ -369,9 +373,13 @@ __global__ void zero_output_kernel(float* out, int64_t count) {
 // Ordinary launch, or - when events are given - a launch whose events carry the kernel's own
 // begin / end timestamps (what a profiler reports), not the stream's dispatch times.
 template <class F, class... Args>
+static void launch_timed_lds(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_t s, hipEvent_t start, hipEvent_t stop, Args... args) {
+  if (start || stop) hipExtLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, s, start, stop, 0, args...);
+  else hipLaunchKernelGGL(kernel, grid, block, lds, s, args...);
+}
+template <class F, class... Args>
 static void launch_timed(F kernel, dim3 grid, dim3 block, hipStream_t s, hipEvent_t start, hipEvent_t stop, Args... args) {
-  if (start || stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, start, stop, 0, args...);
-  else hipLaunchKernelGGL(kernel, grid, block, 0, s, args...);
+  launch_timed_lds(kernel, grid, block, 0, s, start, stop, args...);
 }
 
 static hipError_t launch_scan(const AttnArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
@@ -527,9 +535,12 @@ hipError_t launch_sampled_attention(const AttnArgs& a, const TableArgs* tables, 
   b.g_run_blocks = (int)pieces * kRangeBlocks;
   b.nranges = (int)((nblk + b.g_run_blocks - 1) / b.g_run_blocks);
   const dim3 grid((unsigned)b.nranges, (unsigned)(a.B * a.Hkv)), block(64 * (a.Hq / a.Hkv));
-  if (a.is_fp32) launch_timed(gather_estimate_kernel<kFP32>, grid, block, s, nullptr, ev ? ev[2] : nullptr, b);
-  else if (a.kv_fp8) launch_timed(gather_estimate_kernel<kFP8>, grid, block, s, nullptr, ev ? ev[2] : nullptr, b);
-  else launch_timed(gather_estimate_kernel<kBF16>, grid, block, s, nullptr, ev ? ev[2] : nullptr, b);
+  auto gather = [&](auto kernel, int list) {
+    launch_timed_lds(kernel, grid, block, (size_t)(a.Hq / a.Hkv) * list * sizeof(uint16_t), s, nullptr, ev ? ev[2] : nullptr, b);
+  };
+  if (a.is_fp32) gather(gather_estimate_kernel<kFP32>, kGatherList<kFP32>);
+  else if (a.kv_fp8) gather(gather_estimate_kernel<kFP8>, kGatherList<kFP8>);
+  else gather(gather_estimate_kernel<kBF16>, kGatherList<kBF16>);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_merge(b, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr);
 }
