@@ -125,8 +125,8 @@ AttnWs ws_attention_layout(const magicpig_params* p) {
   const size_t heads = (size_t)p->batch * p->n_q_heads;
   const int64_t st = (int64_t)p->n_sink + p->n_local;
   w.n_static = st < p->n_ctx ? st : p->n_ctx;
-  // room for the separate gather (which takes one partial per run of kRangeBlocks key blocks or more): one for every
-  // kRangeBlocks key blocks, and one for every 32 static keys
+  // room for the separate gather (one partial per run of kRangeBlocks key blocks or more, and per wavefront of 32
+  // static keys or more): one for every kRangeBlocks key blocks, and one for every 32 static keys
   w.nranges = (int)((nblk + mp::kRangeBlocks - 1) / mp::kRangeBlocks + (w.n_static + 31) / 32);
   // lookup + gather in one launch: 16 partials per slice
   const int lg = (int)((nblk + mp::kLgSliceBlocks - 1) / mp::kLgSliceBlocks) * 16;

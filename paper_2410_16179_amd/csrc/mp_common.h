@@ -4,12 +4,12 @@
 #include <stdint.h>
 #include <stddef.h>
 #include "magicpig.h"
+#include "launch_plan.h"
 
 namespace mp {
 
 constexpr int kHeadDim = 128;
 constexpr int kBlockKeys = 64;   // keys per code block = lanes per wavefront
-constexpr int kNumCU = 256;      // MI355X
 
 // ---- packed code layout (documented in magicpig.h) ----
 // Plane word w*K + b holds sign bit b of tables 32w .. 32w+31.  Query codes are stored as
@@ -219,7 +219,9 @@ struct AttnArgs {
   // 4 * f_wave_blocks key blocks (f_wave_blocks: key blocks per wavefront, 1 .. kFusedWaveBlocks)
   int f_nranges, f_wave_blocks;
   int f_touch;               // 1: more than three workgroups per compute unit (wavefronts touch the rows of the keys of their last block)
-  int g_run_blocks;          // the separate gather: key blocks per wavefront, a multiple of kRangeBlocks
+  // the separate gather: key blocks per wavefront, a multiple of kRangeBlocks, wavefronts behind those of a head
+  // that take its static keys (0: the static keys are dealt over the others), and static keys of each
+  int g_run_blocks, g_static_runs, g_static_keys;
   // lookup + gather in one launch: slices of the indexed range; the first lg_app_runs of them
   // also take a run of 16 appended key blocks each
   int lg_nslices, lg_app_runs;
@@ -247,7 +249,6 @@ struct TableArgs {
 constexpr int kBuildWindow = 16384;   // keys one workgroup places into the buckets of one table
 
 constexpr int kPartialStride = 132;   // 128 output elements, running max, running sum, pad
-constexpr int kRangeBlocks = 16;      // key blocks whose ballots a gather wavefront expands at a time (1024 keys)
 constexpr int kLgWaveBlocks = 16;     // lookup + gather in one launch: key blocks per wavefront,
 constexpr int kLgSliceBlocks = 16 * kLgWaveBlocks;   // and per workgroup (16 wavefronts): one build window
 static_assert(kLgSliceBlocks * kBlockKeys == kBuildWindow, "a lookup slice is a window of the table build");

@@ -32,6 +32,7 @@
 //   Sec. 4.4) and writes the output row.
 #include "attention_common.h"
 #include <hip/hip_ext.h>
+#include <type_traits>
 
 #ifndef MP_SCAN_BPW
 #define MP_SCAN_BPW 1
@@ -73,7 +74,8 @@ template <int ET> constexpr int kGatherList = kRangeBlocks * kBlockKeys + 4 * kG
 // the G wavefronts of a workgroup serve the G heads of one KV head on the same run.  The ballots of
 // sixteen blocks at a time are expanded into an index list in LDS by a prefix sum; full batches of rows are taken
 // from its front, and what is left waits for the next sixteen blocks.  The keys of the static set T are
-// dealt over the runs (key j to run j mod runs) and join the last batch.
+// dealt over the runs (key j to run j mod runs) and join the last batch, or they have wavefronts of their own behind those of the runs
+// (plan_gather).  kFull = false: runs of one piece, everything goes through the code of the last batch.
 // Bound by the rows it gathers (random 256-byte rows) and by the vector unit.  512 heads x 131072 keys, (10,170), 1.3
 // million rows: 152 us (643 MB at 4.2 TB/s, vector unit 73 % busy) with a wavefront for each 1024 keys, about 20 of the 32
 // rows of a batch and workgroups of their own for T; now 122 us (5.3 TB/s): the estimator's arithmetic, once per
@@ -81,7 +83,7 @@ template <int ET> constexpr int kGatherList = kRangeBlocks * kBlockKeys + 4 * kG
 // Four wavefronts per SIMD (128 registers; at 141, three, it was 40 % slower); the lists are as many as the workgroup has
 // wavefronts, so that sixteen fit a compute unit with few heads too (room for eight lists in a workgroup of one
 // wavefront: nine fitted; 512 heads of 512 KV heads x 16384 keys, (10,150), the step 40.3 us, now 36.6).
-template <int ET>
+template <int ET, bool kFull>
 __global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
   constexpr bool FP32 = ET == kFP32;
   constexpr int kIt = kGatherIters<ET>, kBatch = 4 * kIt;
@@ -93,20 +95,37 @@ __global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
   const int G = a.Hq / a.Hkv;
   const int64_t bh = (int64_t)b * a.Hq + (int64_t)g * G + wave;
   const int64_t nblk = key_blocks(c.n);
+  // wavefronts behind those of the runs take static keys only
+  const int nruns = (int)gridDim.x - a.g_static_runs;
+  const bool own = run >= nruns;
+  const int run_blocks = own ? 0 : a.g_run_blocks;
   const int64_t blk0 = (int64_t)run * a.g_run_blocks;
   uint16_t* list = lists + wave * kGatherList<ET>;
   HeadVectors<FP32> hv;
   request_head_vectors<FP32>(a, unit, bh, hv);
-  const int nruns = gridDim.x, nst = static_share(c, run, nruns);
   const uint64_t* masks = a.masks + bh * nblk;
   auto ballots = [&](int at) {                             // lane i < 16: block blk0 + at + i
-    return lane < kRangeBlocks && at < a.g_run_blocks && blk0 + at + lane < nblk ? masks[blk0 + at + lane] : 0ull;
+    return lane < kRangeBlocks && at < run_blocks && blk0 + at + lane < nblk ? masks[blk0 + at + lane] : 0ull;
   };
   GatherState st;
   int have = 0;                                            // keys in the list
   uint64_t next = ballots(0);
+  int64_t s0 = run;                                        // static keys of this wavefront: s0, s0 + sstep, ...
+  int sstep = nruns, nst = a.g_static_runs > 0 ? 0 : static_share(c, run, nruns);
+  if (own) {
+    s0 = (int64_t)(run - nruns) * a.g_static_keys;
+    sstep = 1;
+    const int64_t left = c.n_static - s0;
+    nst = left <= 0 ? 0 : (left < a.g_static_keys ? (int)left : a.g_static_keys);
+  }
+  if (kFull && own) {
+    const int full = nst / kBatch * kBatch;
+    if (full > 0) gather_estimate_keys<ET, kIt, true>(st, a, unit, full, 0, hv, [&](int cc) { return static_key(a, c, s0 + cc); });
+    s0 += full;
+    nst -= full;
+  }
 #pragma unroll 1
-  for (int at = 0; at < a.g_run_blocks; at += kRangeBlocks) {
+  for (int at = 0; at < run_blocks; at += kRangeBlocks) {
     uint64_t m = next;
     next = ballots(at + kRangeBlocks);
     const int pc = __popcll(m);
@@ -121,6 +140,7 @@ __global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
     have += __builtin_amdgcn_readlane(incl, kRangeBlocks - 1);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
+    if (!kFull) continue;
     const int full = have / kBatch * kBatch, left = have - full;
     if (full > 0)
       gather_estimate_keys<ET, kIt, true>(st, a, unit, full, full, hv, [&](int cc) { return blk0 * kBlockKeys + (int64_t)list[cc]; });
@@ -133,7 +153,9 @@ __global__ __launch_bounds__(512, 4) void gather_estimate_kernel(AttnArgs a) {
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __builtin_amdgcn_wave_barrier();
   gather_estimate_keys<ET, kIt, false>(st, a, unit, have + nst, have, hv, [&](int cc) {
-    return cc < have ? blk0 * kBlockKeys + (int64_t)list[cc] : static_key(a, c, run + (int64_t)(cc - have) * nruns);
+    const int sampled = list[cc < have ? cc : 0];            // (read for static keys, too: no branch between the reads of a batch)
+    const int64_t fixed = static_key(a, c, s0 + (int64_t)(cc - have) * sstep);
+    return cc < have ? blk0 * kBlockKeys + sampled : fixed;
   });
   store_partial(finish_gather(st), a.partial + (bh * a.nranges + run) * kPartialStride);
 }
@@ -455,16 +477,6 @@ static void launch_scan_gather_for(const AttnArgs& a, dim3 grid, hipStream_t s, 
   }
 }
 
-// Key blocks of a gather wavefront, in pieces of kRangeBlocks.  A wavefront that takes several pieces fills its
-// batches of rows (a piece samples about 20 keys of a batch's 32 at 2 %), asks for the next piece's ballots early
-// and leaves one partial: as many pieces as bring all wavefronts into one round, sixteen per compute unit.
-// Measured (us per step through tables, pieces 1 | 2 | 3 | 4 | 8): 512 heads x 131072 keys, (10,170), - | 181 | - | 166.5 |
-// 161.8 (16: 162.5); (10,150): 512 x 32768 62.9 | 59.6 | 59.3 | 58.2 | 58.0; 128 x 65536
-// 43.6 | 42.4 | 42.5 | 43.1 | 47.4; 64 x 98304 42.4 | 40.6 | 39.2 | 40.6 | 48.6; 256 x 20000, (9,120), 46.0 | 45.6 | 45.5 | 49.5 |
-// 60.8; 512 x 30000, (9,100), six pieces (five runs, 1.25 workgroups per compute unit) 86.6, four 78.0.
-constexpr int64_t kGatherWaves = 16 * kNumCU;
-constexpr int64_t kMaxGatherPieces = 8;
-
 static hipError_t launch_scan_gather(const AttnArgs& a, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
   const dim3 grid((unsigned)a.f_nranges, (unsigned)(a.B * a.Hkv));
 #define MP_TUNED(KT, LL) if (a.K == KT && a.L == LL) launch_scan_gather_for<KT, words_of(LL), tail_of(LL)>(a, grid, s, start, stop); else
@@ -529,18 +541,24 @@ hipError_t launch_sampled_attention(const AttnArgs& a, const TableArgs* tables, 
     return hipGetLastError();
   }
   AttnArgs b = a;                                          // (no more partials than a.nranges, for which there is room)
-  const int64_t nblk = key_blocks(a.n);
-  int64_t pieces = (heads * ((nblk + kRangeBlocks - 1) / kRangeBlocks) + kGatherWaves - 1) / kGatherWaves;
-  pieces = pieces < 1 ? 1 : (pieces > kMaxGatherPieces ? kMaxGatherPieces : pieces);
-  b.g_run_blocks = (int)pieces * kRangeBlocks;
-  b.nranges = (int)((nblk + b.g_run_blocks - 1) / b.g_run_blocks);
-  const dim3 grid((unsigned)b.nranges, (unsigned)(a.B * a.Hkv)), block(64 * (a.Hq / a.Hkv));
+  const int G = a.Hq / a.Hkv;
+  const GatherPlan plan = plan_gather(a.B * a.Hkv, G, key_blocks(a.n), a.n_static, a.tau);
+  b.g_run_blocks = plan.run_blocks;
+  b.g_static_runs = plan.static_runs;
+  b.g_static_keys = plan.static_keys;
+  b.nranges = plan.runs + plan.static_runs;
+  const dim3 grid((unsigned)b.nranges, (unsigned)(a.B * a.Hkv)), block(64 * G);
   auto gather = [&](auto kernel, int list) {
-    launch_timed_lds(kernel, grid, block, (size_t)(a.Hq / a.Hkv) * list * sizeof(uint16_t), s, nullptr, ev ? ev[2] : nullptr, b);
+    launch_timed_lds(kernel, grid, block, (size_t)G * list * sizeof(uint16_t), s, nullptr, ev ? ev[2] : nullptr, b);
   };
-  if (a.is_fp32) gather(gather_estimate_kernel<kFP32>, kGatherList<kFP32>);
-  else if (a.kv_fp8) gather(gather_estimate_kernel<kFP8>, kGatherList<kFP8>);
-  else gather(gather_estimate_kernel<kBF16>, kGatherList<kBF16>);
+  auto gather_as = [&](auto whole) {
+    constexpr bool kFull = decltype(whole)::value;
+    if (a.is_fp32) gather(gather_estimate_kernel<kFP32, kFull>, kGatherList<kFP32>);
+    else if (a.kv_fp8) gather(gather_estimate_kernel<kFP8, kFull>, kGatherList<kFP8>);
+    else gather(gather_estimate_kernel<kBF16, kFull>, kGatherList<kBF16>);
+  };
+  if (plan.full) gather_as(std::true_type{});
+  else gather_as(std::false_type{});
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_merge(b, heads, s, ev ? ev[4] : nullptr, ev ? ev[3] : nullptr);
 }

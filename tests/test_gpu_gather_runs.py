@@ -17,7 +17,26 @@ pytestmark = pytest.mark.gpu
     (16, 64, 8, 35000, 9, 120, 2, "bf16", "fp8", 34944, 300), # eight pieces a run, most runs empty
 ])
 def test_runs_of_several_pieces(b, hq, hkv, n, K, L, tau, dtype, kv, indexed, live):
-    print(f"[case] gather runs B={b} Hq={hq} n={n} K={K} L={L} tau={tau} {dtype} {kv} live={live}", flush=True)
+    _compare(b, hq, hkv, n, K, L, tau, dtype, kv, indexed, live)
+
+
+# static sets with wavefronts of their own, and the forms without code for full batches
+@pytest.mark.parametrize("b,hq,hkv,n,K,L,tau,dtype,kv,indexed,live,sink,local", [
+    (8, 64, 8, 1000, 10, 150, 2, "bf16", "", 960, 0, 4, 900),         # of 64 keys
+    (1, 32, 8, 9000, 10, 150, 3, "bf16", "", 8960, 8000, 31, 4100),   # the length in device memory
+    (1, 32, 8, 9000, 10, 150, 3, "bf16", "fp8", 8960, 777, 16, 4096), # shorter than the static set
+    (1, 32, 8, 2500, 7, 150, 3, "bf16", "", 2432, 0, 30, 200),        # of 32 keys; lists of several batches
+    (1, 16, 8, 3333, 9, 75, 3, "fp32", "", 3328, 0, 333, 3000),       # every key static
+    (65, 4, 4, 200, 10, 100, 2, "bf16", "fp8", 192, 0, 1, 64),        # 65 keys for one run
+    (16, 64, 8, 9000, 10, 150, 2, "bf16", "", 8960, 0, 0, 3000),      # of 128 keys, three pieces a run
+    (1, 32, 8, 16384, 6, 100, 3, "fp32", "", 16384, 16001, 4, 64),    # dealt over the runs, most keys sampled
+])
+def test_large_static_sets(b, hq, hkv, n, K, L, tau, dtype, kv, indexed, live, sink, local):
+    _compare(b, hq, hkv, n, K, L, tau, dtype, kv, indexed, live, n_sink=sink, n_local=local)
+
+
+def _compare(b, hq, hkv, n, K, L, tau, dtype, kv, indexed, live, **static):
+    print(f"[case] gather runs B={b} Hq={hq} n={n} K={K} L={L} tau={tau} {dtype} {kv} live={live} {static}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(n + K)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")   # noqa: E731
     at = torch.float32 if dtype == "fp32" else torch.bfloat16
@@ -29,7 +48,7 @@ def test_runs_of_several_pieces(b, hq, hkv, n, K, L, tau, dtype, kv, indexed, li
         Kc[i] = (rnd(hkv, n, 128) + mu[i, :, None]).to(store)
         Vc[i] = rnd(hkv, n, 128).to(store)
     q, W = rnd(b, hq, 128).to(at), rnd(128, K * L).to(at)
-    same = dict(batch=b, n_q_heads=hq, n_kv_heads=hkv, K=K, L=L, n_cap=n, dtype=dtype, min_hits=tau, kv_dtype=kv)
+    same = dict(batch=b, n_q_heads=hq, n_kv_heads=hkv, K=K, L=L, n_cap=n, dtype=dtype, min_hits=tau, kv_dtype=kv, **static)
     n_dev = torch.tensor([live], dtype=torch.int64, device="cuda") if live else None
     p = mp.make_params(n_ctx=n, n_ctx_dev=n_dev, **same) if live else mp.make_params(n_ctx=n, **same)
     kc, qc, ws = mp.alloc_key_codes(p), mp.alloc_query_codes(p), mp.alloc_workspace(p)
