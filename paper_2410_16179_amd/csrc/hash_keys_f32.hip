@@ -20,9 +20,9 @@
 //
 // A chain of latencies, so all 64 elements of a lane's column are requested at once, together with the keys, which
 // wait in LDS (16 at a time, the next ones requested while those before them are multiplied, cost a round trip to
-// L2 each).  4096 keys x 600 columns (one head, (8,75)): 24.6 us with four wavefronts, two tiles each and the
-// keys in registers, 19.3 now.  8 x 2048 keys x 1500 columns: mean and codes 120 us, 108 now (6.7 GFLOP: 43 us at the rate of the
-// instruction).
+// L2 each).  us of the kernel, four wavefronts with two tiles each and the keys in registers | now: 4096 keys x 600 columns
+// (one head, (8,75)) 22.9 | 16.5; 8 x 2048 keys x 1500 columns 112.8 | 96.8 (6.3 GFLOP: 40 us at the rate of the
+// instruction; workgroups of 64 keys are one per compute unit there, their list taking 4096 K bytes of LDS, and spill five registers).
 #include "mp_common.h"
 #include "exact_dot.h"
 #include "device_utils.h"
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(1024, 4) void hash_keys_f32_kernel(HashDirectArgs a
     if (tid == 0) count = 0;
 
     // ---- A operand: this lane's column of the wavefront's tile, lane half hh holds the elements 64 hh ..
-    // 64 hh + 63; half of them are requested here and travel together with the keys ----
+    // 64 hh + 63; all of them are requested here and travel together with the keys ----
     const int tile = wave;
     const int j = 32 * w * K + 32 * tile + kap;
     const bool col_ok = j < ncol;
@@ -250,19 +250,16 @@ __global__ __launch_bounds__(1024, 4) void hash_keys_f32_kernel(HashDirectArgs a
 
 // Keys [first_key, first_key + n_keys) of every unit (n_keys > 0).
 hipError_t launch_hash_keys_f32(const HashDirectArgs& a, int units, hipStream_t s) {
+  // n_cap <= 2^31 keys: below 2^31 jobs
+  auto tiles_of = [&](int keys) { return (a.first_key + a.n_keys - 1) / keys - a.first_key / keys + 1; };
+  auto jobs_of = [&](int keys) { return tiles_of(keys) * table_words(a.L); };
   auto go = [&](auto kernel, int keys) {
-    const int64_t tiles = (a.first_key + a.n_keys - 1) / keys - a.first_key / keys + 1;
-    const int64_t jobs = tiles * table_words(a.L);         // n_cap <= 2^31 keys: below 2^31
+    const int64_t jobs = jobs_of(keys);
     const int64_t most = (int64_t)1 << 21;                 // (gridDim.x * 1024 threads below 2^32; the kernel walks the rest)
     hipLaunchKernelGGL(kernel, dim3((unsigned)(jobs < most ? jobs : most), (unsigned)units), dim3(64 * a.K), hash_f32_lds(a.K, keys), s, a,
-                       (uint32_t)tiles, (uint32_t)jobs);
+                       (uint32_t)tiles_of(keys), (uint32_t)jobs);
   };
-  // 64 keys as soon as workgroups of 32 are more than one per compute unit: a projector element then serves two
-  // matrix instructions.  Mean and codes, us, 32 | 64 keys: 128 workgroups of 32 (1024 keys, (9,110)) 18.4 | 26.2; 256
-  // (4096, (16,64)) 23.2 | 33.0; 384 (4096, (8,75)) 24.0 | 23.2; 896 (8 x 501, (10,220)) 55.6 | 48.6; 2048 (4 x 4096,
-  // (4,100)) 42.5 | 41.9; 2560 (8 x 2048, (10,150)) 126.9 | 107.6.
-  const int64_t tiles32 = (a.first_key + a.n_keys - 1) / 32 - a.first_key / 32 + 1;
-  if (tiles32 * table_words(a.L) * units > kNumCU) go(hash_keys_f32_kernel<2>, 64);
+  if (hash_f32_keys(a.K, jobs_of(32) * units, jobs_of(64) * units) == 64) go(hash_keys_f32_kernel<2>, 64);
   else go(hash_keys_f32_kernel<1>, 32);
   return hipGetLastError();
 }

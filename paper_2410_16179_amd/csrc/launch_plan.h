@@ -57,4 +57,15 @@ inline GatherPlan plan_gather(int units, int G, int64_t nblk, int64_t n_static, 
   return p;
 }
 
+// Float32 key hashing: keys of a workgroup, 32 or 64 (in which a projector element serves two matrix instructions), by the
+// workgroups of either kind that the fullest compute unit gets: one of 64 keys takes about 1.75 times one of 32.  Below
+// five bits per table 32 throughout: a workgroup is K wavefronts, and many small ones hide each other's latencies.
+// us of the kernel, workgroups of 32: 32 keys | 64 keys: 257 (4,32) 11.1 | 12.5; 512 (2,32) 11.4 | 13.6; 1000 (2,64) 12.5 | 18.2; 8192 (4,100)
+// 114 | 121; 282 (5,75) 15.6 | 16.0, 1002 35.7 | 25.4; 320 (10,150) 24.9 | 20.9, 515 35.1 | 39.2, 770 46.3 | 39.7, 2560 115.9 | 97.5;
+// 384 (8,75) 16.9 | 16.5, 768 24.2 | 27.3, 1536 44.5 | 40.1; 640 (9,100) 35.7 | 39.0, 1272 58.8 | 57.6; 258 (16,64) 29.8 | 26.1, 750 46.2 | 50.8.
+inline int hash_f32_keys(int K, int64_t groups32, int64_t groups64) {
+  auto fullest = [](int64_t groups) { return (groups + kNumCU - 1) / kNumCU; };
+  return K >= 5 && 7 * fullest(groups64) < 4 * fullest(groups32) ? 64 : 32;
+}
+
 }  // namespace mp

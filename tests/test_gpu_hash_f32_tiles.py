@@ -1,4 +1,4 @@
-"""Float32 key hashing in workgroups of 64 keys (more than 256 workgroups of 32) and of 32: ragged ends, one to
+"""Float32 key hashing in workgroups of 64 keys (five bits per table or more, more than 256 workgroups of 32) and of 32: ragged ends, one to
 sixteen bits per table, full and short last table groups, against the oracle bit for bit."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("units,n,first,K,L", [
     (3, 1700, 0, 8, 75), (3, 1701, 33, 9, 65), (5, 1003, 95, 16, 64), (5, 1690, 64, 1, 33), (4, 901, 1, 11, 96),
-    (2, 190, 31, 10, 150)])                                  # (the last one: workgroups of 32 keys)
+    (2, 190, 31, 10, 150)])                                  # (one bit per table and the last one: workgroups of 32 keys)
 def test_tiles(oracle, units, n, first, K, L):
     print(f"[case] f32 tiles units={units} n={n} first={first} K={K} L={L}", flush=True)
     rng = np.random.default_rng(K * L + n)

@@ -13,6 +13,7 @@ void gather(int units, int G, long nblk, long n_static, int tau, int* got) {
   const mp::GatherPlan p = mp::plan_gather(units, G, nblk, n_static, tau);
   got[0] = p.run_blocks; got[1] = p.runs; got[2] = p.static_runs; got[3] = p.static_keys; got[4] = p.full;
 }
+int hash_f32(int K, long groups32, long groups64) { return mp::hash_f32_keys(K, groups32, groups64); }
 }
 """
 
@@ -66,3 +67,12 @@ def test_gather_forms_at_the_sizes_of_its_gpu_test(plan):
     assert form(260, 1, 200, 65) == (1, (3, 32), False)
     assert form(128, 8, 9000, 3000) == (3, (24, 128), True)
     assert form(8, 4, 16384, 68, tau=3) == (1, 0, False)
+
+
+@pytest.mark.parametrize("K,groups32,keys", [
+    (1, 256, 32), (2, 512, 32), (2, 1000, 32), (3, 2550, 32), (4, 257, 32), (4, 8192, 32),   # narrow tables: 32 throughout
+    (5, 1002, 64), (8, 256, 32), (8, 384, 64), (8, 642, 32), (8, 1536, 64), (9, 760, 32), (10, 320, 64), (10, 515, 32), (10, 770, 64),
+    (10, 2560, 64), (16, 258, 64), (16, 750, 32)])
+def test_keys_of_a_float32_hashing_workgroup(plan, K, groups32, keys):
+    # the faster of the two forms where they differ by more than a tenth; either where they do not
+    assert plan.hash_f32(K, ctypes.c_long(groups32), ctypes.c_long((groups32 + 1) // 2)) == keys
