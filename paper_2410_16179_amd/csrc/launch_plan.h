@@ -57,6 +57,20 @@ inline GatherPlan plan_gather(int units, int G, int64_t nblk, int64_t n_static, 
   return p;
 }
 
+// One-launch scan + gather: most workgroups of one head each for which a workgroup serves one of the G > 1 heads of a KV
+// head.  Where few workgroups share the chip a wavefront then compares its blocks with one head's code, not with G one after
+// the other, and gathers for one head (of five to eight heads a wavefront gathers for two); beyond that reading the
+// codes G times costs more.  tuned: table sets with a scan of their own.  us of scan + gather and merge, G heads a
+// workgroup | one (workgroups of one head): G = 2, 8 KV heads, (10,150): 4096 keys 10.5 | 9.9 (256), 6144 10.5 | 10.4 (384), 8192 10.5 | 10.9 (512);
+// (9,110) 8192 13.5 | 13.5 (512).  G = 3: 4096 10.6 | 10.3 (384), (8,75), float32, 5400 12.8 | 12.0 (528); step, 10000 19.2 | 20.0 (960).
+// G = 4: 2048 step 19.0 | 16.7 (256), 6144 11.1 | 11.1 (768), step 10000 19.8 | 21.1 (1280); any K and L: 4096 step 20.8 | 19.5 (512), 6144
+// 13.0 | 13.8 (768).  G = 5: 4096 13.9 | 10.8 (640), 6400 13.9 | 12.5 (1000), (10,100) 16.5 | 15.1; G = 6: (9,120) 5400 15.3 | 12.3 (1056);
+// G = 7, 4 KV heads: 9000 14.5 | 12.2 (1008); G = 8: 4000 14.9 | 12.1 (1024), (10,100) 16.8 | 15.0, step 8000 25.2 | 26.0 (2048).
+inline int64_t head_per_workgroup_limit(bool tuned, int G) {
+  if (G > 4) return 4 * kNumCU;
+  return (G == 4 && tuned ? 3 : (G == 2 ? 1 : 2)) * kNumCU;
+}
+
 // Float32 key hashing: keys of a workgroup, 32 or 64 (in which a projector element serves two matrix instructions), by the
 // workgroups of either kind that the fullest compute unit gets: one of 64 keys takes about 1.75 times one of 32.  Below
 // five bits per table 32 throughout: a workgroup is K wavefronts, and many small ones hide each other's latencies.

@@ -448,15 +448,9 @@ static void launch_scan_gather_as(const AttnArgs& a, dim3 grid, hipStream_t s, h
   const dim3 block(256);
   // (any K and L: 127 registers, four workgroups fit either way)
   constexpr int kOcc = KT == 0 ? 4 : 3;
-  const unsigned G = (unsigned)(a.Hq / a.Hkv);
-  // A workgroup for every head where few workgroups share the chip: a wavefront then compares its blocks with one
-  // head's code, not with G one after the other, and gathers for one head (of five to eight heads a wavefront
-  // gathers for two).  Measured, us per step, G heads a workgroup | one (workgroups of one head): 8 KV heads, G = 4: 2048 keys 18.96 | 16.65
-  // (256), 6144 18.3 | 17.5 (768), 10000 19.8 | 21.1 (1280); G = 8: 4000 25.3 | 20.65 (1024), 8000 25.2 | 26.0 (2048); G = 3: 10000
-  // 19.2 | 20.0 (960), 5000 18.65 | 17.9 (480); G = 2: 4096 17.9 | 16.8 (256); any K and L: G = 8, 2048 keys 27.5 | 20.7 (512), G = 4, 4096 20.8 | 19.5 (512).
-  const int64_t most = G > 4 ? 4 * kNumCU : (G == 4 ? 3 * kNumCU : 2 * kNumCU);
-  if (!DBG && G > 1 && (int64_t)grid.x * grid.y * G <= most)
-    launch_timed(scan_gather_kernel<KT, KT == 0 ? 1 : WDT, LT, ET, false, kOcc, true>, dim3(grid.x, grid.y, G), block, s, start, stop, a);
+  const int G = a.Hq / a.Hkv;
+  if (!DBG && G > 1 && (int64_t)grid.x * grid.y * G <= head_per_workgroup_limit(KT != 0, G))
+    launch_timed(scan_gather_kernel<KT, KT == 0 ? 1 : WDT, LT, ET, false, kOcc, true>, dim3(grid.x, grid.y, (unsigned)G), block, s, start, stop, a);
   else if (KT == 0 || a.f_touch) launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, 4>, grid, block, s, start, stop, a);
   else launch_timed(scan_gather_kernel<KT, WDT, LT, ET, DBG, kOcc>, grid, block, s, start, stop, a);
 }

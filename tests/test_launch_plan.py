@@ -13,6 +13,7 @@ void gather(int units, int G, long nblk, long n_static, int tau, int* got) {
   const mp::GatherPlan p = mp::plan_gather(units, G, nblk, n_static, tau);
   got[0] = p.run_blocks; got[1] = p.runs; got[2] = p.static_runs; got[3] = p.static_keys; got[4] = p.full;
 }
+long head_limit(int tuned, int G) { return mp::head_per_workgroup_limit(tuned, G); }
 int hash_f32(int K, long groups32, long groups64) { return mp::hash_f32_keys(K, groups32, groups64); }
 }
 """
@@ -76,3 +77,15 @@ def test_gather_forms_at_the_sizes_of_its_gpu_test(plan):
 def test_keys_of_a_float32_hashing_workgroup(plan, K, groups32, keys):
     # the faster of the two forms where they differ by more than a tenth; either where they do not
     assert plan.hash_f32(K, ctypes.c_long(groups32), ctypes.c_long((groups32 + 1) // 2)) == keys
+
+
+@pytest.mark.parametrize("units,G,n,tuned,one", [
+    # the sizes of tests/test_gpu_head_per_workgroup.py (up to 780 workgroups a run is four key blocks)
+    (1, 4, 70, True, True), (8, 2, 1001, True, True), (8, 4, 2048, True, True), (8, 3, 1300, True, True), (2, 8, 4096, True, True), (4, 5, 777, True, True),
+    (1, 7, 1500, False, True), (4, 3, 515, False, True), (8, 5, 1600, False, True), (8, 4, 6144, True, True), (8, 4, 6209, True, False), (1, 2, 3, True, True),
+    # and those on which the limits rest
+    (8, 2, 4096, True, True), (8, 2, 8192, True, False), (8, 2, 8192, False, False), (8, 3, 10000, True, False), (8, 4, 10000, True, False),
+    (8, 4, 4096, False, True), (8, 4, 6144, False, False), (8, 5, 6400, True, True), (4, 7, 9000, True, True), (8, 8, 4000, False, True), (8, 8, 8000, True, False)])
+def test_head_per_workgroup(plan, units, G, n, tuned, one):
+    plan.head_limit.restype = ctypes.c_long
+    assert (units * (-(-n // 256)) * G <= plan.head_limit(int(tuned), G)) == one
