@@ -1,6 +1,7 @@
 """The one-launch scan + gather of short contexts, a workgroup for each query head, against its form with debug
 outputs (a workgroup for the heads of a KV head) and the oracle: two to eight heads per KV head, compiled and other
-table sets, contexts of a few keys, on either side of the limit in workgroups, and lengths in device memory."""
+table sets, contexts of a few keys, on either side of the limit in workgroups, and lengths in device memory with
+strided caches."""
 import numpy as np
 import pytest
 import torch
@@ -34,3 +35,25 @@ def test_head_per_workgroup(oracle, B, Hq, Hkv, n, K, L, tau, dtype, kv):
     ref = oracle.decode_step(data["q"], data["K"], data["V"], data["W"], K, L, mu=mu, min_hits=tau, heads=[(0, 0), last])
     for b, h in {(0, 0), last}:
         assert rel_err(one["out"][b, h][None], ref["out"][b, h][None]) <= TOL
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,n,K,L,dtype,kv", [
+    (1, 32, 8, 2000, 10, 150, "bf16", ""), (2, 10, 2, 1500, 9, 110, "bf16", "fp8"), (1, 8, 1, 3000, 8, 75, "fp32", ""), (1, 6, 3, 900, 10, 100, "bf16", "")])
+def test_length_in_device_memory_and_strided_caches(B, Hq, Hkv, n, K, L, dtype, kv):
+    w = wl.Workload("heads", B, Hq, Hkv, n, K, L, dtype, (8,), min_hits=2, kv=kv)
+    data = wl.generate(w)
+    live = torch.tensor([n], dtype=torch.int64, device="cuda")
+    same = dict(K=K, L=L, dtype=dtype, Kc=data["K"], Vc=data["V"], q=data["q"], W=data["W"], min_hits=2, kv=kv)
+    strided = Session(**same, n_ctx_dev=live, layout="token_major")
+    strided.set_mu(data["K"].mean(2).astype(np.float32))
+    strided.hash_keys()
+    strided.hash_query()
+    for m in (n, n - 1, n // 2 + 7, 64, 5):
+        print(f"[case] head per workgroup Hq={Hq} Hkv={Hkv} n={m} of {n} K={K} L={L} {dtype} {kv} strided", flush=True)
+        live.fill_(m)
+        strided.ws.fill_(255)
+        got = strided.attend(debug=False)["out"]
+        # the same length given by the host, dense caches, a workgroup for the heads of a KV head
+        dense = Session(**same, n_ctx=m)
+        dense.mu, dense.key_codes, dense.q_codes = strided.mu, strided.key_codes, strided.q_codes
+        assert rel_err(got, dense.attend()["out"]) <= 1e-5
