@@ -56,4 +56,8 @@ def test_length_in_device_memory_and_strided_caches(B, Hq, Hkv, n, K, L, dtype, 
         # the same length given by the host, dense caches, a workgroup for the heads of a KV head
         dense = Session(**same, n_ctx=m)
         dense.mu, dense.key_codes, dense.q_codes = strided.mu, strided.key_codes, strided.q_codes
-        assert rel_err(got, dense.attend()["out"]) <= 1e-5
+        want = dense.attend()["out"]
+        if m == n:                                           # the same runs: the same sums in the same order
+            np.testing.assert_array_equal(got, want)
+        else:
+            assert rel_err(got, want) <= 1e-5
